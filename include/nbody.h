@@ -105,7 +105,8 @@ int nb_set_stream(nb_ctx *ctx, void *hip_stream);
  * NB_EINVAL (message in nb_last_error) once for any such entries and clears
  * the bit; NB_OK otherwise; NB_EDEVICE on a failed synchronisation.
  * It also checks the context's work-queue counters, which every force
- * launch leaves at zero: non-zero counters mean that calls overlapped on the
+ * launch leaves at zero (launches of no more work items than workgroups do
+ * not use them): non-zero counters mean that calls overlapped on the
  * device (see the conventions above).  They are then cleared, so later calls
  * are correct again, and NB_EINVAL reports that results since the last
  * nb_sync cannot be trusted. */

@@ -61,6 +61,7 @@
 
 #include "nb_internal.h"
 #include "hermite_step.h"
+#include "work_queue.h"
 
 namespace nb {
 namespace {
@@ -490,89 +491,6 @@ __host__ __device__ inline int64_t chunk_len(int64_t n, int S, int tile = kTile)
   return ((per + tile - 1) / tile) * tile;
 }
 
-// Work queues of the persistent force grids.  The items -- (i-block,
-// j-chunk) pairs in chunk-major order -- are cut into kXcd equal ranges, one
-// per XCD: the hardware hands workgroups to the chip's 8 XCDs round-robin by
-// blockIdx, so range x is worked by the workgroups on XCD x, and that XCD's
-// L2 holds only the j-chunks of its own range.  Within a range, workgroups
-// take items from a counter in device memory (wq[x]), so a faster compute
-// unit takes more; once its own range is exhausted, a workgroup takes from
-// the other ranges in turn, so the XCDs (whose clocks differ by a few
-// percent) also finish together.  Each item is computed the same way
-// whichever workgroup takes it: results do not depend on the assignment.
-// wq[0..kXcd-1] are the range counters and wq[kXcd] counts finished
-// workgroups; all are zero before a launch and the last workgroup to finish
-// sets them back to zero.  Without a queue (wq null) the grid strides over
-// the items in the same order.
-constexpr int kXcd = 8;
-constexpr int kQueueWords = kXcd + 1;
-static_assert(kQueueWords <= kWorkQueueWords, "work queue larger than its buffer");
-
-// Thread 0 turns an own-range take into an item: `own` is the counter value
-// the take returned.  When that range is exhausted it reads every range's
-// counter at once (independent loads, one round of latency: device-scope
-// atomics cost about a microsecond each, so the ranges are not visited one
-// by one) and takes from the first range with items left, in the order
-// x0 + 1, x0 + 2, ...  Returns the item, or `items` once all are exhausted.
-__device__ __forceinline__ int64_t queue_pick(unsigned int* wq, int64_t items, unsigned int own) {
-  const int x0 = blockIdx.x % kXcd;
-  const int64_t lo0 = items * x0 / kXcd, len0 = items * (x0 + 1) / kXcd - lo0;
-  if ((int64_t)own < len0) return lo0 + own;
-  for (int attempt = 0; attempt < kXcd; ++attempt) {
-    unsigned int cnt[kXcd];
-#pragma unroll
-    for (int x = 0; x < kXcd; ++x) cnt[x] = __hip_atomic_load(&wq[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    int pick = -1, best = kXcd;
-#pragma unroll
-    for (int x = 0; x < kXcd; ++x) {
-      const int64_t len = items * (x + 1) / kXcd - items * x / kXcd;
-      const int order = (x - x0 - 1 + 2 * kXcd) % kXcd;  // 0 for range x0 + 1
-      if ((int64_t)cnt[x] < len && order < best) {
-        best = order;
-        pick = x;
-      }
-    }
-    if (pick < 0) return items;
-    const int64_t lo = items * pick / kXcd, len = items * (pick + 1) / kXcd - lo;
-    const int64_t k = atomicAdd(&wq[pick], 1u);
-    if (k < len) return lo + k;
-  }
-  return items;
-}
-
-// The first item of a workgroup (w_stride: its item without a queue).
-__device__ __forceinline__ int64_t queue_take(unsigned int* wq, unsigned int& slot, int64_t items,
-                                              int64_t w_stride) {
-  if (!wq) return w_stride;
-  if (threadIdx.x == 0) slot = (unsigned int)queue_pick(wq, items, atomicAdd(&wq[blockIdx.x % kXcd], 1u));
-  __syncthreads();
-  // one value for the whole wave: read into a scalar register, so everything
-  // derived from the item (chunk bounds, record addresses) stays uniform
-  return (int64_t)(unsigned int)__builtin_amdgcn_readfirstlane((int)slot);
-}
-
-// A workgroup's next item (w_stride: its next item without a queue).
-__device__ __forceinline__ int64_t queue_next(unsigned int* wq, unsigned int& slot, int64_t items, int64_t w_stride) {
-  if (!wq) return w_stride;
-  __syncthreads();  // every thread has read `slot` before it is replaced
-  if (threadIdx.x == 0) slot = (unsigned int)queue_pick(wq, items, atomicAdd(&wq[blockIdx.x % kXcd], 1u));
-  __syncthreads();
-  return (int64_t)(unsigned int)__builtin_amdgcn_readfirstlane((int)slot);
-}
-
-// Only the first min(items, grid) workgroups take part in a launch's queue
-// (one item each at least; the rest return at once, so a launch sized for
-// its largest count costs little at a small one).  Every member calls
-// queue_done once, after its last queue_next; the last one resets the queue.
-__device__ __forceinline__ bool queue_member(int64_t items) { return (int64_t)blockIdx.x < items; }
-
-__device__ __forceinline__ void queue_done(unsigned int* wq, int64_t items) {
-  const unsigned int members = items < (int64_t)gridDim.x ? (unsigned int)items : gridDim.x;
-  if (wq && threadIdx.x == 0 && atomicAdd(&wq[kXcd], 1u) == members - 1) {
-    for (int x = 0; x < kQueueWords; ++x) atomicExch(&wq[x], 0u);
-  }
-}
-
 // Shared body: one workgroup processes one (i-block, j-chunk) item.
 // Outputs: final rows (acc/jerk/pot at out_row0 + k) when `final_out`,
 // otherwise partial sums part[c * n_act + k] for c = 0..6.
@@ -710,7 +628,7 @@ __device__ __forceinline__ void run_items(typename P::template JTileT<T>& tile, 
   const int64_t items = n_iblk * S;
   const int64_t clen = chunk_len(a.n, S, T);
   if (!queue_member(items)) return;
-  int64_t w = queue_take(a.wq, slot, items, blockIdx.x);
+  int64_t w = queue_first(a.wq, items);
   while (w < items) {
     const int64_t chunk = w / n_iblk;
     const int64_t iblk = w - chunk * n_iblk;
@@ -1061,7 +979,7 @@ __global__ __launch_bounds__(WG, (SjWaves<P, K>::value)) void k_forces_sj(ForceA
   const int64_t clen = chunk_len(a.n, S);
   __shared__ unsigned int slot;
   if (!queue_member(items)) return;
-  int64_t w = queue_take(a.wq, slot, items, blockIdx.x);
+  int64_t w = queue_first(a.wq, items);
   while (w < items) {
     const int64_t chunk = w / n_iblk;
     const int64_t iblk = w - chunk * n_iblk;
@@ -1201,7 +1119,7 @@ __global__ __launch_bounds__(kWG, (K == 2 ? 5 : 1)) void k_forces_hy(ForceArgs a
   const int64_t clen = chunk_len(a.n, S);
   __shared__ unsigned int slot;
   if (!queue_member(items)) return;
-  int64_t w = queue_take(a.wq, slot, items, blockIdx.x);
+  int64_t w = queue_first(a.wq, items);
   while (w < items) {
     const int64_t chunk = w / n_iblk;
     const int64_t iblk = w - chunk * n_iblk;

@@ -16,7 +16,8 @@ constexpr int kWG = 256;    // threads per workgroup of the force kernels unless
 // hundred rows leave fewer lanes idle in their last i-block
 constexpr int kBatchSjWG = 128;
 constexpr int kTile = 256;  // j-particles staged in LDS per tile
-constexpr int kWorkQueueWords = 16;  // words of a context's work queue (9 used)
+constexpr int kQueueLine = 64;       // words from one counter of a work queue to the next (256 bytes)
+constexpr int kWorkQueueWords = 18 * kQueueLine;  // words of a context's work queue (17 counters, the error word)
 constexpr int kMaxSubRegimes = 16;   // active-count regimes one device-count launch can serve
 constexpr int kErrorWord = kWorkQueueWords - 1;  // word of that buffer holding the device error bits
 constexpr unsigned int kErrActiveRange = 1u;     // an active_idx entry outside its valid range was skipped
@@ -146,9 +147,9 @@ struct ForceArgs {
   int shape;
   int sub_shape[kMaxSubRegimes];
   void* rec;                    // scalar j-path: mirror of n j-records (context-owned)
-  // Work queue of the persistent grid (per-XCD item counters, then the count
-  // of finished workgroups): zero before a launch, and the launch's last
-  // workgroup sets it back to zero (context-owned, kWorkQueueWords words).
+  // Work queue of the persistent grid (work_queue.h): zero before a launch,
+  // and the launch's last workgroup sets it back to zero (context-owned,
+  // kWorkQueueWords words).
   unsigned int* wq;
   // Receiving particles given apart from the j-set: `active` then indexes
   // ipos/ivel (null: the j arrays) and, with no_self set, no self pair is

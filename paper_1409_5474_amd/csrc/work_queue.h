@@ -1,0 +1,118 @@
+// Work queue of the persistent force grids, shared by the force kernels.
+//
+// The items -- (i-block, j-chunk) pairs in chunk-major order -- are cut into
+// kXcd near-equal ranges, one per XCD: the hardware hands workgroups to the
+// chip's 8 XCDs round-robin by blockIdx, so range x is worked by the
+// workgroups on XCD x, and that XCD's L2 holds only the j-chunks of its own
+// range.  Only the first min(items, grid) workgroups take part (the members;
+// the rest return at once, so a launch sized for its largest count costs
+// little at a small one).  A member's first item is fixed: member w starts
+// with item w / kXcd of range w % kXcd, so a launch of no more items than
+// workgroups touches no counter at all.  After that the members of a range
+// take its remaining items from a counter in device memory, so a faster
+// compute unit takes more; once its own range is exhausted, a workgroup
+// takes from the other ranges in turn, so the XCDs (whose clocks differ by a
+// few percent) also finish together.  Each item is computed the same way
+// whichever workgroup takes it: results do not depend on the assignment.
+//
+// Device-scope atomics on one cache line are carried out one after another,
+// about 12 ns each on the MI355X (1024 workgroups, one atomic each: 12.9 us
+// for a kernel that takes 3.0 us without; 3.2 us when each XCD's workgroups
+// use a line of their own).  So every counter has a line of its own, the
+// workgroups that finish are counted per XCD first, and the members' first
+// items cost no atomic.  (With the counters in one line and an atomic for
+// the first item, a launch of 1008 short items spent about 40 us on them.)
+//
+// Lines: [0, kXcd) the range counters (items taken beyond the members' first
+// ones), [kXcd, 2 kXcd) the finished members of each XCD, 2 kXcd the XCDs
+// whose members have all finished.  All are zero before a launch, and the
+// last member to finish sets them back to zero.  Without a queue (wq null)
+// the grid strides over the items in the same order.
+#pragma once
+#include "nb_internal.h"
+
+namespace nb {
+
+constexpr int kXcd = 8;
+static_assert((2 * kXcd + 1) * kQueueLine <= kErrorWord, "work queue larger than its buffer");
+
+__device__ __forceinline__ unsigned int* queue_range(unsigned int* wq, int x) { return wq + x * kQueueLine; }
+
+// Range x of `count` things dealt to the kXcd ranges as evenly as blockIdx
+// deals workgroups to the XCDs: its length and its start.
+__device__ __forceinline__ int64_t range_len(int64_t count, int x) { return count / kXcd + (x < count % kXcd ? 1 : 0); }
+__device__ __forceinline__ int64_t range_lo(int64_t count, int x) {
+  const int64_t r = count % kXcd;
+  return x * (count / kXcd) + (x < r ? x : r);
+}
+__device__ __forceinline__ int64_t queue_members(int64_t items) {
+  return items < (int64_t)gridDim.x ? items : (int64_t)gridDim.x;
+}
+__device__ __forceinline__ bool queue_member(int64_t items) { return (int64_t)blockIdx.x < items; }
+
+// The first item of a member (members <= items, so range x has an item for
+// each of its members).
+__device__ __forceinline__ int64_t queue_first(const unsigned int* wq, int64_t items) {
+  if (!wq) return blockIdx.x;
+  return range_lo(items, blockIdx.x % kXcd) + blockIdx.x / kXcd;
+}
+
+// Thread 0 turns an own-range take into an item: `own` is the counter value
+// the take returned.  When that range is exhausted it reads every range's
+// counter at once (independent loads, one round of latency: device-scope
+// atomics cost about a microsecond each, so the ranges are not visited one
+// by one) and takes from the first range with items left, in the order
+// x0 + 1, x0 + 2, ...  Returns the item, or `items` once all are exhausted.
+__device__ __forceinline__ int64_t queue_pick(unsigned int* wq, int64_t items, unsigned int own) {
+  const int x0 = blockIdx.x % kXcd;
+  const int64_t members = queue_members(items);
+  const int64_t k0 = range_len(members, x0) + own;
+  if (k0 < range_len(items, x0)) return range_lo(items, x0) + k0;
+  for (int attempt = 0; attempt < kXcd; ++attempt) {
+    unsigned int cnt[kXcd];
+#pragma unroll
+    for (int x = 0; x < kXcd; ++x)
+      cnt[x] = __hip_atomic_load(queue_range(wq, x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int pick = -1, best = kXcd;
+#pragma unroll
+    for (int x = 0; x < kXcd; ++x) {
+      const int order = (x - x0 - 1 + 2 * kXcd) % kXcd;  // 0 for range x0 + 1
+      if (range_len(members, x) + cnt[x] < range_len(items, x) && order < best) {
+        best = order;
+        pick = x;
+      }
+    }
+    if (pick < 0) return items;
+    const int64_t k = range_len(members, pick) + atomicAdd(queue_range(wq, pick), 1u);
+    if (k < range_len(items, pick)) return range_lo(items, pick) + k;
+  }
+  return items;
+}
+
+// A member's next item (w_stride: its next item without a queue).
+__device__ __forceinline__ int64_t queue_next(unsigned int* wq, unsigned int& slot, int64_t items, int64_t w_stride) {
+  if (!wq) return w_stride;
+  if (items <= (int64_t)gridDim.x) return items;  // every item was some member's first
+  __syncthreads();  // every thread has read `slot` before it is replaced
+  if (threadIdx.x == 0)
+    slot = (unsigned int)queue_pick(wq, items, atomicAdd(queue_range(wq, blockIdx.x % kXcd), 1u));
+  __syncthreads();
+  // one value for the whole wave: read into a scalar register, so everything
+  // derived from the item (chunk bounds, record addresses) stays uniform
+  return (int64_t)(unsigned int)__builtin_amdgcn_readfirstlane((int)slot);
+}
+
+// Every member calls queue_done once, after its last queue_next; the last
+// member of the last XCD resets the queue (each member's own takes are
+// complete by then).
+__device__ __forceinline__ void queue_done(unsigned int* wq, int64_t items) {
+  if (!wq || items <= (int64_t)gridDim.x || threadIdx.x != 0) return;
+  const int64_t members = gridDim.x;  // fewer than the items
+  const int x = blockIdx.x % kXcd;
+  if (atomicAdd(queue_range(wq, kXcd + x), 1u) != range_len(members, x) - 1) return;
+  const unsigned int xcds = members < kXcd ? (unsigned int)members : kXcd;
+  if (atomicAdd(queue_range(wq, 2 * kXcd), 1u) != xcds - 1) return;
+  for (int k = 0; k <= 2 * kXcd; ++k) atomicExch(queue_range(wq, k), 0u);
+}
+
+}  // namespace nb
