@@ -916,15 +916,15 @@ static int run_forces6(nb_ctx* c, const double* pos, const double* vel, const do
                        double* acc, double* jerk, double* snap, double* pot) {
   const bool mask = eps2 == 0.0;
   const int grid = c->num_cus * nb::forces6_resident_wgs(mask);
-  const int target = 4 * grid;
   nb::Force6Args a{};
   a.pos = pos; a.vel = vel; a.accj = accj; a.mass = mass; a.n = N;
   a.active = active; a.n_active = n_max; a.n_active_dev = n_active_dev; a.eps2 = eps2;
-  a.target_items = target;
-  a.S = nb::forces6_split(n_max, target, N);
+  a.slots = grid;
+  a.S = nb::forces6_split(n_max, grid, N);
   a.acc = acc; a.jerk = jerk; a.snap = snap; a.pot = pot;
+  a.wq = c->wq;
   a.err = c->wq + nb::kErrorWord;
-  const int64_t rows = n_active_dev ? nb::forces6_workspace_rows(n_max, target, N) : (int64_t)a.S * n_max;
+  const int64_t rows = n_active_dev ? nb::forces6_workspace_rows(n_max, grid, N) : (int64_t)a.S * n_max;
   if (n_active_dev || a.S > 1) {
     int rc = ensure_ws(c, (size_t)rows * 10 * sizeof(double));
     if (rc) return rc;

@@ -10,10 +10,18 @@
 //   phi -= m q
 // (the recursive form of the successive time derivatives of m r s^{-3/2}).
 //
-// All arithmetic is double precision.  Layout as the LDS path of the
-// fourth-order kernel: j-tiles of kTile particles staged in LDS as five
-// double2 streams (x y | z m | vx vy | vz ax | ay az), one i-particle per
-// lane, the j-range cut into S chunks over a persistent grid, per-tile
+// The kernel forms them without the common factor, U = u - 3 alpha r and
+// W = w - 6 alpha U - 3 beta r, and adds m q^3 r, m q^3 U, m q^3 W: the factor
+// enters once per component, in the accumulating multiply-add, 55 double
+// instructions per pair besides the reciprocal square root instead of 66.
+//
+// All arithmetic is double precision and the kernel is bound by it: 131072
+// all active run at 563 G pairs/s (474 G with the recursive form), 65 issue
+// slots of a SIMD per pair where the pair's instructions need 58.
+// Layout as the LDS path of the fourth-order kernel: j-tiles of kTile
+// particles staged in LDS as five double2 streams (x y | z m | vx vy | vz ax |
+// ay az), one or four lanes per i-particle, the j-range cut into S chunks over
+// a persistent grid fed by the work queue, per-tile
 // double sums folded into a compensated (TwoSum) accumulator, and a second
 // kernel adding the S partial blocks in a fixed order.  The active count may
 // be read from device memory, so a block step can be captured in a graph.
@@ -24,6 +32,7 @@
 #include <mutex>
 
 #include "nb_internal.h"
+#include "work_queue.h"
 
 namespace nb {
 namespace {
@@ -31,6 +40,10 @@ namespace {
 constexpr int kWG6 = 256;   // threads per workgroup = i-particles per block
 constexpr int kT6 = 256;    // j-particles per staged tile
 constexpr int kC6 = 10;     // acc, jerk, snap, pot
+// Work items aimed at per resident workgroup: short items even out the last
+// round, at the price of more partial sums (20011 all active: 2 per slot 892,
+// 4: 821, 8: 785, 12: 840 us; 131072: 31.7, 31.6, 30.5, 30.6 ms).
+constexpr int kItems6 = 8;
 
 // v_rsq_f64 is accurate to about 2^-24; one third-order Newton step
 // y <- y (1 + e/2 + 3 e^2/8), e = 1 - s y^2, brings it to double rounding.
@@ -49,21 +62,35 @@ __device__ __forceinline__ void two_sum6(double& hi, double& lo, double x) {
   lo += err;
 }
 
-// Chunks per i-block: enough (i-block, chunk) items to fill the chip, each
-// chunk at least one tile.
-__host__ __device__ inline int split6(int64_t n_act, int target_items, int64_t n) {
-  const int64_t n_iblk = (n_act + kWG6 - 1) / kWG6;
-  if (n_iblk <= 0) return 1;
-  int64_t s = (target_items + n_iblk - 1) / n_iblk;
-  const int64_t max_s = (n + kT6 - 1) / kT6;
-  if (s > max_s) s = max_s;
-  if (s < 1) s = 1;
-  return (int)s;
-}
-
 __host__ __device__ inline int64_t chunk6(int64_t n, int S) {
   const int64_t per = (n + S - 1) / S;
   return ((per + kT6 - 1) / kT6) * kT6;
+}
+
+// How an active count is cut: L lanes per i-particle (an i-block holds
+// kWG6 / L rows) and S j-chunks.
+struct Split6 {
+  int L, S;
+};
+__host__ __device__ inline Split6 split6(int64_t n_act, int slots, int64_t n) {
+  Split6 r{1, 1};
+  if (n_act <= 0) return r;
+  const int64_t max_s = (n + kT6 - 1) / kT6;
+  // Four lanes per row while the whole pair matrix, cut into 256 x 256 blocks,
+  // leaves most of the chip idle (at most two items per slot even then): a
+  // block of 256 pairs per lane takes about 40 us however few there are.
+  // 1000 all active: 41.6 us with one lane per row, 18.7 us with four; 4001:
+  // 47.2 and 46.4 us; 65536 with 100 active: 46.1 and 28.7 us.  Above the line
+  // four lanes only quarter the work per staged tile (8000: 160 and 188 us).
+  if ((n_act + kWG6 - 1) / kWG6 * max_s * 4 <= 2 * (int64_t)slots) r.L = 4;
+  const int64_t ib = kWG6 / r.L;
+  const int64_t n_iblk = (n_act + ib - 1) / ib;
+  int64_t s = ((int64_t)kItems6 * slots + n_iblk - 1) / n_iblk;
+  if (s > max_s) s = max_s;
+  if (s < 1) s = 1;
+  const int64_t c = chunk6(n, (int)s);  // whole tiles, so fewer chunks may cover n
+  r.S = (int)((n + c - 1) / c);
+  return r;
 }
 
 struct Tile6 {
@@ -85,29 +112,30 @@ __device__ __forceinline__ void pair6(const double* I, double2 xy, double2 zm, d
   if (MASK) q = (s > 0.0) ? q : 0.0;
   const double q2 = q * q;
   const double ru = fma(rz, uz, fma(ry, uy, rx * ux));
-  const double uu = fma(uz, uz, fma(uy, uy, ux * ux));
-  const double rw = fma(rz, wz, fma(ry, wy, rx * wx));
+  // u.u + r.w in one chain
+  const double z = fma(rz, wz, fma(ry, wy, fma(rx, wx, fma(uz, uz, fma(uy, uy, ux * ux)))));
   const double alpha = ru * q2;
-  const double beta = fma(alpha, alpha, (uu + rw) * q2);
+  const double beta = fma(alpha, alpha, z * q2);
   const double mq = zm.y * q;
   const double mq3 = mq * q2;
-  const double ax = mq3 * rx, ay = mq3 * ry, az = mq3 * rz;
-  const double a3 = -3.0 * alpha;
-  const double jx = fma(a3, ax, mq3 * ux), jy = fma(a3, ay, mq3 * uy), jz = fma(a3, az, mq3 * uz);
-  const double a6 = -6.0 * alpha, b3 = -3.0 * beta;
-  T[0] += ax; T[1] += ay; T[2] += az;
-  T[3] += jx; T[4] += jy; T[5] += jz;
-  T[6] += fma(b3, ax, fma(a6, jx, mq3 * wx));
-  T[7] += fma(b3, ay, fma(a6, jy, mq3 * wy));
-  T[8] += fma(b3, az, fma(a6, jz, mq3 * wz));
+  const double a3 = -3.0 * alpha, a6 = -6.0 * alpha, b3 = -3.0 * beta;
+  const double Ux = fma(a3, rx, ux), Uy = fma(a3, ry, uy), Uz = fma(a3, rz, uz);
+  T[0] = fma(mq3, rx, T[0]); T[1] = fma(mq3, ry, T[1]); T[2] = fma(mq3, rz, T[2]);
+  T[3] = fma(mq3, Ux, T[3]); T[4] = fma(mq3, Uy, T[4]); T[5] = fma(mq3, Uz, T[5]);
+  T[6] = fma(mq3, fma(a6, Ux, fma(b3, rx, wx)), T[6]);
+  T[7] = fma(mq3, fma(a6, Uy, fma(b3, ry, wy)), T[7]);
+  T[8] = fma(mq3, fma(a6, Uz, fma(b3, rz, wz)), T[8]);
   T[9] += mq;
 }
 
-template <bool MASK>
+// One (i-block, j-chunk) item.  L lanes share an i-particle: lane `sub` takes
+// j = sub, sub + L, ... of every tile, and a butterfly folds the L sums.
+template <int L, bool MASK>
 __device__ __forceinline__ void item6(Tile6& tile, const Force6Args& a, int64_t jbeg, int64_t jend, int64_t n_act,
                                       int64_t k0, bool final_out, double* part) {
   const int t = threadIdx.x;
-  const int64_t k = k0 + t;
+  const int64_t k = k0 + t / L;
+  const int sub = t % L;
   int64_t irow = k < n_act ? (int64_t)a.active[k] : -1;
   if (k < n_act && !row_in_range(irow, 0, a.n)) {  // not a particle: skipped, and reported by nb_sync
     if (a.err) atomicOr(a.err, kErrActiveRange);
@@ -140,7 +168,7 @@ __device__ __forceinline__ void item6(Tile6& tile, const Force6Args& a, int64_t 
     }
     __syncthreads();
 #pragma unroll 2
-    for (int jj = 0; jj < kT6; ++jj)
+    for (int jj = sub; jj < kT6; jj += L)
       pair6<MASK>(I, tile.xy[jj], tile.zm[jj], tile.vxy[jj], tile.vza[jj], tile.ayz[jj], e2, T);
 #pragma unroll
     for (int c = 0; c < kC6; ++c) {
@@ -148,10 +176,15 @@ __device__ __forceinline__ void item6(Tile6& tile, const Force6Args& a, int64_t 
       T[c] = 0.0;
     }
   }
-  if (irow < 0) return;
   double v[kC6];
 #pragma unroll
   for (int c = 0; c < kC6; ++c) v[c] = hi[c] + lo[c];
+#pragma unroll
+  for (int o = L / 2; o > 0; o >>= 1) {
+#pragma unroll
+    for (int c = 0; c < kC6; ++c) v[c] += __shfl_xor(v[c], o, 64);
+  }
+  if (sub != 0 || irow < 0) return;
   if (final_out) {
     const double self = (e2 > 0.0) ? a.mass[irow] * rsqrt6(e2) : 0.0;
 #pragma unroll
@@ -167,6 +200,27 @@ __device__ __forceinline__ void item6(Tile6& tile, const Force6Args& a, int64_t 
   }
 }
 
+// The items of one launch, taken from the work queue until none is left.
+template <int L, bool MASK>
+__device__ __forceinline__ void run_items6(Tile6& tile, unsigned int& slot, const Force6Args& a, int64_t n_act,
+                                           int S) {
+  constexpr int IB = kWG6 / L;
+  const int64_t n_iblk = (n_act + IB - 1) / IB;
+  const int64_t items = n_iblk * S;
+  const int64_t clen = chunk6(a.n, S);
+  if (!queue_member(items)) return;
+  int64_t w = queue_first(a.wq, items);
+  while (w < items) {
+    const int64_t chunk = w / n_iblk;
+    const int64_t iblk = w - chunk * n_iblk;
+    const int64_t jb = chunk * clen;
+    const int64_t je = jb + clen < a.n ? jb + clen : a.n;
+    item6<L, MASK>(tile, a, jb, je, n_act, iblk * IB, S == 1, a.part + chunk * kC6 * n_act);
+    w = queue_next(a.wq, slot, items, w + gridDim.x);
+  }
+  queue_done(a.wq, items);
+}
+
 __device__ __forceinline__ int64_t active_count6(const Force6Args& a) {
   int64_t n_act = a.n_active;
   if (a.n_active_dev) {
@@ -179,24 +233,17 @@ __device__ __forceinline__ int64_t active_count6(const Force6Args& a) {
 template <bool MASK>
 __global__ __launch_bounds__(kWG6) void k_forces6(Force6Args a) {
   __shared__ Tile6 tile;
+  __shared__ unsigned int slot;
   const int64_t n_act = active_count6(a);
-  const int S = a.n_active_dev ? split6(n_act, a.target_items, a.n) : a.S;
-  const int64_t n_iblk = (n_act + kWG6 - 1) / kWG6;
-  const int64_t items = n_iblk * S;
-  const int64_t clen = chunk6(a.n, S);
-  for (int64_t w = blockIdx.x; w < items; w += gridDim.x) {
-    const int64_t chunk = w / n_iblk;
-    const int64_t iblk = w - chunk * n_iblk;
-    const int64_t jb = chunk * clen;
-    const int64_t je = jb + clen < a.n ? jb + clen : a.n;
-    item6<MASK>(tile, a, jb, je, n_act, iblk * kWG6, S == 1, a.part + chunk * kC6 * n_act);
-  }
+  const Split6 sp = split6(n_act, a.slots, a.n);
+  if (sp.L == 1) run_items6<1, MASK>(tile, slot, a, n_act, sp.S);
+  else run_items6<4, MASK>(tile, slot, a, n_act, sp.S);
 }
 
 // Fixed-order sum of the S partial blocks, self-term removal, output.
 __global__ __launch_bounds__(256) void k_reduce6(Force6Args a) {
   const int64_t n_act = active_count6(a);
-  const int S = a.n_active_dev ? split6(n_act, a.target_items, a.n) : a.S;
+  const int S = split6(n_act, a.slots, a.n).S;
   if (S <= 1) return;
   const int64_t total = kC6 * n_act;
   const int g = chunk_lanes(S);
@@ -240,12 +287,13 @@ int forces6_resident_wgs(bool mask) {
   return nblk;
 }
 
-int forces6_split(int64_t n_act, int target_items, int64_t n) { return split6(n_act, target_items, n); }
+int forces6_split(int64_t n_act, int slots, int64_t n) { return split6(n_act, slots, n).S; }
 
-int64_t forces6_workspace_rows(int64_t n_max, int target_items, int64_t n) {
-  // S * n_act over every count up to n_max: S <= target / n_iblk + 1, so
-  // S * n_act <= (target + n_iblk) * kWG6 <= target * kWG6 + n_max + kWG6
-  const int64_t bound = (int64_t)target_items * kWG6 + n_max + kWG6;
+int64_t forces6_workspace_rows(int64_t n_max, int slots, int64_t n) {
+  // S * n_act over every count up to n_max: S <= kItems6 slots / n_iblk + 1
+  // with i-blocks of at most kWG6 rows, so
+  // S * n_act <= (kItems6 slots + n_iblk) * IB <= kItems6 slots kWG6 + n_max + kWG6
+  const int64_t bound = (int64_t)kItems6 * slots * kWG6 + n_max + kWG6;
   const int64_t max_s = (n + kT6 - 1) / kT6;
   return bound < max_s * n_max ? bound : max_s * n_max;
 }

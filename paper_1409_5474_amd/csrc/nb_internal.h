@@ -176,13 +176,14 @@ struct Force6Args {
   int64_t n_active;             // host count (or the maximum, with n_active_dev)
   const int32_t* n_active_dev;  // optional device count
   double eps2;
-  int S;                        // j-chunks (host count only)
-  int target_items;             // device count: chunks chosen for this many items
+  int S;                        // j-chunks (host count only: sizes the reduce)
+  int slots;                    // workgroups the chip holds at once; the split follows from them and the count
   double* acc;
   double* jerk;
   double* snap;
   double* pot;
   double* part;                 // [S][10][n_active] partial sums when S > 1
+  unsigned int* wq;             // work queue of the persistent grid (see ForceArgs::wq)
   unsigned int* err;            // i-set entries outside [0, n) are skipped and flagged here
 };
 
@@ -329,8 +330,8 @@ void tree_scratch_free(TreeScratch& s);
 
 // Sixth-order force kernel (forces6.hip).
 int forces6_resident_wgs(bool mask);
-int forces6_split(int64_t n_act, int target_items, int64_t n);
-int64_t forces6_workspace_rows(int64_t n_max, int target_items, int64_t n);
+int forces6_split(int64_t n_act, int slots, int64_t n);
+int64_t forces6_workspace_rows(int64_t n_max, int slots, int64_t n);
 hipError_t launch_forces6(const Force6Args& a, bool mask, int grid, hipStream_t st);
 
 // Sixth-order Hermite passes (hermite6.hip).

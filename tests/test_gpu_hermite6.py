@@ -55,6 +55,16 @@ def test_forces6_match_oracle(ctx, n, na, seed):
     check_fp64(_gpu6(ctx, p, acc_j, eps2, act), ref, names=NAMES)
 
 
+@pytest.mark.parametrize("n,na", [(257, 63), (256, 64), (513, 65), (4864, 4864), (5121, 5121), (70001, 100)])
+def test_forces6_at_the_edges_of_the_lane_split(ctx, n, na):
+    # four lanes per row (i-blocks of 64 rows) for small pair matrices, one
+    # lane (blocks of 256 rows) above; both sides of the line at its two ends
+    p, acc_j = _state(n, 13)
+    act = np.sort(np.random.default_rng(n + na).choice(n, na, replace=False)).astype(np.int32)
+    ref = oracle.snap_ld(p.pos, p.vel, acc_j, p.mass, 1e-3, act)
+    check_fp64(_gpu6(ctx, p, acc_j, 1e-3, act), ref, names=NAMES)
+
+
 def test_forces6_unsoftened_with_a_coincident_pair(ctx):
     p, acc_j = _state(700, 9)
     p.pos[5] = p.pos[600]
