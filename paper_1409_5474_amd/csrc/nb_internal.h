@@ -298,7 +298,7 @@ int energy_blocks(int64_t n);
 // Tree code (tree.hip).
 struct TreeCell {
   int32_t begin, end;      // range of the cell's particles along the curve
-  int32_t child0, nchild;  // children are contiguous; nchild == 0 for a leaf
+  int32_t child0, child1;  // the children are [child0, child1); both -1 for a leaf
   int32_t level, pad;
   double corner[3];        // cube corner and side
   double side;

@@ -22,13 +22,13 @@
 //    phi = -M s^-1/2 - (y.Qy)/2 s^-5/2 with y = x - X, s = |y|^2 + eps2,
 //    Q = sum m (3 d d^T - |d|^2 I) about the centre of mass X
 //
-// Structure on the chip: the build is level-synchronous and data-parallel
-// -- one thread per particle or per cell, with the library's own stable
-// radix sort and exclusive scans placing the outputs, so every array keeps
-// curve order and the results are reproducible run to run.  The level
-// bounds stay in device memory and the buffers are sized from bounds known
-// up front, so nothing is read on the host until the forces are written and
-// a whole evaluation can be captured in a graph.  The walk and the force evaluation are one kernel, as in the
+// Structure on the chip: the build is data-parallel -- one thread per
+// particle, with the library's own stable radix sort and exclusive scans
+// placing the outputs, so every array keeps curve order and the results are
+// reproducible run to run.  All levels are built at once; the level bounds
+// stay in device memory and the buffers are sized from bounds known up front,
+// so nothing is read on the host until the forces are written and a whole
+// evaluation can be captured in a graph.  The walk and the force evaluation are one kernel, as in the
 // paper's GPU tree code: one wavefront per group walks the tree for its 64
 // particles and evaluates accepted cells and opened leaves 64 at a time from
 // LDS as it finds them, so no interaction list is written to memory.  The
@@ -179,45 +179,43 @@ __global__ __launch_bounds__(kTB) void k_keys(const double* __restrict__ pos, in
   }
 }
 
-__global__ __launch_bounds__(kTB) void k_gather(const double* __restrict__ pos, const double* __restrict__ mass,
-                                                const int32_t* __restrict__ idx, int64_t n,
-                                                const Box* __restrict__ box, double* __restrict__ pos_s,
-                                                double* __restrict__ mass_s, int32_t* __restrict__ ijk_s) {
-  const Box b = *box;
-  for (int64_t k = (int64_t)blockIdx.x * kTB + threadIdx.x; k < n; k += (int64_t)gridDim.x * kTB) {
-    const int64_t i = idx[k];
-    for (int c = 0; c < 3; ++c) pos_s[3 * k + c] = pos[3 * i + c];
-    mass_s[k] = mass[i];
-    grid_of(pos + 3 * i, b, ijk_s + 3 * k);
-  }
-}
-
 // --------------------------------------------------------------- tree -----
-__device__ __forceinline__ void set_geometry(TreeCell& c, const int32_t* ijk_s, const Box& b) {
+// The whole tree follows from the sorted keys at once, without a pass per
+// level.  A cell (l, p) exists when its parent holds more than n_crit
+// particles, so particle i has cells on levels 0 .. top(i) = min(e(i) + 1, 21)
+// where e(i) is the deepest level whose cell around i holds more than n_crit
+// particles; and i is the first particle of its level-l cell for every
+// l >= d(i), one more than the levels its key shares with the key before it.
+// So i starts exactly the cells of levels d(i) .. top(i).  Three kernels: per
+// tile of kTB particles the number of cells starting on each level
+// (k_cell_starts), the prefix of those counts over the tiles, one block per
+// level (k_level_scan), and the cells at their places (k_write_cells): level
+// after level, in curve order within each, children contiguous.  (A pass of
+// three kernels per level, 63 launches whatever the depth, took 0.3-0.35 ms
+// per evaluation of 10^4 and of 2.6 x 10^5 particles, most of it launches and
+// latency; these three take 26 and 40 us.)
+__device__ __forceinline__ void set_geometry(TreeCell& c, const int32_t* ijk, const Box& b) {
 #pragma clang fp contract(off)
   const int shift = kBits - c.level;
   for (int k = 0; k < 3; ++k) {
-    const int64_t ci = ((int64_t)ijk_s[3 * c.begin + k] >> shift) << shift;
+    const int64_t ci = ((int64_t)ijk[k] >> shift) << shift;
     c.corner[k] = b.lo[k] + (double)ci * b.h;
   }
   c.side = ldexp(b.h, shift);
 }
 
-// The root, and the level table: the cells of level l are [lvl[l], lvl[l+1])
-// (kept in device memory, so no count goes to the host while the tree grows).
-__global__ void k_root(TreeCell* __restrict__ cells, int32_t n, const int32_t* __restrict__ ijk_s,
-                       const Box* __restrict__ box, int32_t* __restrict__ lvl) {
-  if (blockIdx.x != 0) return;
-  for (int l = threadIdx.x; l < kLevels + 1; l += blockDim.x) lvl[l] = l == 0 ? 0 : 1;
-  if (threadIdx.x != 0) return;
-  TreeCell c{};
-  c.begin = 0; c.end = n; c.child0 = -1; c.nchild = 0; c.level = 0;
-  set_geometry(c, ijk_s, *box);
-  cells[0] = c;
+constexpr int kRows = kLevels + 1;  // per-tile counts: cells starting on each level, then groups
+constexpr int kMaxWindow = 256;     // n_crit + 1 up to which the window maximum runs in LDS
+
+// leading octal digits two 63-bit keys share (21: equal)
+__device__ __forceinline__ int shared_levels(uint64_t a, uint64_t b) {
+  const uint64_t x = a ^ b;
+  return x ? (__clzll((long long)x) - 1) / 3 : kBits;
 }
 
-// first position in [lo, hi) whose key is >= bound
-__device__ __forceinline__ int32_t lower_bound_key(const uint64_t* keys, int32_t lo, int32_t hi, uint64_t bound) {
+// first position in [lo, hi) whose key is >= bound (hi if none)
+__device__ __forceinline__ int32_t lower_bound_key(const uint64_t* __restrict__ keys, int32_t lo, int32_t hi,
+                                                   uint64_t bound) {
   while (lo < hi) {
     const int32_t mid = lo + (hi - lo) / 2;
     if (keys[mid] < bound) lo = mid + 1;
@@ -226,136 +224,20 @@ __device__ __forceinline__ int32_t lower_bound_key(const uint64_t* keys, int32_t
   return lo;
 }
 
-// The child boundaries of every cell that splits, kept in `ends` [ncell][8]
-// for the write pass: eight consecutive lanes per cell, lane k finds where
-// child k ends (a binary search over the cell's keys; child k of a cell at
-// level l covers the keys [(p<<3|k) << s, (p<<3|k)+1 << s), s = 3(20 - l),
-// and the last child ends with the cell), and the cell's count of non-empty
-// children is summed over the eight lanes.
-__global__ __launch_bounds__(kTB) void k_count_children(const TreeCell* __restrict__ all_cells,
-                                                        const int32_t* __restrict__ lvl, int l,
-                                                        const uint64_t* __restrict__ keys, int n_crit,
-                                                        int32_t* __restrict__ cnt, int32_t* __restrict__ ends) {
-  const TreeCell* cells = all_cells + lvl[l];
-  const int32_t ncell = lvl[l + 1] - lvl[l];
-  const int64_t total = 8 * (int64_t)ncell;  // whole groups of eight lanes
-  for (int64_t t = (int64_t)blockIdx.x * kTB + threadIdx.x; t < total; t += (int64_t)gridDim.x * kTB) {
-    const int32_t i = (int32_t)(t >> 3);
-    const int k = (int)(t & 7);
-    const TreeCell& c = cells[i];
-    const bool split = c.end - c.begin > n_crit && c.level < kBits;
-    int32_t e = c.end;
-    if (split && k < 7) {
-      const int sh = 3 * (kBits - c.level - 1);
-      const uint64_t prefix = keys[c.begin] >> (sh + 3);
-      e = lower_bound_key(keys, c.begin, c.end, ((prefix << 3) | (uint64_t)(k + 1)) << sh);
-    }
-    const int32_t prev = __shfl_up(e, 1, 8);
-    const int32_t b = k == 0 ? c.begin : prev;
-    int m = (split && e > b) ? 1 : 0;
-    m += __shfl_xor(m, 1, 8);
-    m += __shfl_xor(m, 2, 8);
-    m += __shfl_xor(m, 4, 8);
-    if (split) ends[t] = e;
-    if (k == 0) cnt[i] = m;
+// e(i) for any n_crit: the deepest level (below 22, -1 for none) whose cell
+// around i holds more than n_crit particles, by bisection over the levels
+__device__ __forceinline__ int deepest_full(const uint64_t* __restrict__ keys, int32_t n, int32_t i, int n_crit) {
+  int lo = -1, hi = kBits;
+  while (lo < hi) {
+    const int l = (lo + hi + 1) >> 1;
+    const int sh = 3 * (kBits - l);
+    const uint64_t p = keys[i] >> sh;
+    const int32_t b = lower_bound_key(keys, 0, i, p << sh);
+    const int32_t e = lower_bound_key(keys, i, n, (p + 1) << sh);
+    if (e - b > n_crit) lo = l;
+    else hi = l - 1;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) cnt[ncell] = 0;
-}
-
-__global__ __launch_bounds__(kTB) void k_write_children(TreeCell* __restrict__ cells, int32_t* __restrict__ lvl, int l,
-                                                        const int32_t* __restrict__ ends,
-                                                        const int32_t* __restrict__ ijk_s,
-                                                        const Box* __restrict__ box, int n_crit,
-                                                        const int32_t* __restrict__ off) {
-  const int32_t first = lvl[l], next = lvl[l + 1], ncell = next - first;
-  const Box bx = *box;
-  // the next level's cells follow this one's; off[ncell] is their number
-  if (blockIdx.x == 0 && threadIdx.x == 0) lvl[l + 2] = next + off[ncell];
-  for (int32_t i = blockIdx.x * kTB + threadIdx.x; i < ncell; i += gridDim.x * kTB) {
-    TreeCell& c = cells[first + i];
-    if (!(c.end - c.begin > n_crit && c.level < kBits)) {
-      c.child0 = -1;
-      c.nchild = 0;
-      continue;
-    }
-    const int32_t base = next + off[i];
-    int32_t b = c.begin, m = 0;
-    for (int k = 0; k < 8; ++k) {
-      const int32_t e = ends[8 * (int64_t)i + k];
-      if (e > b) {
-        TreeCell ch{};
-        ch.begin = b; ch.end = e; ch.child0 = -1; ch.nchild = 0; ch.level = c.level + 1;
-        set_geometry(ch, ijk_s, bx);
-        cells[base + m] = ch;
-        ++m;
-      }
-      b = e;
-    }
-    c.child0 = base;
-    c.nchild = m;
-  }
-}
-
-// Moments: leaves from their particles, internal cells from their children.
-__global__ __launch_bounds__(kTB) void k_moments(TreeCell* __restrict__ cells, const int32_t* __restrict__ lvl, int l,
-                                                 const double* __restrict__ pos_s, const double* __restrict__ mass_s) {
-  const int32_t first = lvl[l], ncell = lvl[l + 1] - lvl[l];
-  for (int32_t i = blockIdx.x * kTB + threadIdx.x; i < ncell; i += gridDim.x * kTB) {
-    TreeCell& c = cells[first + i];
-    double M = 0.0, S[3] = {0.0, 0.0, 0.0}, Q[6] = {0, 0, 0, 0, 0, 0}, X[3];
-    if (c.nchild == 0) {
-      for (int32_t j = c.begin; j < c.end; ++j) {
-        const double m = mass_s[j];
-        M += m;
-        for (int k = 0; k < 3; ++k) S[k] += m * pos_s[3 * j + k];
-      }
-      for (int k = 0; k < 3; ++k) X[k] = M > 0.0 ? S[k] / M : c.corner[k] + 0.5 * c.side;
-      for (int32_t j = c.begin; j < c.end; ++j) {
-        const double m = mass_s[j];
-        const double d0 = pos_s[3 * j] - X[0], d1 = pos_s[3 * j + 1] - X[1], d2 = pos_s[3 * j + 2] - X[2];
-        const double dd = d0 * d0 + d1 * d1 + d2 * d2;
-        Q[0] += m * (3.0 * (d0 * d0) - dd);
-        Q[1] += m * (3.0 * (d1 * d1) - dd);
-        Q[2] += m * (3.0 * (d2 * d2) - dd);
-        Q[3] += m * (3.0 * (d0 * d1));
-        Q[4] += m * (3.0 * (d0 * d2));
-        Q[5] += m * (3.0 * (d1 * d2));
-      }
-    } else {
-      for (int32_t k = 0; k < c.nchild; ++k) {
-        const TreeCell& ch = cells[c.child0 + k];
-        M += ch.M;
-        for (int q = 0; q < 3; ++q) S[q] += ch.M * ch.X[q];
-      }
-      for (int k = 0; k < 3; ++k) X[k] = M > 0.0 ? S[k] / M : c.corner[k] + 0.5 * c.side;
-      for (int32_t k = 0; k < c.nchild; ++k) {
-        const TreeCell& ch = cells[c.child0 + k];
-        const double e0 = ch.X[0] - X[0], e1 = ch.X[1] - X[1], e2 = ch.X[2] - X[2];
-        const double ee = e0 * e0 + e1 * e1 + e2 * e2;
-        const double m = ch.M;
-        Q[0] += ch.Q[0] + m * (3.0 * (e0 * e0) - ee);
-        Q[1] += ch.Q[1] + m * (3.0 * (e1 * e1) - ee);
-        Q[2] += ch.Q[2] + m * (3.0 * (e2 * e2) - ee);
-        Q[3] += ch.Q[3] + m * (3.0 * (e0 * e1));
-        Q[4] += ch.Q[4] + m * (3.0 * (e0 * e2));
-        Q[5] += ch.Q[5] + m * (3.0 * (e1 * e2));
-      }
-    }
-    c.M = M;
-    for (int k = 0; k < 3; ++k) c.X[k] = X[k];
-    for (int k = 0; k < 6; ++k) c.Q[k] = Q[k];
-  }
-}
-
-// ------------------------------------------------------------- groups -----
-__device__ __forceinline__ double extent(const double* pos_s, int32_t b, int32_t e) {
-  double mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
-  for (int32_t j = b; j < e; ++j)
-    for (int k = 0; k < 3; ++k) {
-      mn[k] = fmin(mn[k], pos_s[3 * j + k]);
-      mx[k] = fmax(mx[k], pos_s[3 * j + k]);
-    }
-  return fmax(mx[0] - mn[0], fmax(mx[1] - mn[1], mx[2] - mn[2]));
+  return lo;
 }
 
 // number of set bits of `mask` below this lane
@@ -363,66 +245,24 @@ __device__ __forceinline__ int lane_rank(uint64_t mask) {
   return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// Groups of one curve chunk of up to 64 particles: the chunk is halved
-// (first half ceil(n/2)) while a piece holding more than one particle is
-// wider than g_max, first half first.  An explicit stack replaces the
-// recursion; a chunk of 64 is halved at most six times, so seven entries
-// suffice.  Returns the number of groups; writes them when `gb` is set.
-__device__ __forceinline__ int32_t split_chunk(const double* __restrict__ pos_s, int32_t b0, int32_t e0,
-                                               double g_max, int32_t* __restrict__ gb, int32_t* __restrict__ ge) {
-  int32_t sb[8], se[8];
-  int sp = 1;
-  sb[0] = b0;
-  se[0] = e0;
-  int32_t cnt = 0;
-  while (sp > 0) {
-    --sp;
-    const int32_t b = sb[sp], e = se[sp];
-    if (e - b > 1 && sp + 2 <= 8 && extent(pos_s, b, e) > g_max) {
-      const int32_t m = b + (e - b + 1) / 2;
-      sb[sp] = m; se[sp] = e; ++sp;
-      sb[sp] = b; se[sp] = m; ++sp;
-    } else {
-      if (gb) {
-        gb[cnt] = b;
-        ge[cnt] = e;
-      }
-      ++cnt;
-    }
-  }
-  return cnt;
-}
-
-// One wavefront per chunk.  A full chunk of 64 is only ever cut at aligned
-// halves, and a piece that fits (extent <= g_max) has pieces that fit, so
-// the group holding particle j is the largest aligned piece around j that
-// fits (a single particle always does): lane j reduces the minimum and
-// maximum position over the aligned pieces of 2, 4, ..., 64 around it by
-// butterfly shuffles and keeps the largest size that fits.  The last,
-// shorter chunk takes the recursion above on lane 0.  WRITE = false counts
-// the groups per chunk, WRITE = true writes them at their offsets.
-template <bool WRITE>
-__global__ __launch_bounds__(kTB) void k_groups(int32_t n, int32_t nchunk, const double* __restrict__ pos_s,
-                                                const Box* __restrict__ box, double g_frac,
-                                                int32_t* __restrict__ cnt, const int32_t* __restrict__ off,
-                                                int32_t* __restrict__ gb, int32_t* __restrict__ ge,
-                                                int32_t* __restrict__ ng) {
-  const double g_max = g_frac > 0.0 ? g_frac * box->side : INFINITY;
-  const int lane = threadIdx.x & (kGS - 1);
-  const int64_t wave = ((int64_t)blockIdx.x * kTB + threadIdx.x) / kGS;
-  const int64_t nwaves = (int64_t)gridDim.x * kTB / kGS;
-  for (int64_t c = wave; c < nchunk; c += nwaves) {
-    const int32_t b = (int32_t)c * kGS, e = b + kGS < n ? b + kGS : n;
-    if (e - b < kGS) {
-      if (lane == 0) {
-        if (WRITE) split_chunk(pos_s, b, e, g_max, gb + off[c], ge + off[c]);
-        else cnt[c] = split_chunk(pos_s, b, e, g_max, nullptr, nullptr);
-      }
-      continue;
-    }
-    const int32_t j = b + lane;
+// The group that holds this lane's particle: a chunk of m <= 64 particles is
+// halved (first half ceil(n/2)) while a piece of more than one particle is
+// wider than g_max.  A full chunk is only ever cut at aligned halves, and a
+// piece that fits has pieces that fit, so the group is the largest aligned
+// piece around the lane that fits: minimum and maximum over the aligned
+// pieces of 2, 4, ..., 64 lanes by butterfly shuffles.  In the last, shorter
+// chunk every lane follows the halving of its own piece on the positions in
+// LDS (one lane doing it for all took 19 us).
+struct Piece {
+  int begin, end;          // lanes of the group
+  double lo[3], hi[3];     // its bounding box
+};
+__device__ __forceinline__ Piece group_of(int lane, int m, const double* x, double g_max, double (*xs)[3]) {
+  Piece p;
+  for (int k = 0; k < 3; ++k) p.lo[k] = p.hi[k] = x[k];
+  if (m == kGS) {
     double mn[3], mx[3];
-    for (int k = 0; k < 3; ++k) mn[k] = mx[k] = pos_s[3 * j + k];
+    for (int k = 0; k < 3; ++k) mn[k] = mx[k] = x[k];
     int size = 1;
     for (int h = 1; h < kGS; h <<= 1) {
       for (int k = 0; k < 3; ++k) {
@@ -430,38 +270,377 @@ __global__ __launch_bounds__(kTB) void k_groups(int32_t n, int32_t nchunk, const
         mx[k] = fmax(mx[k], __shfl_xor(mx[k], h, kGS));
       }
       const double ext = fmax(mx[0] - mn[0], fmax(mx[1] - mn[1], mx[2] - mn[2]));
-      if (size == h && !(ext > g_max)) size = 2 * h;
-    }
-    const bool start = (lane & (size - 1)) == 0;
-    const uint64_t starts = __ballot(start);
-    if (WRITE) {
-      if (start) {
-        const int32_t o = off[c] + lane_rank(starts);
-        gb[o] = j;
-        ge[o] = j + size;
+      if (size == h && !(ext > g_max)) {
+        size = 2 * h;
+        for (int k = 0; k < 3; ++k) {
+          p.lo[k] = mn[k];
+          p.hi[k] = mx[k];
+        }
       }
-    } else if (lane == 0) {
-      cnt[c] = __popcll(starts);
     }
+    p.begin = lane & ~(size - 1);
+    p.end = p.begin + size;
+    return p;
   }
-  if (WRITE && blockIdx.x == 0 && threadIdx.x == 0) *ng = off[nchunk - 1] + cnt[nchunk - 1];
+  for (int k = 0; k < 3; ++k) xs[lane][k] = x[k];
+  __builtin_amdgcn_wave_barrier();
+  p.begin = 0;
+  p.end = m;
+  while (lane < m && p.end - p.begin > 1) {
+    double mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
+    for (int j = p.begin; j < p.end; ++j)
+      for (int k = 0; k < 3; ++k) {
+        mn[k] = fmin(mn[k], xs[j][k]);
+        mx[k] = fmax(mx[k], xs[j][k]);
+      }
+    if (!(fmax(mx[0] - mn[0], fmax(mx[1] - mn[1], mx[2] - mn[2])) > g_max)) {
+      for (int k = 0; k < 3; ++k) {
+        p.lo[k] = mn[k];
+        p.hi[k] = mx[k];
+      }
+      break;
+    }
+    const int mid = p.begin + (p.end - p.begin + 1) / 2;
+    if (lane < mid) p.end = mid;
+    else p.begin = mid;
+  }
+  return p;
 }
 
-__global__ __launch_bounds__(kTB) void k_group_box(const int32_t* __restrict__ gb, const int32_t* __restrict__ ge,
-                                                   const int32_t* __restrict__ ng_dev, const double* __restrict__ pos_s,
-                                                   double* __restrict__ gbox) {
-  const int32_t ng = *ng_dev;
-  for (int32_t g = blockIdx.x * kTB + threadIdx.x; g < ng; g += gridDim.x * kTB) {
-    double mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
-    for (int32_t j = gb[g]; j < ge[g]; ++j)
-      for (int k = 0; k < 3; ++k) {
-        mn[k] = fmin(mn[k], pos_s[3 * j + k]);
-        mx[k] = fmax(mx[k], pos_s[3 * j + k]);
-      }
+// Mass, centre of mass and traceless quadrupole of a tile's particles.
+struct TileMoments {
+  double M, X[3], Q[6];
+};
+
+template <int G>
+__device__ __forceinline__ double fold_lanes(double v) {
+#pragma unroll
+  for (int o = G / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+// Q += the traceless quadrupole of mass m at offset e
+__device__ __forceinline__ void add_quad(double* Q, double m, double e0, double e1, double e2) {
+  const double ee = e0 * e0 + e1 * e1 + e2 * e2;
+  Q[0] += m * (3.0 * (e0 * e0) - ee);
+  Q[1] += m * (3.0 * (e1 * e1) - ee);
+  Q[2] += m * (3.0 * (e2 * e2) - ee);
+  Q[3] += m * (3.0 * (e0 * e1));
+  Q[4] += m * (3.0 * (e0 * e2));
+  Q[5] += m * (3.0 * (e1 * e2));
+}
+
+// Sums of N values over the block's threads, in a fixed order; red is free
+// again after the next barrier.
+template <int N>
+__device__ __forceinline__ void block_fold(double* v, double (*red)[6]) {
+  constexpr int W = kTB / kGS;
+  for (int k = 0; k < N; ++k) {
+    v[k] = fold_lanes<64>(v[k]);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][k] = v[k];
+  }
+  __syncthreads();
+  for (int k = 0; k < N; ++k) {
+    v[k] = red[0][k];
+    for (int w = 1; w < W; ++w) v[k] += red[w][k];
+  }
+}
+
+// Per tile: the particles in curve order, d(i) and top(i) of each (span), the
+// numbers of cells starting on each level and of groups, and the moments.
+__global__ __launch_bounds__(kTB) void k_cell_starts(const uint64_t* __restrict__ keys, const int32_t* __restrict__ idx,
+                                                     const double* __restrict__ pos, const double* __restrict__ mass,
+                                                     int32_t n, int n_crit, const Box* __restrict__ box, double g_frac,
+                                                     double* __restrict__ pos_s, double* __restrict__ mass_s,
+                                                     uint16_t* __restrict__ span, int32_t* __restrict__ cnt,
+                                                     int32_t ntile, TileMoments* __restrict__ tiles) {
+  constexpr int W = kTB / kGS;
+  __shared__ double red[2][W][6];
+  __shared__ int8_t win[2][kTB + kMaxWindow];
+  __shared__ int32_t wcnt[W][kRows];
+  __shared__ double xs[W][kGS][3];
+  const int t = threadIdx.x, lane = t & (kGS - 1), wave = t / kGS;
+  const int32_t tile0 = (int32_t)blockIdx.x * kTB, i = tile0 + t;
+  const bool valid = i < n;
+  double x[3] = {0.0, 0.0, 0.0}, pm = 0.0;
+  if (valid) {
+    const int64_t o = idx[i];
     for (int k = 0; k < 3; ++k) {
-      gbox[6 * g + k] = mn[k];
-      gbox[6 * g + 3 + k] = mx[k];
+      x[k] = pos[3 * o + k];
+      pos_s[3 * (int64_t)i + k] = x[k];
     }
+    pm = mass[o];
+    mass_s[i] = pm;
+  }
+  {
+    double v[4] = {pm, pm * x[0], pm * x[1], pm * x[2]}, q[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    block_fold<4>(v, red[0]);
+    double X[3];
+    for (int k = 0; k < 3; ++k) X[k] = v[0] > 0.0 ? v[1 + k] / v[0] : 0.0;
+    if (valid) add_quad(q, pm, x[0] - X[0], x[1] - X[1], x[2] - X[2]);
+    block_fold<6>(q, red[1]);
+    if (t == 0) {
+      TileMoments& tm = tiles[blockIdx.x];
+      tm.M = v[0];
+      for (int k = 0; k < 3; ++k) tm.X[k] = X[k];
+      for (int k = 0; k < 6; ++k) tm.Q[k] = q[k];
+    }
+  }
+  int e = -1;
+  if (n_crit < kMaxWindow) {
+    // e(i) is the largest number of levels that keys k and k + n_crit share
+    // over the windows k <= i <= k + n_crit; maximum by doubling
+    const int len = kTB + n_crit;
+    for (int q = t; q < len; q += kTB) {
+      const int64_t k = (int64_t)tile0 - n_crit + q;
+      win[0][q] = (k >= 0 && k + n_crit < n) ? (int8_t)shared_levels(keys[k], keys[k + n_crit]) : (int8_t)-1;
+    }
+    __syncthreads();
+    int p = 1, cur = 0;
+    for (; 2 * p <= n_crit + 1; p *= 2, cur ^= 1) {
+      for (int q = t; q < len; q += kTB) {
+        const int8_t u = win[cur][q], v = q + p < len ? win[cur][q + p] : (int8_t)-1;
+        win[cur ^ 1][q] = u > v ? u : v;
+      }
+      __syncthreads();
+    }
+    const int8_t u = win[cur][t], v = win[cur][t + n_crit + 1 - p];
+    e = u > v ? u : v;
+  } else if (valid) {
+    e = deepest_full(keys, n, i, n_crit);
+  }
+  const int top = e + 1 < kBits ? e + 1 : kBits;
+  const int d = i == 0 ? 0 : (valid ? shared_levels(keys[i - 1], keys[i]) + 1 : kBits + 1);
+  if (valid) span[i] = (uint16_t)(d | (top << 8));
+  int32_t mine = 0;
+  for (int l = 0; l < kLevels; ++l) {
+    const int32_t c = __popcll(__ballot(valid && d <= l && l <= top));
+    if (lane == l) mine = c;
+  }
+  if (lane < kLevels) wcnt[wave][lane] = mine;
+  // groups of the wavefront's chunk
+  const int32_t left = n - (tile0 + wave * kGS);
+  const int m = left < kGS ? (left > 0 ? left : 0) : kGS;
+  const double g_max = g_frac > 0.0 ? g_frac * box->side : INFINITY;
+  const Piece p = group_of(lane, m, x, g_max, xs[wave]);
+  const uint64_t starts = __ballot(lane < m && p.begin == lane);
+  if (lane == 0) wcnt[wave][kLevels] = __popcll(starts);
+  __syncthreads();
+  if (t < kRows) {
+    int32_t sum = 0;
+    for (int w = 0; w < W; ++w) sum += wcnt[w][t];
+    cnt[(int64_t)t * ntile + blockIdx.x] = sum;
+  }
+}
+
+// Exclusive prefix of one row of tile counts (block r), in place, and its
+// total; also zeroes the walk's counters.
+__global__ __launch_bounds__(1024) void k_level_scan(int32_t* __restrict__ cnt, int32_t ntile,
+                                                     int32_t* __restrict__ total,
+                                                     unsigned long long* __restrict__ ctr) {
+  constexpr int T = 1024, W = T / 64;
+  __shared__ int32_t wsum[2][W];
+  int32_t* row = cnt + (int64_t)blockIdx.x * ntile;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  int32_t carry = 0;
+  int buf = 0;
+  for (int32_t base = 0; base < ntile; base += T) {
+    const int32_t k = base + t;
+    const int32_t v = k < ntile ? row[k] : 0;
+    int32_t x = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int32_t y = __shfl_up(x, o, 64);
+      if (lane >= o) x += y;
+    }
+    if (lane == 63) wsum[buf][wave] = x;
+    __syncthreads();  // the totals alternate between two buffers: one barrier per round
+    int32_t before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      before += w < wave ? wsum[buf][w] : 0;
+      all += wsum[buf][w];
+    }
+    if (k < ntile) row[k] = carry + before + x - v;
+    carry += all;
+    buf ^= 1;
+  }
+  if (t == 0) total[blockIdx.x] = carry;
+  if (blockIdx.x == 0 && t < 4) ctr[t] = 0ull;
+}
+
+// Cells and groups at their places.  Thread i writes the cells its particle
+// starts (levels d(i) .. top(i)) and closes those that end before it: levels
+// d(i) .. top(i - 1), each the last cell starting before i on its level.  The
+// first child of a cell starts at the cell's own particle; the last child is
+// the cell closed together with it one level deeper.
+__global__ __launch_bounds__(kTB) void k_write_cells(TreeCell* __restrict__ cells, const uint16_t* __restrict__ span,
+                                                     const int32_t* __restrict__ cnt,
+                                                     const int32_t* __restrict__ total, int32_t ntile, int32_t n,
+                                                     const double* __restrict__ pos_s, const Box* __restrict__ box,
+                                                     double g_frac, int32_t* __restrict__ lvl,
+                                                     int32_t* __restrict__ gb, int32_t* __restrict__ ge,
+                                                     double* __restrict__ gbox, int32_t* __restrict__ ng) {
+  constexpr int W = kTB / kGS;
+  __shared__ int32_t first[W][kRows];  // index of a wavefront's first cell of a level, or group
+  __shared__ int32_t wcnt[W][kRows];
+  __shared__ double xs[W][kGS][3];
+  const int t = threadIdx.x, lane = t & (kGS - 1), wave = t / kGS;
+  const int32_t tile0 = (int32_t)blockIdx.x * kTB, i = tile0 + t;
+  const bool valid = i < n;
+  const Box bx = *box;
+  int d = kLevels, top = -1;
+  double x[3] = {0.0, 0.0, 0.0};
+  if (valid) {
+    const int sp = span[i];
+    d = sp & 255;
+    top = sp >> 8;
+    for (int k = 0; k < 3; ++k) x[k] = pos_s[3 * (int64_t)i + k];
+  }
+  int32_t mine = 0;
+  for (int l = 0; l < kLevels; ++l) {
+    const int32_t c = __popcll(__ballot(d <= l && l <= top));
+    if (lane == l) mine = c;
+  }
+  if (lane < kLevels) wcnt[wave][lane] = mine;
+  const int32_t left = n - (tile0 + wave * kGS);
+  const int m = left < kGS ? (left > 0 ? left : 0) : kGS;
+  const double g_max = g_frac > 0.0 ? g_frac * bx.side : INFINITY;
+  const Piece p = group_of(lane, m, x, g_max, xs[wave]);
+  const bool gstart = lane < m && p.begin == lane;
+  const uint64_t gmask = __ballot(gstart);
+  if (lane == 0) wcnt[wave][kLevels] = __popcll(gmask);
+  __syncthreads();
+  if (t < kRows) {
+    int32_t at = cnt[(int64_t)t * ntile + blockIdx.x];
+    if (t < kLevels)
+      for (int l = 0; l < t; ++l) at += total[l];
+    for (int w = 0; w < W; ++w) {
+      first[w][t] = at;
+      at += wcnt[w][t];
+    }
+  }
+  if (blockIdx.x == 0 && t <= kLevels) {
+    int32_t at = 0;
+    for (int l = 0; l < t; ++l) at += total[l];
+    lvl[t] = at;  // the cells of level l are [lvl[l], lvl[l + 1])
+    if (t == kLevels) *ng = total[kLevels];
+  }
+  __syncthreads();
+  if (gstart) {
+    const int32_t g = first[wave][kLevels] + lane_rank(gmask);
+    gb[g] = i;
+    ge[g] = i + (p.end - p.begin);
+    for (int k = 0; k < 3; ++k) {
+      gbox[6 * (int64_t)g + k] = p.lo[k];
+      gbox[6 * (int64_t)g + 3 + k] = p.hi[k];
+    }
+  }
+  int32_t q[3] = {0, 0, 0};
+  if (d <= top) grid_of(x, bx, q);
+  const int before_top = valid && i > 0 ? span[i - 1] >> 8 : -1;
+  const bool last = i == n - 1;
+  int32_t above = 0, above_incl = 0;  // one level up: cells before those starting at i; and including them
+  for (int l = 0; l < kLevels; ++l) {
+    const bool start = d <= l && l <= top;
+    const int32_t c = first[wave][l] + lane_rank(__ballot(start));
+    const int32_t incl = c + (start ? 1 : 0);
+    if (start) {
+      TreeCell& cell = cells[c];
+      cell.begin = i;
+      cell.level = l;
+      set_geometry(cell, q, bx);
+      if (l == top) cell.child0 = cell.child1 = -1;
+      if (l > d) cells[above].child0 = c;
+    }
+    if (l >= d && l <= before_top) {
+      cells[c - 1].end = i;
+      if (l > d) cells[above - 1].child1 = c;
+    }
+    if (last && l <= top) {
+      cells[incl - 1].end = n;
+      if (l > 0) cells[above_incl - 1].child1 = incl;
+    }
+    above = c;
+    above_incl = incl;
+  }
+}
+
+// ------------------------------------------------------------ moments -----
+// Every cell's moments from its particles, or, where a cell holds whole tiles
+// of the curve, from those tiles' moments (k_cell_starts computes them), so no
+// level waits for the one below and one launch does all.  Cells of up to
+// kSmallCell particles take eight lanes, larger ones a wavefront.  Cell c
+// belongs to block c mod the grid: the large cells, which come first in the
+// level order, go to different blocks.  The root is never accepted and gets
+// no moments.  2.6 x 10^5 particles: 38 us (22 launches, one per level,
+// summing children: 140 us; without the tile moments: 640 us, spent on the
+// largest cells).
+constexpr int kSmallCell = 64;
+constexpr int kDirectCell = 512;  // up to here a wavefront takes the particles one by one
+
+// The moments of one cell by the G lanes `t`: of its tm0 <= tile < tm1 whole
+// tiles and of the particles before and after them.
+template <int G>
+__device__ __forceinline__ void moments_of(TreeCell& c, const double* __restrict__ pos_s,
+                                           const double* __restrict__ mass_s, const TileMoments* __restrict__ tiles,
+                                           int32_t tm0, int32_t tm1, int t) {
+  const int32_t b = c.begin, e = c.end;
+  const int32_t head = tm1 > tm0 ? tm0 * kTB - b : e - b;  // particles before the tiles (all of them without)
+  const int32_t skip = (tm1 - tm0) * kTB;
+  const int32_t singles = e - b - skip;
+  double M = 0.0, S[3] = {0.0, 0.0, 0.0}, Q[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, X[3];
+  for (int32_t u = t; u < singles; u += G) {
+    const int64_t j = b + u + (u < head ? 0 : skip);
+    const double m = mass_s[j];
+    M += m;
+    for (int k = 0; k < 3; ++k) S[k] += m * pos_s[3 * j + k];
+  }
+  for (int32_t u = tm0 + t; u < tm1; u += G) {
+    M += tiles[u].M;
+    for (int k = 0; k < 3; ++k) S[k] += tiles[u].M * tiles[u].X[k];
+  }
+  M = fold_lanes<G>(M);
+  for (int k = 0; k < 3; ++k) {
+    S[k] = fold_lanes<G>(S[k]);
+    X[k] = M > 0.0 ? S[k] / M : c.corner[k] + 0.5 * c.side;
+  }
+  for (int32_t u = t; u < singles; u += G) {
+    const int64_t j = b + u + (u < head ? 0 : skip);
+    add_quad(Q, mass_s[j], pos_s[3 * j] - X[0], pos_s[3 * j + 1] - X[1], pos_s[3 * j + 2] - X[2]);
+  }
+  for (int32_t u = tm0 + t; u < tm1; u += G) {
+    for (int k = 0; k < 6; ++k) Q[k] += tiles[u].Q[k];
+    add_quad(Q, tiles[u].M, tiles[u].X[0] - X[0], tiles[u].X[1] - X[1], tiles[u].X[2] - X[2]);
+  }
+  for (int k = 0; k < 6; ++k) Q[k] = fold_lanes<G>(Q[k]);
+  if (t == 0) {
+    c.M = M;
+    for (int k = 0; k < 3; ++k) c.X[k] = X[k];
+    for (int k = 0; k < 6; ++k) c.Q[k] = Q[k];
+  }
+}
+
+__global__ __launch_bounds__(kTB) void k_cell_moments(TreeCell* __restrict__ cells, const int32_t* __restrict__ lvl,
+                                                      const double* __restrict__ pos_s,
+                                                      const double* __restrict__ mass_s,
+                                                      const TileMoments* __restrict__ tiles) {
+  const int32_t ncell = lvl[kLevels];
+  const int t = threadIdx.x;
+  const int32_t nb = gridDim.x;
+  for (int64_t c = blockIdx.x + (int64_t)(t >> 3) * nb; c < ncell; c += (int64_t)(kTB / 8) * nb) {
+    const int32_t size = cells[c].end - cells[c].begin;
+    if (c > 0 && size <= kSmallCell) moments_of<8>(cells[c], pos_s, mass_s, tiles, 0, 0, t & 7);
+  }
+  for (int64_t c = blockIdx.x + (int64_t)(t >> 6) * nb; c < ncell; c += (int64_t)(kTB / 64) * nb) {
+    const int32_t b = cells[c].begin, e = cells[c].end;
+    if (c == 0 || e - b <= kSmallCell) continue;
+    int32_t tm0 = 0, tm1 = 0;
+    if (e - b > kDirectCell) {  // holds a whole tile: the tiles within [b, e)
+      tm0 = (int32_t)(((int64_t)b + kTB - 1) / kTB);
+      tm1 = e / kTB;
+    }
+    moments_of<64>(cells[c], pos_s, mass_s, tiles, tm0, tm1, t & 63);
   }
 }
 
@@ -730,7 +909,7 @@ __global__ __launch_bounds__(kGS, NB_TREE_WAVES) void k_tree_walk_forces(const i
   const int lane = threadIdx.x;
   const int32_t ngroups = *ngroups_dev;
   int32_t* stack = stack_all + (int64_t)blockIdx.x * stack_cap;
-  const int32_t root_child0 = cells[0].child0, root_nchild = cells[0].nchild;
+  const int32_t root_child0 = cells[0].child0, root_nchild = cells[0].child1 - root_child0;
   for (;;) {
     int32_t g = 0;
     if (lane == 0) g = (int32_t)atomicAdd(&counters[0], 1ull);
@@ -768,12 +947,12 @@ __global__ __launch_bounds__(kGS, NB_TREE_WAVES) void k_tree_walk_forces(const i
         const TreeCell& c = cells[cid];
         if (accepted(c, box, theta)) {
           kind = 0;
-        } else if (c.nchild == 0) {
+        } else if (c.child0 < 0) {
           kind = 1;
         } else {
           kind = 2;
-          nch = c.nchild;
           ch0 = c.child0;
+          nch = c.child1 - ch0;
         }
       }
       sp = base;
@@ -825,68 +1004,6 @@ __global__ __launch_bounds__(kGS, NB_TREE_WAVES) void k_tree_walk_forces(const i
       }
     }
     __syncthreads();
-  }
-}
-
-__global__ void k_zero_u64(unsigned long long* p, int n) {
-  if (blockIdx.x == 0 && (int)threadIdx.x < n) p[threadIdx.x] = 0ull;
-}
-
-// ---------------------------------------------------------------- scans -----
-// Exclusive prefix sum of n int32 counts by one workgroup (out may be in), in
-// rounds of kScanThreads x kScanPer consecutive entries: each thread loads
-// kScanPer consecutive counts, the thread sums are scanned within each
-// wavefront by shuffles and across the wavefronts through LDS (one barrier
-// per round: the wavefront totals alternate between two buffers, and a
-// wavefront can only overwrite a buffer after every wavefront has passed the
-// next round's barrier, i.e. finished reading it), and each thread writes its
-// entries' running sums.  Entries are read before they are written, by the
-// same thread, so out may be in.  n is n_host, or, when lvl is set, the cell
-// count of level l plus one (the extra zero count makes the last entry the
-// level's total).  Every sum counts cells or particles, so it stays below
-// 2^31.
-constexpr int kScanThreads = 1024;
-constexpr int kScanPer = 16;
-
-__global__ __launch_bounds__(kScanThreads) void k_exscan(const int32_t* in, int32_t* out, int64_t n_host,
-                                                         const int32_t* __restrict__ lvl, int l) {
-  constexpr int W = kScanThreads / 64;
-  __shared__ int32_t wsum[2][W];
-  const int64_t n = lvl ? (int64_t)(lvl[l + 1] - lvl[l]) + 1 : n_host;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  int32_t carry = 0;
-  int buf = 0;
-  for (int64_t base = 0; base < n; base += (int64_t)kScanThreads * kScanPer) {
-    const int64_t b = base + (int64_t)t * kScanPer;
-    int32_t v[kScanPer];
-#pragma unroll
-    for (int j = 0; j < kScanPer; ++j) v[j] = b + j < n ? in[b + j] : 0;
-    int32_t sum = 0;
-#pragma unroll
-    for (int j = 0; j < kScanPer; ++j) sum += v[j];
-    int32_t x = sum;  // inclusive scan of the thread sums over the wavefront
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int32_t y = __shfl_up(x, o, 64);
-      if (lane >= o) x += y;
-    }
-    if (lane == 63) wsum[buf][wave] = x;
-    __syncthreads();
-    int32_t before = 0, total = 0;
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-      const int32_t ws = wsum[buf][w];
-      before += w < wave ? ws : 0;
-      total += ws;
-    }
-    int32_t run = carry + before + x - sum;
-#pragma unroll
-    for (int j = 0; j < kScanPer; ++j) {
-      if (b + j < n) out[b + j] = run;
-      run += v[j];
-    }
-    carry += total;
-    buf ^= 1;
   }
 }
 
@@ -1056,14 +1173,9 @@ struct Alloc {
 };
 
 enum Slot {
-  S_BOXPART, S_BOX, S_KEYS, S_KEYS2, S_IDX, S_IDX2, S_POS, S_MASS, S_IJK, S_CELLS, S_CNT, S_OFF, S_TMP,
-  S_GB, S_GE, S_GN, S_GBOX, S_STACK, S_CTR, S_ENDS, S_LVL, S_HIST
+  S_BOXPART, S_BOX, S_KEYS, S_KEYS2, S_IDX, S_IDX2, S_POS, S_MASS, S_SPAN, S_CELLS, S_CNT,
+  S_GB, S_GE, S_GN, S_GBOX, S_STACK, S_CTR, S_LVL, S_HIST, S_TILE
 };
-
-hipError_t exclusive_sum(hipStream_t st, const int32_t* in, int32_t* out, int64_t n) {
-  hipLaunchKernelGGL(k_exscan, dim3(1), dim3(kScanThreads), 0, st, in, out, n, nullptr, 0);
-  return hipGetLastError();
-}
 
 // Sort (keys, idx) by the low `bits` bits of the keys; returns the buffers
 // holding the result (the inputs or the alternates, which are overwritten).
@@ -1167,56 +1279,33 @@ hipError_t tree_forces_run(TreeScratch& s, hipStream_t st, const double* pos, co
   }
   double* pos_s = al.get<double>(S_POS, 3 * (int64_t)n);
   double* mass_s = al.get<double>(S_MASS, n);
-  int32_t* ijk_s = al.get<int32_t>(S_IJK, 3 * (int64_t)n);
-  NB_TRY(need(ijk_s));
-  hipLaunchKernelGGL(k_gather, dim3(blocks_for(n)), dim3(kTB), 0, st, pos, mass, idx_s, (int64_t)n, box, pos_s,
-                     mass_s, ijk_s);
-  NB_TRY(hipGetLastError());
-
-  // cells, level by level, sized once by a bound: a cell that splits holds
-  // more than n_crit particles and the cells of one level are disjoint, so
-  // each level has at most n / (n_crit + 1) of them; the leaves hold at least
-  // one particle each, so there are at most n.  A level has at most
-  // min(n, 8 x that) cells.
+  // cells, sized by a bound: a cell that splits holds more than n_crit
+  // particles and the cells of one level are disjoint, so each level has at
+  // most n / (n_crit + 1) of them; the leaves hold at least one particle each,
+  // so there are at most n.
   const int64_t inner = n / ((int64_t)n_crit + 1);
   const int64_t cap_cells = 1 + (int64_t)kLevels * inner + n;
-  const int64_t per_level = std::min<int64_t>(n, 8 * inner + 8);
   TreeCell* cells = al.get<TreeCell>(S_CELLS, cap_cells);
+  uint16_t* span = al.get<uint16_t>(S_SPAN, n);
+  const int32_t ntile = (n + kTB - 1) / kTB;
+  int32_t* cnt = al.get<int32_t>(S_CNT, (int64_t)kRows * ntile + kRows);
   int32_t* lvl = al.get<int32_t>(S_LVL, kLevels + 1);
+  TileMoments* tiles = al.get<TileMoments>(S_TILE, ntile);
   const int32_t nchunk = (n + kGS - 1) / kGS;
-  int32_t* cnt = al.get<int32_t>(S_CNT, std::max<int64_t>(per_level + 1, nchunk));
-  int32_t* off = al.get<int32_t>(S_OFF, std::max<int64_t>(per_level + 1, nchunk));
-  int32_t* ends = al.get<int32_t>(S_ENDS, 8 * per_level);
-  NB_TRY(need(ends));
-  hipLaunchKernelGGL(k_root, dim3(1), dim3(64), 0, st, cells, n, ijk_s, box, lvl);
-  // grid-stride level kernels: a few hundred blocks cover the largest level
-  // and keep the launches of the empty levels below the tree cheap
-  const int gcount = blocks_for(8 * per_level, 256), gcell = blocks_for(per_level, 256);
-  for (int l = 0; l < kBits; ++l) {
-    hipLaunchKernelGGL(k_count_children, dim3(gcount), dim3(kTB), 0, st, cells, lvl, l, keys_s, n_crit, cnt, ends);
-    hipLaunchKernelGGL(k_exscan, dim3(1), dim3(kScanThreads), 0, st, cnt, off, (int64_t)0, lvl, l);
-    hipLaunchKernelGGL(k_write_children, dim3(gcell), dim3(kTB), 0, st, cells, lvl, l, ends, ijk_s, box, n_crit, off);
-  }
-  NB_TRY(hipGetLastError());
-  // moments from the deepest level up (empty levels return at once)
-  for (int l = kBits; l >= 0; --l)
-    hipLaunchKernelGGL(k_moments, dim3(gcell), dim3(kTB), 0, st, cells, lvl, l, pos_s, mass_s);
-  NB_TRY(hipGetLastError());
-
-  // groups: chunks of 64, halved while wider than g_max (one pass to count,
-  // one to write)
   int32_t* gb = al.get<int32_t>(S_GB, n);
   int32_t* ge = al.get<int32_t>(S_GE, n);
   int32_t* gn = al.get<int32_t>(S_GN, 1);
   double* gbox = al.get<double>(S_GBOX, 6 * (int64_t)n);
-  NB_TRY(need(gbox));
-  const int gblocks = blocks_for((int64_t)nchunk * kGS);
-  hipLaunchKernelGGL(k_groups<false>, dim3(gblocks), dim3(kTB), 0, st, n, nchunk, pos_s, box, g_frac, cnt,
-                     nullptr, nullptr, nullptr, nullptr);
-  NB_TRY(exclusive_sum(st, cnt, off, nchunk));
-  hipLaunchKernelGGL(k_groups<true>, dim3(gblocks), dim3(kTB), 0, st, n, nchunk, pos_s, box, g_frac, cnt, off,
-                     gb, ge, gn);
-  hipLaunchKernelGGL(k_group_box, dim3(blocks_for(n, 1024)), dim3(kTB), 0, st, gb, ge, gn, pos_s, gbox);
+  unsigned long long* ctr = al.get<unsigned long long>(S_CTR, 4);
+  NB_TRY(need(ctr));
+  int32_t* total = cnt + (int64_t)kRows * ntile;
+  hipLaunchKernelGGL(k_cell_starts, dim3(ntile), dim3(kTB), 0, st, keys_s, idx_s, pos, mass, n, n_crit, box, g_frac,
+                     pos_s, mass_s, span, cnt, ntile, tiles);
+  hipLaunchKernelGGL(k_level_scan, dim3(kRows), dim3(1024), 0, st, cnt, ntile, total, ctr);
+  hipLaunchKernelGGL(k_write_cells, dim3(ntile), dim3(kTB), 0, st, cells, span, cnt, total, ntile, n, pos_s,
+                     box, g_frac, lvl, gb, ge, gbox, gn);
+  hipLaunchKernelGGL(k_cell_moments, dim3((unsigned)std::min<int64_t>(1024, cap_cells)), dim3(kTB), 0, st, cells, lvl,
+                     pos_s, mass_s, tiles);
   NB_TRY(hipGetLastError());
 
   // walk and forces: one wavefront per group, groups handed out by a counter
@@ -1233,10 +1322,7 @@ hipError_t tree_forces_run(TreeScratch& s, hipStream_t st, const double* pos, co
   if (grid > 2 * (int64_t)nchunk) grid = 2 * (int64_t)nchunk;
   const int32_t cap = (int32_t)(cap_cells < kStackCap ? cap_cells : kStackCap);
   int32_t* stack = al.get<int32_t>(S_STACK, grid * cap);
-  unsigned long long* ctr = al.get<unsigned long long>(S_CTR, 4);
-  NB_TRY(need(ctr));
   NB_TRY(need(stack));
-  hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, st, ctr, 4);
   if (mixed)
     hipLaunchKernelGGL(k_tree_walk_forces<true>, dim3((unsigned)grid), dim3(kGS), 0, st, gb, ge, gn, gbox,
                        cells, theta, pos_s, mass_s, eps2, idx_s, stack, cap, ctr, err, acc, pot);

@@ -77,6 +77,27 @@ def test_tree_matches_oracle(ctx, n, theta, n_crit, seed):
     _close((acc, pot), (ra, rp), 1e-12, p.pos, p.mass, eps2)
 
 
+@pytest.mark.parametrize("n,n_crit,seed", [(64, 1, 21), (255, 16, 22), (256, 3, 23), (257, 1, 24), (513, 255, 25),
+                                           (1023, 254, 26), (1100, 256, 27), (2049, 300, 28), (5000, 2, 29)])
+def test_tree_build_at_the_edges_of_its_tiles(ctx, n, n_crit, seed):
+    # tiles of 256 particles, chunks of 64, the window maximum up to n_crit
+    # 255 and the bisection above, cells holding whole tiles; unequal and zero
+    # masses, and forty particles on one spot (a level-21 leaf)
+    p = synth.plummer(n, seed)
+    rng = np.random.default_rng(seed)
+    mass = p.mass * rng.uniform(0.0, 2.0, n)
+    mass[rng.integers(0, n, 5)] = 0.0
+    p.pos[rng.integers(0, n, 40)] = p.pos[0]
+    acc, pot, st = _gpu(ctx, p.pos, mass, 1e-3, 0.6, n_crit)
+    ra, rp, rst, t = _oracle(p.pos, mass, 1e-3, 0.6, n_crit)
+    assert st["cells"] == len(t.cells)
+    assert st["groups"] == len(rst)
+    assert st["accepted"] == sum(c for c, _, _ in rst)
+    assert st["opened_leaves"] == sum(l for _, l, _ in rst)
+    assert st["depth"] == max(c.level for c in t.cells)
+    _close((acc, pot), (ra, rp), 1e-12, p.pos, mass, 1e-3)
+
+
 def test_theta_zero_is_the_direct_sum(ctx):
     import torch
     p = synth.plummer(2000, 7)
