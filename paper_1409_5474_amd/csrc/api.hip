@@ -1042,7 +1042,7 @@ int nb_tree_forces(nb_ctx* c, const double* pos, const double* mass, int64_t N, 
   nb::TreeStats st{};
   hipError_t e = nb::tree_forces_run(c->tree, c->stream, pos, mass, (int32_t)N, eps2, theta, n_crit, g_frac,
                                      c->prec != NB_PREC_FP64, acc, pot, stats ? &st : nullptr, cap,
-                                     c->wq + nb::kErrorWord, &msg);
+                                     c->wq, c->wq + nb::kErrorWord, &msg);
   if (e == hipErrorStreamCaptureUnsupported)
     return fail(c, NB_ENOTSUP, "the tree buffers must grow: call once outside the capture with this N first%s");
   if (e == hipErrorInvalidValue) return fail(c, NB_ENOMEM, "%s", msg);

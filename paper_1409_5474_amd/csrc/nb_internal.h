@@ -296,16 +296,6 @@ hipError_t launch_energy(const double* pos, const double* vel, const double* mas
 int energy_blocks(int64_t n);
 
 // Tree code (tree.hip).
-struct TreeCell {
-  int32_t begin, end;      // range of the cell's particles along the curve
-  int32_t child0, child1;  // the children are [child0, child1); both -1 for a leaf
-  int32_t level, pad;
-  double corner[3];        // cube corner and side
-  double side;
-  double M;                // mass, centre of mass, traceless quadrupole
-  double X[3];
-  double Q[6];             // xx, yy, zz, xy, xz, yz
-};
 struct TreeStats {
   int64_t cells, groups, accepted, opened_leaves;
   int depth;
@@ -321,7 +311,8 @@ struct TreeScratch {
 // capture sizes them); a stack overflow is then flagged in *err only.
 hipError_t tree_forces_run(TreeScratch& s, hipStream_t st, const double* pos, const double* mass, int32_t n,
                            double eps2, double theta, int n_crit, double g_frac, bool mixed, double* acc,
-                           double* pot, TreeStats* stats, bool capturing, unsigned int* err, const char** msg);
+                           double* pot, TreeStats* stats, bool capturing, unsigned int* wq, unsigned int* err,
+                           const char** msg);
 // The Peano-Hilbert keys of the positions in curve order and the input row
 // of each (the tree code's first stage).
 hipError_t tree_sorted_keys(TreeScratch& s, hipStream_t st, const double* pos, int32_t n, uint64_t* keys_out,

@@ -42,6 +42,7 @@
 #include <vector>
 
 #include "nb_internal.h"
+#include "work_queue.h"
 
 namespace nb {
 namespace {
@@ -60,6 +61,30 @@ struct Box {
   double lo[3];
   double side;
   double h;
+};
+
+// A particle in curve order.
+struct Part {
+  double x[3], m;
+};
+
+// What the walk reads of a cell.
+struct TreeCell {
+  int32_t begin, end;      // range of the cell's particles along the curve
+  int32_t child0, child1;  // the children are [child0, child1); both -1 for a leaf
+  double corner[3];        // cube corner and side
+  double side;
+};
+// What the evaluation reads of it: centre of mass, mass and traceless
+// quadrupole (xx, yy, zz, xy, xz, yz).
+struct CellMom {
+  double X[3], M, Q[6];
+};
+// The same for the mixed terms: the separation is formed in double, the rest
+// is float.
+struct CellMomF {
+  double X[3];
+  float M, Q[6], pad[3];
 };
 
 // ---------------------------------------------------------------- box -----
@@ -194,9 +219,9 @@ __global__ __launch_bounds__(kTB) void k_keys(const double* __restrict__ pos, in
 // three kernels per level, 63 launches whatever the depth, took 0.3-0.35 ms
 // per evaluation of 10^4 and of 2.6 x 10^5 particles, most of it launches and
 // latency; these three take 26 and 40 us.)
-__device__ __forceinline__ void set_geometry(TreeCell& c, const int32_t* ijk, const Box& b) {
+__device__ __forceinline__ void set_geometry(TreeCell& c, int level, const int32_t* ijk, const Box& b) {
 #pragma clang fp contract(off)
-  const int shift = kBits - c.level;
+  const int shift = kBits - level;
   for (int k = 0; k < 3; ++k) {
     const int64_t ci = ((int64_t)ijk[k] >> shift) << shift;
     c.corner[k] = b.lo[k] + (double)ci * b.h;
@@ -204,6 +229,7 @@ __device__ __forceinline__ void set_geometry(TreeCell& c, const int32_t* ijk, co
   c.side = ldexp(b.h, shift);
 }
 
+constexpr int kCtrWords = 256;      // the walk's counters (kCtrLine words per XCD)
 constexpr int kRows = kLevels + 1;  // per-tile counts: cells starting on each level, then groups
 constexpr int kMaxWindow = 256;     // n_crit + 1 up to which the window maximum runs in LDS
 
@@ -351,9 +377,9 @@ __device__ __forceinline__ void block_fold(double* v, double (*red)[6]) {
 __global__ __launch_bounds__(kTB) void k_cell_starts(const uint64_t* __restrict__ keys, const int32_t* __restrict__ idx,
                                                      const double* __restrict__ pos, const double* __restrict__ mass,
                                                      int32_t n, int n_crit, const Box* __restrict__ box, double g_frac,
-                                                     double* __restrict__ pos_s, double* __restrict__ mass_s,
-                                                     uint16_t* __restrict__ span, int32_t* __restrict__ cnt,
-                                                     int32_t ntile, TileMoments* __restrict__ tiles) {
+                                                     Part* __restrict__ part, uint16_t* __restrict__ span,
+                                                     int32_t* __restrict__ cnt, int32_t ntile,
+                                                     TileMoments* __restrict__ tiles) {
   constexpr int W = kTB / kGS;
   __shared__ double red[2][W][6];
   __shared__ int8_t win[2][kTB + kMaxWindow];
@@ -365,12 +391,9 @@ __global__ __launch_bounds__(kTB) void k_cell_starts(const uint64_t* __restrict_
   double x[3] = {0.0, 0.0, 0.0}, pm = 0.0;
   if (valid) {
     const int64_t o = idx[i];
-    for (int k = 0; k < 3; ++k) {
-      x[k] = pos[3 * o + k];
-      pos_s[3 * (int64_t)i + k] = x[k];
-    }
+    for (int k = 0; k < 3; ++k) x[k] = pos[3 * o + k];
     pm = mass[o];
-    mass_s[i] = pm;
+    part[i] = Part{{x[0], x[1], x[2]}, pm};
   }
   {
     double v[4] = {pm, pm * x[0], pm * x[1], pm * x[2]}, q[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
@@ -466,7 +489,7 @@ __global__ __launch_bounds__(1024) void k_level_scan(int32_t* __restrict__ cnt, 
     buf ^= 1;
   }
   if (t == 0) total[blockIdx.x] = carry;
-  if (blockIdx.x == 0 && t < 4) ctr[t] = 0ull;
+  if (blockIdx.x == 0 && t < kCtrWords) ctr[t] = 0ull;
 }
 
 // Cells and groups at their places.  Thread i writes the cells its particle
@@ -477,7 +500,7 @@ __global__ __launch_bounds__(1024) void k_level_scan(int32_t* __restrict__ cnt, 
 __global__ __launch_bounds__(kTB) void k_write_cells(TreeCell* __restrict__ cells, const uint16_t* __restrict__ span,
                                                      const int32_t* __restrict__ cnt,
                                                      const int32_t* __restrict__ total, int32_t ntile, int32_t n,
-                                                     const double* __restrict__ pos_s, const Box* __restrict__ box,
+                                                     const Part* __restrict__ part, const Box* __restrict__ box,
                                                      double g_frac, int32_t* __restrict__ lvl,
                                                      int32_t* __restrict__ gb, int32_t* __restrict__ ge,
                                                      double* __restrict__ gbox, int32_t* __restrict__ ng) {
@@ -495,7 +518,7 @@ __global__ __launch_bounds__(kTB) void k_write_cells(TreeCell* __restrict__ cell
     const int sp = span[i];
     d = sp & 255;
     top = sp >> 8;
-    for (int k = 0; k < 3; ++k) x[k] = pos_s[3 * (int64_t)i + k];
+    for (int k = 0; k < 3; ++k) x[k] = part[i].x[k];
   }
   int32_t mine = 0;
   for (int l = 0; l < kLevels; ++l) {
@@ -548,8 +571,7 @@ __global__ __launch_bounds__(kTB) void k_write_cells(TreeCell* __restrict__ cell
     if (start) {
       TreeCell& cell = cells[c];
       cell.begin = i;
-      cell.level = l;
-      set_geometry(cell, q, bx);
+      set_geometry(cell, l, q, bx);
       if (l == top) cell.child0 = cell.child1 = -1;
       if (l > d) cells[above].child0 = c;
     }
@@ -580,10 +602,11 @@ constexpr int kSmallCell = 64;
 constexpr int kDirectCell = 512;  // up to here a wavefront takes the particles one by one
 
 // The moments of one cell by the G lanes `t`: of its tm0 <= tile < tm1 whole
-// tiles and of the particles before and after them.
+// tiles and of the particles before and after them.  momf: the float copy of
+// the mixed terms, when they are wanted.
 template <int G>
-__device__ __forceinline__ void moments_of(TreeCell& c, const double* __restrict__ pos_s,
-                                           const double* __restrict__ mass_s, const TileMoments* __restrict__ tiles,
+__device__ __forceinline__ void moments_of(const TreeCell& c, CellMom* __restrict__ mom, CellMomF* __restrict__ momf,
+                                           const Part* __restrict__ part, const TileMoments* __restrict__ tiles,
                                            int32_t tm0, int32_t tm1, int t) {
   const int32_t b = c.begin, e = c.end;
   const int32_t head = tm1 > tm0 ? tm0 * kTB - b : e - b;  // particles before the tiles (all of them without)
@@ -591,10 +614,9 @@ __device__ __forceinline__ void moments_of(TreeCell& c, const double* __restrict
   const int32_t singles = e - b - skip;
   double M = 0.0, S[3] = {0.0, 0.0, 0.0}, Q[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, X[3];
   for (int32_t u = t; u < singles; u += G) {
-    const int64_t j = b + u + (u < head ? 0 : skip);
-    const double m = mass_s[j];
-    M += m;
-    for (int k = 0; k < 3; ++k) S[k] += m * pos_s[3 * j + k];
+    const Part p = part[(int64_t)b + u + (u < head ? 0 : skip)];
+    M += p.m;
+    for (int k = 0; k < 3; ++k) S[k] += p.m * p.x[k];
   }
   for (int32_t u = tm0 + t; u < tm1; u += G) {
     M += tiles[u].M;
@@ -606,31 +628,41 @@ __device__ __forceinline__ void moments_of(TreeCell& c, const double* __restrict
     X[k] = M > 0.0 ? S[k] / M : c.corner[k] + 0.5 * c.side;
   }
   for (int32_t u = t; u < singles; u += G) {
-    const int64_t j = b + u + (u < head ? 0 : skip);
-    add_quad(Q, mass_s[j], pos_s[3 * j] - X[0], pos_s[3 * j + 1] - X[1], pos_s[3 * j + 2] - X[2]);
+    const Part p = part[(int64_t)b + u + (u < head ? 0 : skip)];
+    add_quad(Q, p.m, p.x[0] - X[0], p.x[1] - X[1], p.x[2] - X[2]);
   }
   for (int32_t u = tm0 + t; u < tm1; u += G) {
     for (int k = 0; k < 6; ++k) Q[k] += tiles[u].Q[k];
     add_quad(Q, tiles[u].M, tiles[u].X[0] - X[0], tiles[u].X[1] - X[1], tiles[u].X[2] - X[2]);
   }
   for (int k = 0; k < 6; ++k) Q[k] = fold_lanes<G>(Q[k]);
-  if (t == 0) {
-    c.M = M;
-    for (int k = 0; k < 3; ++k) c.X[k] = X[k];
-    for (int k = 0; k < 6; ++k) c.Q[k] = Q[k];
+  if (t != 0) return;
+  if (momf) {
+    CellMomF f{};
+    f.M = (float)M;
+    for (int k = 0; k < 3; ++k) f.X[k] = X[k];
+    for (int k = 0; k < 6; ++k) f.Q[k] = (float)Q[k];
+    *momf = f;
+  } else {
+    CellMom f;
+    f.M = M;
+    for (int k = 0; k < 3; ++k) f.X[k] = X[k];
+    for (int k = 0; k < 6; ++k) f.Q[k] = Q[k];
+    *mom = f;
   }
 }
 
-__global__ __launch_bounds__(kTB) void k_cell_moments(TreeCell* __restrict__ cells, const int32_t* __restrict__ lvl,
-                                                      const double* __restrict__ pos_s,
-                                                      const double* __restrict__ mass_s,
+__global__ __launch_bounds__(kTB) void k_cell_moments(const TreeCell* __restrict__ cells, CellMom* __restrict__ mom,
+                                                      CellMomF* __restrict__ momf, const int32_t* __restrict__ lvl,
+                                                      const Part* __restrict__ part,
                                                       const TileMoments* __restrict__ tiles) {
   const int32_t ncell = lvl[kLevels];
   const int t = threadIdx.x;
   const int32_t nb = gridDim.x;
   for (int64_t c = blockIdx.x + (int64_t)(t >> 3) * nb; c < ncell; c += (int64_t)(kTB / 8) * nb) {
     const int32_t size = cells[c].end - cells[c].begin;
-    if (c > 0 && size <= kSmallCell) moments_of<8>(cells[c], pos_s, mass_s, tiles, 0, 0, t & 7);
+    if (c > 0 && size <= kSmallCell)
+      moments_of<8>(cells[c], mom + c, momf ? momf + c : nullptr, part, tiles, 0, 0, t & 7);
   }
   for (int64_t c = blockIdx.x + (int64_t)(t >> 6) * nb; c < ncell; c += (int64_t)(kTB / 64) * nb) {
     const int32_t b = cells[c].begin, e = cells[c].end;
@@ -640,7 +672,7 @@ __global__ __launch_bounds__(kTB) void k_cell_moments(TreeCell* __restrict__ cel
       tm0 = (int32_t)(((int64_t)b + kTB - 1) / kTB);
       tm1 = e / kTB;
     }
-    moments_of<64>(cells[c], pos_s, mass_s, tiles, tm0, tm1, t & 63);
+    moments_of<64>(cells[c], mom + c, momf ? momf + c : nullptr, part, tiles, tm0, tm1, t & 63);
   }
 }
 
@@ -655,7 +687,7 @@ __global__ __launch_bounds__(kTB) void k_cell_moments(TreeCell* __restrict__ cel
 // Walk step: pop up to 64 cells from the top of the stack, one per lane;
 // each lane tests its cell and the wavefront appends accepted cells and
 // opened leaves to two LDS lists (ballot + rank) and pushes the children of
-// opened internal cells, in lane order, onto the stack (wave prefix sum).
+// opened internal cells, in lane order, onto the stack (prefix sum).
 // Bound on the stack: the pushes keep it ordered by level from bottom to
 // top (lane order is stack order, children sit one level below their
 // parents, and what is left after a pop is no deeper than what was popped).
@@ -699,312 +731,501 @@ __device__ __forceinline__ int wave_inclusive_sum(int v, int lane) {
   return v;
 }
 
-struct CellLite {
-  double M, X[3], Q[6];
-};
-// Mixed precision: the separation from a cell's centre of mass or from a
-// particle is formed in double and rounded to float, the rest of the term
-// is float; the float sums of one staged chunk (at most 64 cells or 64
-// particles) are added into double accumulators.  The walk, and so the
-// interaction set, is the double one.
-struct CellLiteF {
-  double X[3];
-  float M, Q[6], pad;
-};
-
-// LDS of one wavefront: the staged cells and the staged leaf particles are
-// never live at the same time and share their storage.
-template <bool MIXED>
-struct WalkLds {
-  using Cell = typename std::conditional<MIXED, CellLiteF, CellLite>::type;
-  struct Parts {
-    double px[kGS], py[kGS], pz[kGS], pm[kGS];
-    int32_t pj[kGS];
-  };
-  union {
-    Cell tile[kGS];
-    Parts p;
-  };
-  int32_t acc_list[2 * kGS];
-  int32_t leaf_list[2 * kGS];
-  int32_t leaf_begin[kGS];
-  int32_t leaf_pre[kGS + 1];
-};
+// What one lane of a wavefront has written, in LDS or memory, is read by
+// others of the same wavefront after this.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+}
 
 struct Accum {
   double a0, a1, a2, ph;
 };
 
-// The first `cnt` (<= 64) accepted cells of the list: each lane stages one
-// cell, then every lane adds all of them to its particle.
-template <bool MIXED>
-__device__ __forceinline__ void eval_cells(WalkLds<MIXED>& L, int cnt, const TreeCell* __restrict__ cells,
-                                           double x0, double x1, double x2, double eps2, Accum& A, int lane) {
-  if (lane < cnt) {
-    const TreeCell& c = cells[L.acc_list[lane]];
-    if constexpr (MIXED) {
-      CellLiteF cl;
-      cl.M = (float)c.M;
-      for (int q = 0; q < 3; ++q) cl.X[q] = c.X[q];
-      for (int q = 0; q < 6; ++q) cl.Q[q] = (float)c.Q[q];
-      cl.pad = 0.0f;
-      L.tile[lane] = cl;
-    } else {
-      CellLite cl;
-      cl.M = c.M;
-      for (int q = 0; q < 3; ++q) cl.X[q] = c.X[q];
-      for (int q = 0; q < 6; ++q) cl.Q[q] = c.Q[q];
-      L.tile[lane] = cl;
-    }
-  }
-  __syncthreads();
-  if constexpr (MIXED) {
-    const float e2 = (float)eps2;
-    float f0 = 0.0f, f1 = 0.0f, f2 = 0.0f, fp = 0.0f;
-    for (int t = 0; t < cnt; ++t) {
-      const CellLiteF& c = L.tile[t];
-      const float y0 = (float)(x0 - c.X[0]), y1 = (float)(x1 - c.X[1]), y2 = (float)(x2 - c.X[2]);
-      const float s = fmaf(y2, y2, fmaf(y1, y1, fmaf(y0, y0, e2)));
-      const float q = __builtin_amdgcn_rsqf(s);
-      const float q2 = q * q;
-      const float q3 = q2 * q, q5 = q3 * q2;
-      const float Qy0 = c.Q[0] * y0 + c.Q[3] * y1 + c.Q[4] * y2;
-      const float Qy1 = c.Q[3] * y0 + c.Q[1] * y1 + c.Q[5] * y2;
-      const float Qy2 = c.Q[4] * y0 + c.Q[5] * y1 + c.Q[2] * y2;
-      const float w = (y0 * Qy0 + y1 * Qy1 + y2 * Qy2) * q5;  // (y.Qy) s^-5/2
-      const float f = fmaf(-2.5f * w, q2, -c.M * q3);         // -M s^-3/2 - (5/2)(y.Qy) s^-7/2
-      f0 = fmaf(Qy0, q5, fmaf(f, y0, f0));
-      f1 = fmaf(Qy1, q5, fmaf(f, y1, f1));
-      f2 = fmaf(Qy2, q5, fmaf(f, y2, f2));
-      fp = fmaf(-0.5f, w, fmaf(-c.M, q, fp));
-    }
-    A.a0 += (double)f0; A.a1 += (double)f1; A.a2 += (double)f2; A.ph += (double)fp;
-  } else {
-    for (int t = 0; t < cnt; ++t) {
-      const CellLite& c = L.tile[t];
-      const double y0 = x0 - c.X[0], y1 = x1 - c.X[1], y2 = x2 - c.X[2];
-      const double s = fma(y2, y2, fma(y1, y1, fma(y0, y0, eps2)));
-      const double q = rsqrt_tree(s);
-      const double q2 = q * q;
-      const double q3 = q2 * q, q5 = q3 * q2;
-      const double Qy0 = c.Q[0] * y0 + c.Q[3] * y1 + c.Q[4] * y2;
-      const double Qy1 = c.Q[3] * y0 + c.Q[1] * y1 + c.Q[5] * y2;
-      const double Qy2 = c.Q[4] * y0 + c.Q[5] * y1 + c.Q[2] * y2;
-      const double w = (y0 * Qy0 + y1 * Qy1 + y2 * Qy2) * q5;  // (y.Qy) s^-5/2
-      const double f = fma(-2.5 * w, q2, -c.M * q3);          // -M s^-3/2 - (5/2)(y.Qy) s^-7/2
-      A.a0 = fma(Qy0, q5, fma(f, y0, A.a0));
-      A.a1 = fma(Qy1, q5, fma(f, y1, A.a1));
-      A.a2 = fma(Qy2, q5, fma(f, y2, A.a2));
-      A.ph = fma(-0.5, w, fma(-c.M, q, A.ph));
-    }
-  }
-  __syncthreads();
+// One cell on the lane's particle.  In double the sums go straight into A; in
+// mixed precision the separation from the centre of mass is formed in double
+// and rounded, the rest of the term is float, and the float sums F of one
+// chunk (64 cells of the list) are added into A at its end.
+__device__ __forceinline__ void cell_term(const CellMomF& c, double x0, double x1, double x2, float e2, float* F) {
+  const float y0 = (float)(x0 - c.X[0]), y1 = (float)(x1 - c.X[1]), y2 = (float)(x2 - c.X[2]);
+  const float s = fmaf(y2, y2, fmaf(y1, y1, fmaf(y0, y0, e2)));
+  const float q = __builtin_amdgcn_rsqf(s);
+  const float q2 = q * q;
+  const float q3 = q2 * q, q5 = q3 * q2;
+  const float Qy0 = c.Q[0] * y0 + c.Q[3] * y1 + c.Q[4] * y2;
+  const float Qy1 = c.Q[3] * y0 + c.Q[1] * y1 + c.Q[5] * y2;
+  const float Qy2 = c.Q[4] * y0 + c.Q[5] * y1 + c.Q[2] * y2;
+  const float w = (y0 * Qy0 + y1 * Qy1 + y2 * Qy2) * q5;  // (y.Qy) s^-5/2
+  const float f = fmaf(-2.5f * w, q2, -c.M * q3);         // -M s^-3/2 - (5/2)(y.Qy) s^-7/2
+  F[0] = fmaf(Qy0, q5, fmaf(f, y0, F[0]));
+  F[1] = fmaf(Qy1, q5, fmaf(f, y1, F[1]));
+  F[2] = fmaf(Qy2, q5, fmaf(f, y2, F[2]));
+  F[3] = fmaf(-0.5f, w, fmaf(-c.M, q, F[3]));
+}
+__device__ __forceinline__ void cell_term(const CellMom& c, double x0, double x1, double x2, double e2, double* F) {
+  const double y0 = x0 - c.X[0], y1 = x1 - c.X[1], y2 = x2 - c.X[2];
+  const double s = fma(y2, y2, fma(y1, y1, fma(y0, y0, e2)));
+  const double q = rsqrt_tree(s);
+  const double q2 = q * q;
+  const double q3 = q2 * q, q5 = q3 * q2;
+  const double Qy0 = c.Q[0] * y0 + c.Q[3] * y1 + c.Q[4] * y2;
+  const double Qy1 = c.Q[3] * y0 + c.Q[1] * y1 + c.Q[5] * y2;
+  const double Qy2 = c.Q[4] * y0 + c.Q[5] * y1 + c.Q[2] * y2;
+  const double w = (y0 * Qy0 + y1 * Qy1 + y2 * Qy2) * q5;  // (y.Qy) s^-5/2
+  const double f = fma(-2.5 * w, q2, -c.M * q3);          // -M s^-3/2 - (5/2)(y.Qy) s^-7/2
+  F[0] = fma(Qy0, q5, fma(f, y0, F[0]));
+  F[1] = fma(Qy1, q5, fma(f, y1, F[1]));
+  F[2] = fma(Qy2, q5, fma(f, y2, F[2]));
+  F[3] = fma(-0.5, w, fma(-c.M, q, F[3]));
 }
 
-// The particles of the first `cnt` (<= 64) opened leaves of the list, 64 at
-// a time: lane p stages particle p of the chunk (found by a binary search
-// over the leaves' prefix sums), then every lane adds the chunk's pair terms
-// to its particle, skipping itself and coincident particles.
+// One leaf particle on the lane's particle (itself and coincident ones are
+// skipped).
+__device__ __forceinline__ void part_term(const Part& p, bool self, double x0, double x1, double x2, float e2,
+                                          float* F) {
+  const float r0 = (float)(p.x[0] - x0), r1 = (float)(p.x[1] - x1), r2 = (float)(p.x[2] - x2);
+  const float s = fmaf(r2, r2, fmaf(r1, r1, fmaf(r0, r0, e2)));
+  const bool keep = !self && s > 0.0f;
+  const float q = keep ? __builtin_amdgcn_rsqf(s) : 0.0f;
+  const float mq = (float)p.m * q;
+  const float mq3 = mq * q * q;
+  F[0] += mq3 * r0;
+  F[1] += mq3 * r1;
+  F[2] += mq3 * r2;
+  F[3] -= mq;
+}
+__device__ __forceinline__ void part_term(const Part& p, bool self, double x0, double x1, double x2, double e2,
+                                          double* F) {
+  const double r0 = p.x[0] - x0, r1 = p.x[1] - x1, r2 = p.x[2] - x2;
+  const double s = fma(r2, r2, fma(r1, r1, fma(r0, r0, e2)));
+  const bool keep = !self && s > 0.0;
+  const double q = keep ? rsqrt_tree(s) : 0.0;
+  const double mq = p.m * q;
+  const double mq3 = mq * q * q;
+  F[0] += mq3 * r0;
+  F[1] += mq3 * r1;
+  F[2] += mq3 * r2;
+  F[3] -= mq;
+}
+
 template <bool MIXED>
-__device__ __forceinline__ void eval_leaves(WalkLds<MIXED>& L, int cnt, const TreeCell* __restrict__ cells,
-                                            const double* __restrict__ pos_s, const double* __restrict__ mass_s,
+struct Terms {
+  using Mom = typename std::conditional<MIXED, CellMomF, CellMom>::type;
+  using T = typename std::conditional<MIXED, float, double>::type;
+};
+
+// The sums of one chunk: in double the accumulators themselves.
+template <bool MIXED>
+__device__ __forceinline__ void chunk_open(const Accum& A, typename Terms<MIXED>::T* F) {
+  if constexpr (MIXED) {
+    F[0] = F[1] = F[2] = F[3] = 0.0f;
+  } else {
+    F[0] = A.a0; F[1] = A.a1; F[2] = A.a2; F[3] = A.ph;
+  }
+}
+template <bool MIXED>
+__device__ __forceinline__ void chunk_close(Accum& A, const typename Terms<MIXED>::T* F) {
+  if constexpr (MIXED) {
+    A.a0 += (double)F[0]; A.a1 += (double)F[1]; A.a2 += (double)F[2]; A.ph += (double)F[3];
+  } else {
+    A.a0 = F[0]; A.a1 = F[1]; A.a2 = F[2]; A.ph = F[3];
+  }
+}
+
+// What a wavefront stages for evaluation: up to 64 cells or 64 leaf
+// particles, never both at a time.
+template <bool MIXED>
+struct Stage {
+  struct Parts {
+    Part p[kGS];
+    int32_t j[kGS];
+  };
+  union {
+    typename Terms<MIXED>::Mom cell[kGS];
+    Parts leaf;
+  };
+  int32_t begin[kGS], incl[kGS];
+};
+
+// The cnt (1 to 64) cells of a list: each lane stages one, then every lane
+// adds all of them to its particle.
+template <bool MIXED>
+__device__ __forceinline__ void eval_cells(Stage<MIXED>& st, const int32_t* list, int cnt,
+                                           const typename Terms<MIXED>::Mom* __restrict__ mom, double x0, double x1,
+                                           double x2, double eps2, Accum& A, int lane) {
+  using T = typename Terms<MIXED>::T;
+  if (lane < cnt) st.cell[lane] = mom[list[lane]];
+  wave_sync();
+  const T e2 = (T)eps2;
+  T F[4];
+  chunk_open<MIXED>(A, F);
+  for (int t = 0; t < cnt; ++t) cell_term(st.cell[t], x0, x1, x2, e2, F);
+  chunk_close<MIXED>(A, F);
+  wave_sync();
+}
+
+// The particles of the cnt (<= 64) leaves of a list, one leaf after another,
+// in chunks of 64: this call evaluates chunks u0, u0 + ustep, ...  Lane p
+// stages particle p of the chunk (found by a binary search over the leaves'
+// prefix sums).
+template <bool MIXED>
+__device__ __forceinline__ void eval_leaves(Stage<MIXED>& st, const int32_t* list, int cnt,
+                                            const TreeCell* __restrict__ cells, const Part* __restrict__ part,
                                             int32_t i, double x0, double x1, double x2, double eps2, Accum& A,
-                                            int lane) {
+                                            int lane, int u0, int ustep) {
+  using T = typename Terms<MIXED>::T;
   int size = 0, begin = 0;
   if (lane < cnt) {
-    const TreeCell& c = cells[L.leaf_list[lane]];
+    const TreeCell& c = cells[list[lane]];
     begin = c.begin;
     size = c.end - c.begin;
   }
   const int incl = wave_inclusive_sum(size, lane);
-  const int total = __shfl(incl, kGS - 1, kGS);
-  L.leaf_begin[lane] = begin;
-  L.leaf_pre[lane + 1] = incl;
-  if (lane == 0) L.leaf_pre[0] = 0;
-  __syncthreads();
-  for (int base = 0; base < total; base += kGS) {
+  const int total = __builtin_amdgcn_readlane(incl, kGS - 1);
+  st.begin[lane] = begin;
+  st.incl[lane] = incl;
+  wave_sync();
+  const T e2 = (T)eps2;
+  for (int base = u0 * kGS; base < total; base += ustep * kGS) {
     const int f = base + lane;
     if (f < total) {
-      // the leaf k < cnt with leaf_pre[k] <= f < leaf_pre[k + 1]
+      // the first leaf k whose prefix sum exceeds f
       int lo = 0, hi = cnt - 1;
       while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (L.leaf_pre[mid] <= f) lo = mid;
-        else hi = mid - 1;
+        const int mid = (lo + hi) >> 1;
+        if (st.incl[mid] > f) hi = mid;
+        else lo = mid + 1;
       }
-      const int32_t j = L.leaf_begin[lo] + (f - L.leaf_pre[lo]);
-      L.p.px[lane] = pos_s[3 * j];
-      L.p.py[lane] = pos_s[3 * j + 1];
-      L.p.pz[lane] = pos_s[3 * j + 2];
-      L.p.pm[lane] = mass_s[j];
-      L.p.pj[lane] = j;
+      const int32_t j = st.begin[lo] + (f - (lo > 0 ? st.incl[lo - 1] : 0));
+      st.leaf.p[lane] = part[j];
+      st.leaf.j[lane] = j;
     }
-    __syncthreads();
+    wave_sync();
     const int m = total - base < kGS ? total - base : kGS;
-    if constexpr (MIXED) {
-      const float e2 = (float)eps2;
-      float f0 = 0.0f, f1 = 0.0f, f2 = 0.0f, fp = 0.0f;
+    T F[4];
+    chunk_open<MIXED>(A, F);
 #pragma unroll 4
-      for (int t = 0; t < m; ++t) {
-        const float r0 = (float)(L.p.px[t] - x0), r1 = (float)(L.p.py[t] - x1), r2 = (float)(L.p.pz[t] - x2);
-        const float s = fmaf(r2, r2, fmaf(r1, r1, fmaf(r0, r0, e2)));
-        const bool keep = L.p.pj[t] != i && s > 0.0f;
-        const float q = keep ? __builtin_amdgcn_rsqf(s) : 0.0f;
-        const float mq = (float)L.p.pm[t] * q;
-        const float mq3 = mq * q * q;
-        f0 += mq3 * r0;
-        f1 += mq3 * r1;
-        f2 += mq3 * r2;
-        fp -= mq;
-      }
-      A.a0 += (double)f0; A.a1 += (double)f1; A.a2 += (double)f2; A.ph += (double)fp;
-    } else {
-#pragma unroll 4
-      for (int t = 0; t < m; ++t) {
-        const double r0 = L.p.px[t] - x0, r1 = L.p.py[t] - x1, r2 = L.p.pz[t] - x2;
-        const double s = fma(r2, r2, fma(r1, r1, fma(r0, r0, eps2)));
-        const bool keep = L.p.pj[t] != i && s > 0.0;
-        const double q = keep ? rsqrt_tree(s) : 0.0;
-        const double mq = L.p.pm[t] * q;
-        const double mq3 = mq * q * q;
-        A.a0 += mq3 * r0;
-        A.a1 += mq3 * r1;
-        A.a2 += mq3 * r2;
-        A.ph -= mq;
-      }
-    }
-    __syncthreads();
+    for (int t = 0; t < m; ++t) part_term(st.leaf.p[t], st.leaf.j[t] == i, x0, x1, x2, e2, F);
+    chunk_close<MIXED>(A, F);
+    wave_sync();
   }
 }
 
 // drop the first 64 entries of a list of n (64 <= n < 128)
 __device__ __forceinline__ void shift_list(int32_t* list, int n, int lane) {
   const int32_t v = lane + kGS < n ? list[lane + kGS] : 0;
-  __syncthreads();
+  wave_sync();
   if (lane + kGS < n) list[lane] = v;
-  __syncthreads();
+  wave_sync();
 }
 
-// Waves per SIMD asked of the register allocator.
-#ifndef NB_TREE_WAVES
-#define NB_TREE_WAVES 1
-#endif
+// The stack of a walk: its first LDS entries in LDS, the rest in memory.
+template <int LDS>
+struct Stack {
+  int32_t* near_;
+  int32_t* far_;
+  __device__ __forceinline__ int32_t get(int k) const {
+    if constexpr (LDS > 0) return k < LDS ? near_[k] : far_[k];
+    else return far_[k];
+  }
+  __device__ __forceinline__ void put(int k, int32_t v) const {
+    if constexpr (LDS > 0) {
+      if (k < LDS) near_[k] = v;
+      else far_[k] = v;
+    } else {
+      far_[k] = v;
+    }
+  }
+};
 
-// counters[0]: next group, [1]: accepted (group, cell) pairs, [2]: opened
-// (group, leaf) pairs, [3]: stack overflow flag
+// One step of a walk by one wavefront.  Returns false when the push does not
+// fit the stack.
+template <int LDS>
+__device__ __forceinline__ bool walk_step(const Stack<LDS>& stack, int& sp, int32_t stack_cap, int32_t* acc_list,
+                                          int& n_acc, int32_t* leaf_list, int& n_leaf,
+                                          const TreeCell* __restrict__ cells, const double* box, double theta,
+                                          int lane) {
+  const int k = sp < kGS ? sp : kGS;
+  const int base = sp - k;
+  int kind = 3, nch = 0, ch0 = 0;
+  int32_t cid = 0;
+  if (lane < k) {
+    cid = stack.get(base + lane);
+    const TreeCell c = cells[cid];
+    if (accepted(c, box, theta)) {
+      kind = 0;
+    } else if (c.child0 < 0) {
+      kind = 1;
+    } else {
+      kind = 2;
+      ch0 = c.child0;
+      nch = c.child1 - ch0;
+    }
+  }
+  sp = base;
+  const uint64_t ma = __ballot(kind == 0), ml = __ballot(kind == 1);
+  if (kind == 0) acc_list[n_acc + lane_rank(ma)] = cid;
+  if (kind == 1) leaf_list[n_leaf + lane_rank(ml)] = cid;
+  n_acc += __popcll(ma);
+  n_leaf += __popcll(ml);
+  // where each lane's children go: the prefix of nch (0 to 8) over the lanes,
+  // bit by bit from ballots
+  int before = 0, pushed = 0;
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    const uint64_t m = __ballot((nch >> b) & 1);
+    before += lane_rank(m) << b;
+    pushed += __popcll(m) << b;
+  }
+  if (sp + pushed > stack_cap) return false;
+  for (int t = 0; t < nch; ++t) stack.put(sp + before + t, ch0 + t);
+  sp += pushed;
+  wave_sync();
+  return true;
+}
+
+struct WalkArgs {
+  const int32_t* gb;
+  const int32_t* ge;
+  const int32_t* ngroups;
+  const double* gbox;
+  const TreeCell* cells;
+  const void* mom;            // CellMom or CellMomF [cells]
+  const Part* part;
+  const int32_t* idx;         // input row of each particle
+  double theta, eps2;
+  int32_t* stack;             // stack_cap entries per workgroup
+  int32_t stack_cap;
+  unsigned int* wq;           // work queue (work_queue.h)
+  unsigned long long* ctr;    // kCtrLine words per XCD: accepted pairs, opened pairs, stack overflow; null: not counted
+  unsigned int* err;
+  double* acc;
+  double* pot;
+};
+constexpr int kCtrLine = 32;  // 64-bit words between the XCDs' counters
+static_assert(kCtrLine * kXcd == kCtrWords, "counter buffer");
+
+__device__ __forceinline__ void walk_count(const WalkArgs& a, unsigned long long acc, unsigned long long leaf,
+                                           bool overflow) {
+  if (a.ctr) {
+    unsigned long long* c = a.ctr + (blockIdx.x % kXcd) * kCtrLine;
+    atomicAdd(&c[0], acc);
+    atomicAdd(&c[1], leaf);
+    if (overflow) atomicOr(&c[2], 1ull);
+  }
+  if (overflow && a.err) atomicOr(a.err, kErrTreeStack);
+}
+
+// Many groups: one wavefront per workgroup, each walking and evaluating the
+// groups it takes from the work queue, dealt to the XCDs in turn along the
+// curve (groups in dense regions cost several times the others).
 template <bool MIXED>
-__global__ __launch_bounds__(kGS, NB_TREE_WAVES) void k_tree_walk_forces(const int32_t* __restrict__ gb,
-                                                          const int32_t* __restrict__ ge,
-                                                          const int32_t* __restrict__ ngroups_dev,
-                                                          const double* __restrict__ gbox,
-                                                          const TreeCell* __restrict__ cells, double theta,
-                                                          const double* __restrict__ pos_s,
-                                                          const double* __restrict__ mass_s, double eps2,
-                                                          const int32_t* __restrict__ idx_s,
-                                                          int32_t* __restrict__ stack_all, int32_t stack_cap,
-                                                          unsigned long long* __restrict__ counters,
-                                                          unsigned int* __restrict__ err,
-                                                          double* __restrict__ acc, double* __restrict__ pot) {
-  __shared__ WalkLds<MIXED> L;
+__global__ __launch_bounds__(kGS) void k_tree_walk_forces(WalkArgs a) {
+  __shared__ Stage<MIXED> stage;
+  __shared__ int32_t acc_list[2 * kGS], leaf_list[2 * kGS];
+  __shared__ unsigned int slot;
+  using Mom = typename Terms<MIXED>::Mom;
+  const TreeCell* __restrict__ cells = a.cells;
+  const Mom* __restrict__ mom = static_cast<const Mom*>(a.mom);
+  const Part* __restrict__ part = a.part;
   const int lane = threadIdx.x;
-  const int32_t ngroups = *ngroups_dev;
-  int32_t* stack = stack_all + (int64_t)blockIdx.x * stack_cap;
+  const int64_t ngroups = *a.ngroups;
+  const Stack<0> stack{nullptr, a.stack + (int64_t)blockIdx.x * a.stack_cap};
   const int32_t root_child0 = cells[0].child0, root_nchild = cells[0].child1 - root_child0;
-  for (;;) {
-    int32_t g = 0;
-    if (lane == 0) g = (int32_t)atomicAdd(&counters[0], 1ull);
-    g = __shfl(g, 0, kGS);
-    if (g >= ngroups) break;
-    const int32_t b = gb[g], e = ge[g];
+  unsigned long long tot_acc = 0, tot_leaf = 0;
+  bool overflow = false;
+  if (!queue_member(ngroups)) return;
+  int64_t w = queue_first(a.wq, ngroups);
+  while (w < ngroups) {
+    const int64_t g = interleaved(w, ngroups);
+    const int32_t b = a.gb[g], e = a.ge[g];
     const int32_t i = b + lane;
     const bool valid = i < e;
     const int32_t ir = valid ? i : b;
-    const double x0 = pos_s[3 * ir], x1 = pos_s[3 * ir + 1], x2 = pos_s[3 * ir + 2];
+    const double x0 = part[ir].x[0], x1 = part[ir].x[1], x2 = part[ir].x[2];
     double box[6];
-    for (int k = 0; k < 6; ++k) box[k] = gbox[6 * g + k];
+    for (int k = 0; k < 6; ++k) box[k] = a.gbox[6 * g + k];
     Accum A{0.0, 0.0, 0.0, 0.0};
     // the root is never accepted: the walk starts from its children, or
     // opens it when it is a leaf
     int sp = 0, n_acc = 0, n_leaf = 0;
-    unsigned long long tot_acc = 0, tot_leaf = 0;
-    bool overflow = false;
+    bool fits = true;
     if (root_nchild > 0) {
-      if (lane < root_nchild) stack[lane] = root_child0 + lane;
+      if (lane < root_nchild) stack.put(lane, root_child0 + lane);
       sp = root_nchild;
     } else {
-      if (lane == 0) L.leaf_list[0] = 0;
+      if (lane == 0) leaf_list[0] = 0;
       n_leaf = 1;
-      tot_leaf = 1;
     }
-    __syncthreads();
+    wave_sync();
     while (sp > 0) {
-      const int k = sp < kGS ? sp : kGS;
-      const int base = sp - k;
-      int kind = 3, nch = 0, ch0 = 0;
-      int32_t cid = 0;
-      if (lane < k) {
-        cid = stack[base + lane];
-        const TreeCell& c = cells[cid];
-        if (accepted(c, box, theta)) {
-          kind = 0;
-        } else if (c.child0 < 0) {
-          kind = 1;
-        } else {
-          kind = 2;
-          ch0 = c.child0;
-          nch = c.child1 - ch0;
-        }
-      }
-      sp = base;
-      const uint64_t ma = __ballot(kind == 0), ml = __ballot(kind == 1);
-      if (kind == 0) L.acc_list[n_acc + lane_rank(ma)] = cid;
-      if (kind == 1) L.leaf_list[n_leaf + lane_rank(ml)] = cid;
-      n_acc += __popcll(ma);
-      n_leaf += __popcll(ml);
-      tot_acc += __popcll(ma);
-      tot_leaf += __popcll(ml);
-      const int incl = wave_inclusive_sum(nch, lane);
-      const int pushed = __shfl(incl, kGS - 1, kGS);
-      if (sp + pushed > stack_cap) {
-        overflow = true;
-        break;
-      }
-      for (int t = 0; t < nch; ++t) stack[sp + incl - nch + t] = ch0 + t;
-      sp += pushed;
-      __syncthreads();
+      fits = walk_step<0>(stack, sp, a.stack_cap, acc_list, n_acc, leaf_list, n_leaf, cells, box, a.theta, lane);
+      if (!fits) break;
       if (n_acc >= kGS) {
-        eval_cells<MIXED>(L, kGS, cells, x0, x1, x2, eps2, A, lane);
-        shift_list(L.acc_list, n_acc, lane);
+        eval_cells<MIXED>(stage, acc_list, kGS, mom, x0, x1, x2, a.eps2, A, lane);
+        shift_list(acc_list, n_acc, lane);
         n_acc -= kGS;
+        tot_acc += kGS;
       }
       if (n_leaf >= kGS) {
-        eval_leaves<MIXED>(L, kGS, cells, pos_s, mass_s, i, x0, x1, x2, eps2, A, lane);
-        shift_list(L.leaf_list, n_leaf, lane);
+        eval_leaves<MIXED>(stage, leaf_list, kGS, cells, part, i, x0, x1, x2, a.eps2, A, lane, 0, 1);
+        shift_list(leaf_list, n_leaf, lane);
         n_leaf -= kGS;
+        tot_leaf += kGS;
       }
     }
-    __syncthreads();
-    if (!overflow) {
-      if (n_acc > 0) eval_cells<MIXED>(L, n_acc, cells, x0, x1, x2, eps2, A, lane);
-      if (n_leaf > 0) eval_leaves<MIXED>(L, n_leaf, cells, pos_s, mass_s, i, x0, x1, x2, eps2, A, lane);
+    if (fits) {
+      if (n_acc > 0) eval_cells<MIXED>(stage, acc_list, n_acc, mom, x0, x1, x2, a.eps2, A, lane);
+      if (n_leaf > 0) eval_leaves<MIXED>(stage, leaf_list, n_leaf, cells, part, i, x0, x1, x2, a.eps2, A, lane, 0, 1);
+      tot_acc += n_acc;
+      tot_leaf += n_leaf;
       if (valid) {
-        const int32_t o = idx_s[i];
-        acc[3 * o] = A.a0;
-        acc[3 * o + 1] = A.a1;
-        acc[3 * o + 2] = A.a2;
-        pot[o] = A.ph;
+        const int64_t o = a.idx[i];
+        a.acc[3 * o] = A.a0;
+        a.acc[3 * o + 1] = A.a1;
+        a.acc[3 * o + 2] = A.a2;
+        a.pot[o] = A.ph;
       }
     }
-    if (lane == 0) {
-      atomicAdd(&counters[1], tot_acc);
-      atomicAdd(&counters[2], tot_leaf);
-      if (overflow) {
-        atomicOr(&counters[3], 1ull);
-        if (err) atomicOr(err, kErrTreeStack);
-      }
-    }
-    __syncthreads();
+    overflow |= !fits;
+    wave_sync();
+    w = queue_next(a.wq, slot, ngroups, w + gridDim.x);
   }
+  if (lane == 0 && (a.ctr || overflow)) walk_count(a, tot_acc, tot_leaf, overflow);
+  queue_done(a.wq, ngroups);
+}
+
+// Few groups (they leave most of the chip idle at one wavefront each): a team
+// of kTeam wavefronts per group.  Wavefront 0 walks, with its stack in LDS,
+// and fills one of two pairs of lists; the others meanwhile evaluate the pair
+// of the round before, the list's chunks dealt to them in turn, each in the
+// composition a single wavefront would give it; when the walk has ended all
+// evaluate the last pair.  The partial sums are added in wavefront order.
+// Up to kTeamChunks chunks of 64 per compute unit (131072 particles on 256):
+// whole evaluations in us, one wavefront per group and teams, double / mixed:
+// 10007: 648 / 615 and 377 / 315; 65536: 998 / 871 and 803 / 634; 131072: 1431 /
+// 1079 and 1294 / 1059; 262144: 2378 / 1685 and 2402 / 1926.
+constexpr int kTeamChunks = 8;
+constexpr int kTeam = 8;
+constexpr int kTeamStack = 2048;                  // stack entries in LDS
+constexpr int kTeamCells = 8 * kGS, kTeamLeaves = 2 * kGS;  // list lengths that end a round
+
+template <bool MIXED>
+__global__ __launch_bounds__(kTeam * kGS) void k_tree_walk_team(WalkArgs a) {
+  __shared__ int32_t near_[kTeamStack];
+  __shared__ int32_t acc_list[2][kTeamCells + kGS], leaf_list[2][kTeamLeaves + kGS];
+  __shared__ int count[2][2];  // entries to evaluate of each list pair
+  __shared__ int done_s[2];
+  __shared__ Stage<MIXED> stage[kTeam];
+  __shared__ unsigned int slot;
+  // the sums of each wavefront, at the end, in the staging space
+  static_assert(sizeof(stage) >= kTeam * 4 * kGS * sizeof(double), "partial sums");
+  double (*red)[4][kGS] = reinterpret_cast<double (*)[4][kGS]>(&stage);
+  using Mom = typename Terms<MIXED>::Mom;
+  const TreeCell* __restrict__ cells = a.cells;
+  const Mom* __restrict__ mom = static_cast<const Mom*>(a.mom);
+  const Part* __restrict__ part = a.part;
+  const int lane = threadIdx.x & (kGS - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kGS);
+  const int64_t ngroups = *a.ngroups;
+  const Stack<kTeamStack> stack{near_, a.stack + (int64_t)blockIdx.x * a.stack_cap};
+  const int32_t root_child0 = cells[0].child0, root_nchild = cells[0].child1 - root_child0;
+  unsigned long long tot_acc = 0, tot_leaf = 0;
+  bool overflow = false;
+  if (!queue_member(ngroups)) return;
+  if (threadIdx.x < 2) done_s[threadIdx.x] = 0;
+  __syncthreads();
+  int64_t w = queue_first(a.wq, ngroups);
+  while (w < ngroups) {
+    const int64_t g = interleaved(w, ngroups);
+    const int32_t b = a.gb[g], e = a.ge[g];
+    const int32_t i = b + lane;
+    const bool valid = i < e;
+    const int32_t ir = valid ? i : b;
+    const double x0 = part[ir].x[0], x1 = part[ir].x[1], x2 = part[ir].x[2];
+    double box[6];
+    for (int k = 0; k < 6; ++k) box[k] = a.gbox[6 * g + k];
+    Accum A{0.0, 0.0, 0.0, 0.0};
+    // the walk's state, kept by wavefront 0: entries carried over from the
+    // previous round (its last, partial chunks) come first in the new lists
+    int sp = 0, n_acc = 0, n_leaf = 0;
+    bool fits = true;
+    if (wave == 0) {
+      if (root_nchild > 0) {
+        if (lane < root_nchild) stack.put(lane, root_child0 + lane);
+        sp = root_nchild;
+      } else {
+        if (lane == 0) leaf_list[0][0] = 0;
+        n_leaf = 1;
+      }
+      wave_sync();
+    }
+    bool done = false;
+    for (int r = 0;; ++r) {
+      const int cur = r & 1, prev = cur ^ 1;
+      if (!done && wave == 0) {
+        int32_t* al = acc_list[cur];
+        int32_t* ll = leaf_list[cur];
+        while (sp > 0 && n_acc < kTeamCells && n_leaf < kTeamLeaves) {
+          fits = walk_step<kTeamStack>(stack, sp, a.stack_cap, al, n_acc, ll, n_leaf, cells, box, a.theta, lane);
+          if (!fits) break;
+        }
+        const bool end = sp == 0 || !fits;
+        const int ea = end ? n_acc : n_acc & ~(kGS - 1), el = end ? n_leaf : n_leaf & ~(kGS - 1);
+        if (lane == 0) {
+          count[cur][0] = ea;
+          count[cur][1] = el;
+          done_s[cur] = end ? (fits ? 1 : 2) : 0;
+        }
+        tot_acc += ea;
+        tot_leaf += el;
+        // the rest goes to the other lists once the team has read them
+        n_acc -= ea;
+        n_leaf -= el;
+      } else if (r > 0) {
+        const int first = done ? wave : wave - 1, step = done ? kTeam : kTeam - 1;
+        const int ea = count[prev][0], el = count[prev][1];
+        for (int u = first; u * kGS < ea; u += step)
+          eval_cells<MIXED>(stage[wave], acc_list[prev] + u * kGS, ea - u * kGS < kGS ? ea - u * kGS : kGS, mom, x0, x1, x2,
+                            a.eps2, A, lane);
+        for (int u = 0; u * kGS < el; ++u)
+          eval_leaves<MIXED>(stage[wave], leaf_list[prev] + u * kGS, el - u * kGS < kGS ? el - u * kGS : kGS, cells, part, i, x0,
+                             x1, x2, a.eps2, A, lane, first, step);
+      }
+      __syncthreads();
+      if (done) break;
+      const int end = done_s[cur];
+      done = end != 0;
+      if (end == 2) break;  // the stack overflowed: the group is not written
+      if (!done && wave == 0) {
+        // the team is done with the other lists; entries carry over to them
+        const int ea = count[cur][0], el = count[cur][1];
+        if (lane < n_acc) acc_list[prev][lane] = acc_list[cur][ea + lane];
+        if (lane < n_leaf) leaf_list[prev][lane] = leaf_list[cur][el + lane];
+        wave_sync();
+      }
+    }
+    const bool group_fits = done_s[0] != 2 && done_s[1] != 2;
+    __syncthreads();  // every wavefront has finished with the staging space
+    red[wave][0][lane] = A.a0;
+    red[wave][1][lane] = A.a1;
+    red[wave][2][lane] = A.a2;
+    red[wave][3][lane] = A.ph;
+    __syncthreads();
+    if (wave < 4 && valid && group_fits) {
+      double v = red[0][wave][lane];
+      for (int u = 1; u < kTeam; ++u) v += red[u][wave][lane];
+      const int64_t o = a.idx[i];
+      if (wave < 3) a.acc[3 * o + wave] = v;
+      else a.pot[o] = v;
+    }
+    overflow |= !group_fits;
+    if (threadIdx.x < 2) done_s[threadIdx.x] = 0;
+    __syncthreads();
+    w = queue_next(a.wq, slot, ngroups, w + gridDim.x);
+  }
+  if (threadIdx.x == 0 && (a.ctr || overflow)) walk_count(a, tot_acc, tot_leaf, overflow);
+  queue_done(a.wq, ngroups);
 }
 
 // ----------------------------------------------------------- radix sort -----
@@ -1173,7 +1394,7 @@ struct Alloc {
 };
 
 enum Slot {
-  S_BOXPART, S_BOX, S_KEYS, S_KEYS2, S_IDX, S_IDX2, S_POS, S_MASS, S_SPAN, S_CELLS, S_CNT,
+  S_BOXPART, S_BOX, S_KEYS, S_KEYS2, S_IDX, S_IDX2, S_PART, S_MOM, S_SPAN, S_CELLS, S_CNT,
   S_GB, S_GE, S_GN, S_GBOX, S_STACK, S_CTR, S_LVL, S_HIST, S_TILE
 };
 
@@ -1263,7 +1484,8 @@ hipError_t tree_sorted_keys(TreeScratch& s, hipStream_t st, const double* pos, i
 
 hipError_t tree_forces_run(TreeScratch& s, hipStream_t st, const double* pos, const double* mass, int32_t n,
                            double eps2, double theta, int n_crit, double g_frac, bool mixed, double* acc,
-                           double* pot, TreeStats* stats, bool capturing, unsigned int* err, const char** msg) {
+                           double* pot, TreeStats* stats, bool capturing, unsigned int* wq, unsigned int* err,
+                           const char** msg) {
   *msg = "";
   if (!capturing && !s.host) NB_TRY(hipHostMalloc(&s.host, 64 * sizeof(int64_t), hipHostMallocDefault));
   Alloc al{s, st, capturing};
@@ -1277,8 +1499,7 @@ hipError_t tree_forces_run(TreeScratch& s, hipStream_t st, const double* pos, co
     hipError_t e = keys_and_order(al, pos, n, &box, &keys_s, &idx_s, msg);
     if (e != hipSuccess) return e;
   }
-  double* pos_s = al.get<double>(S_POS, 3 * (int64_t)n);
-  double* mass_s = al.get<double>(S_MASS, n);
+  Part* part = al.get<Part>(S_PART, n);
   // cells, sized by a bound: a cell that splits holds more than n_crit
   // particles and the cells of one level are disjoint, so each level has at
   // most n / (n_crit + 1) of them; the leaves hold at least one particle each,
@@ -1286,6 +1507,8 @@ hipError_t tree_forces_run(TreeScratch& s, hipStream_t st, const double* pos, co
   const int64_t inner = n / ((int64_t)n_crit + 1);
   const int64_t cap_cells = 1 + (int64_t)kLevels * inner + n;
   TreeCell* cells = al.get<TreeCell>(S_CELLS, cap_cells);
+  CellMom* mom = al.get<CellMom>(S_MOM, cap_cells);  // or CellMomF, which is smaller
+  CellMomF* momf = mixed ? reinterpret_cast<CellMomF*>(mom) : nullptr;
   uint16_t* span = al.get<uint16_t>(S_SPAN, n);
   const int32_t ntile = (n + kTB - 1) / kTB;
   int32_t* cnt = al.get<int32_t>(S_CNT, (int64_t)kRows * ntile + kRows);
@@ -1296,44 +1519,51 @@ hipError_t tree_forces_run(TreeScratch& s, hipStream_t st, const double* pos, co
   int32_t* ge = al.get<int32_t>(S_GE, n);
   int32_t* gn = al.get<int32_t>(S_GN, 1);
   double* gbox = al.get<double>(S_GBOX, 6 * (int64_t)n);
-  unsigned long long* ctr = al.get<unsigned long long>(S_CTR, 4);
+  unsigned long long* ctr = al.get<unsigned long long>(S_CTR, kCtrWords);
   NB_TRY(need(ctr));
   int32_t* total = cnt + (int64_t)kRows * ntile;
   hipLaunchKernelGGL(k_cell_starts, dim3(ntile), dim3(kTB), 0, st, keys_s, idx_s, pos, mass, n, n_crit, box, g_frac,
-                     pos_s, mass_s, span, cnt, ntile, tiles);
+                     part, span, cnt, ntile, tiles);
   hipLaunchKernelGGL(k_level_scan, dim3(kRows), dim3(1024), 0, st, cnt, ntile, total, ctr);
-  hipLaunchKernelGGL(k_write_cells, dim3(ntile), dim3(kTB), 0, st, cells, span, cnt, total, ntile, n, pos_s,
+  hipLaunchKernelGGL(k_write_cells, dim3(ntile), dim3(kTB), 0, st, cells, span, cnt, total, ntile, n, part,
                      box, g_frac, lvl, gb, ge, gbox, gn);
-  hipLaunchKernelGGL(k_cell_moments, dim3((unsigned)std::min<int64_t>(1024, cap_cells)), dim3(kTB), 0, st, cells, lvl,
-                     pos_s, mass_s, tiles);
+  hipLaunchKernelGGL(k_cell_moments, dim3((unsigned)std::min<int64_t>(1024, cap_cells)), dim3(kTB), 0, st, cells, mom,
+                     momf, lvl, part, tiles);
   NB_TRY(hipGetLastError());
 
-  // walk and forces: one wavefront per group, groups handed out by a counter
+  // walk and forces: a team per group while the groups are few, else one
+  // wavefront per group
   int dev = 0, num_cus = 0, per_cu = 0;
   NB_TRY(hipGetDevice(&dev));
   NB_TRY(hipDeviceGetAttribute(&num_cus, hipDeviceAttributeMultiprocessorCount, dev));
-  if (mixed)
-    NB_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_tree_walk_forces<true>, kGS, 0));
-  else
-    NB_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_tree_walk_forces<false>, kGS, 0));
-  int64_t grid = (int64_t)(num_cus > 0 ? num_cus : 1) * (per_cu > 0 ? per_cu : 1);
-  // the counter hands out every group whatever the grid; a chunk of 64 rarely
-  // splits into more than two groups, so more workgroups would mostly find none
+  if (num_cus < 1) num_cus = 1;
+  const bool team = nchunk <= kTeamChunks * num_cus;
+  using WalkFn = void (*)(WalkArgs);
+  const WalkFn fn = team ? (mixed ? k_tree_walk_team<true> : k_tree_walk_team<false>)
+                         : (mixed ? k_tree_walk_forces<true> : k_tree_walk_forces<false>);
+  const int wg = team ? kTeam * kGS : kGS;
+  NB_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(fn), wg, 0));
+  int64_t grid = (int64_t)num_cus * (per_cu > 0 ? per_cu : 1);
+  // a chunk of 64 rarely splits into more than two groups, so more workgroups
+  // would mostly find none
   if (grid > 2 * (int64_t)nchunk) grid = 2 * (int64_t)nchunk;
   const int32_t cap = (int32_t)(cap_cells < kStackCap ? cap_cells : kStackCap);
   int32_t* stack = al.get<int32_t>(S_STACK, grid * cap);
   NB_TRY(need(stack));
-  if (mixed)
-    hipLaunchKernelGGL(k_tree_walk_forces<true>, dim3((unsigned)grid), dim3(kGS), 0, st, gb, ge, gn, gbox,
-                       cells, theta, pos_s, mass_s, eps2, idx_s, stack, cap, ctr, err, acc, pot);
-  else
-    hipLaunchKernelGGL(k_tree_walk_forces<false>, dim3((unsigned)grid), dim3(kGS), 0, st, gb, ge, gn, gbox,
-                       cells, theta, pos_s, mass_s, eps2, idx_s, stack, cap, ctr, err, acc, pot);
+  const WalkArgs wa{gb, ge, gn, gbox, cells, mom, part, idx_s, theta, eps2, stack, cap, wq, stats ? ctr : nullptr,
+                    err, acc, pot};
+  hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(wg), 0, st, wa);
   NB_TRY(hipGetLastError());
   if (!stats) return hipSuccess;
   // counts for the caller (synchronises)
-  unsigned long long c[3];
-  NB_TRY(read_entries(s, st, ctr + 1, 3, c));
+  unsigned long long c[3] = {0, 0, 0};
+  for (int x = 0; x < kXcd; ++x) {
+    unsigned long long cx[3];
+    NB_TRY(read_entries(s, st, ctr + x * kCtrLine, 3, cx));
+    c[0] += cx[0];
+    c[1] += cx[1];
+    c[2] |= cx[2];
+  }
   if (c[2]) {
     *msg = "tree walk stack exceeded its bound";
     return hipErrorInvalidValue;

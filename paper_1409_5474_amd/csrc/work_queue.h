@@ -57,6 +57,15 @@ __device__ __forceinline__ int64_t queue_first(const unsigned int* wq, int64_t i
   return range_lo(items, blockIdx.x % kXcd) + blockIdx.x / kXcd;
 }
 
+// The k-th entry of range x as entry 8 k + x of a list: an order in which the
+// ranges interleave, for items whose cost varies slowly along the list (the
+// XCDs then share the expensive stretches).
+__device__ __forceinline__ int64_t interleaved(int64_t w, int64_t items) {
+  const int64_t q = items / kXcd, cut = (items % kXcd) * (q + 1);
+  const int64_t x = w < cut ? w / (q + 1) : (q > 0 ? items % kXcd + (w - cut) / q : 0);
+  return (w - range_lo(items, (int)x)) * kXcd + x;
+}
+
 // Thread 0 turns an own-range take into an item: `own` is the counter value
 // the take returned.  When that range is exhausted it reads every range's
 // counter at once (independent loads, one round of latency: device-scope

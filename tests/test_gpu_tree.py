@@ -109,6 +109,30 @@ def test_theta_zero_is_the_direct_sum(ctx):
     _close((acc, pot), (a_ref.cpu().numpy(), p_ref.cpu().numpy()), 1e-13, p.pos, p.mass, eps2)
 
 
+@pytest.mark.parametrize("n", [131072, 131073, 140001])
+def test_both_walks_at_their_boundary(ctx, n):
+    # teams of wavefronts per group up to 131072 particles on 256 compute
+    # units, one wavefront per group above: theta = 0 is the direct sum, and at
+    # theta = 0.5 both kernels meet the same approximation error
+    import torch
+    import paper_1409_5474_amd as nb
+    p = synth.plummer(n, 31)
+    eps2 = 2.0 ** -16
+    x, m = T(p.pos), T(p.mass)
+    a_ref, _, p_ref = ctx.forces(x, T(p.vel), m, T(np.arange(n, dtype=np.int32)), eps2)
+    a0, f0, _ = ctx.tree_forces(x, m, eps2, 0.0)
+    assert torch.linalg.norm(a0 - a_ref) <= 1e-13 * torch.linalg.norm(a_ref)
+    assert torch.linalg.norm(f0 - p_ref) <= 1e-13 * torch.linalg.norm(p_ref)
+    a1, f1, _ = ctx.tree_forces(x, m, eps2, 0.5)
+    rel = torch.linalg.norm(a1 - a_ref, dim=1) / torch.linalg.norm(a_ref, dim=1)
+    assert float(torch.sqrt((rel ** 2).mean())) <= 1e-3
+    mixed = nb.Context(0, "mixed")
+    a2, f2, _ = mixed.tree_forces(x, m, eps2, 0.5)
+    assert torch.linalg.norm(a2 - a1) <= 1e-6 * torch.linalg.norm(a1)
+    assert torch.linalg.norm(f2 - f1) <= 1e-6 * torch.linalg.norm(f1)
+    mixed.close()
+
+
 def test_one_particle_and_a_small_set(ctx):
     acc, pot, st = _gpu(ctx, np.array([[0.3, -0.2, 0.1]]), np.array([1.0]), 1e-3, 0.5)
     assert np.all(acc == 0) and np.all(pot == 0)
