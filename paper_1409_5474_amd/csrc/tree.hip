@@ -88,9 +88,38 @@ struct CellMomF {
 };
 
 // ---------------------------------------------------------------- box -----
+// Minimum and maximum of three components over the kTB threads of a block
+// (red is free again after the next barrier).
+__device__ __forceinline__ void block_minmax(double* mn, double* mx, double (*red)[6]) {
+  constexpr int W = kTB / 64;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      mn[c] = fmin(mn[c], __shfl_xor(mn[c], o, 64));
+      mx[c] = fmax(mx[c], __shfl_xor(mx[c], o, 64));
+    }
+    if ((threadIdx.x & 63) == 0) {
+      red[threadIdx.x >> 6][c] = mn[c];
+      red[threadIdx.x >> 6][3 + c] = mx[c];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    mn[c] = red[0][c];
+    mx[c] = red[0][3 + c];
+#pragma unroll
+    for (int w = 1; w < W; ++w) {
+      mn[c] = fmin(mn[c], red[w][c]);
+      mx[c] = fmax(mx[c], red[w][3 + c]);
+    }
+  }
+}
+
 __global__ __launch_bounds__(kTB) void k_bbox_partial(const double* __restrict__ pos, int64_t n,
                                                       double* __restrict__ part) {
-  __shared__ double red[6][kTB];
+  __shared__ double red[kTB / 64][6];
   double mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
   for (int64_t i = (int64_t)blockIdx.x * kTB + threadIdx.x; i < n; i += (int64_t)gridDim.x * kTB)
     for (int c = 0; c < 3; ++c) {
@@ -98,47 +127,27 @@ __global__ __launch_bounds__(kTB) void k_bbox_partial(const double* __restrict__
       mn[c] = fmin(mn[c], x);
       mx[c] = fmax(mx[c], x);
     }
-  for (int c = 0; c < 3; ++c) {
-    red[c][threadIdx.x] = mn[c];
-    red[3 + c][threadIdx.x] = mx[c];
-  }
-  __syncthreads();
-  for (int o = kTB / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o)
-      for (int c = 0; c < 3; ++c) {
-        red[c][threadIdx.x] = fmin(red[c][threadIdx.x], red[c][threadIdx.x + o]);
-        red[3 + c][threadIdx.x] = fmax(red[3 + c][threadIdx.x], red[3 + c][threadIdx.x + o]);
-      }
-    __syncthreads();
-  }
-  if (threadIdx.x < 6) part[6 * blockIdx.x + threadIdx.x] = red[threadIdx.x][0];
+  block_minmax(mn, mx, red);
+  if (threadIdx.x == 0)
+    for (int c = 0; c < 3; ++c) {
+      part[6 * (int64_t)blockIdx.x + c] = mn[c];
+      part[6 * (int64_t)blockIdx.x + 3 + c] = mx[c];
+    }
 }
 
-__global__ __launch_bounds__(kTB) void k_bbox_final(const double* __restrict__ part, int nblk,
-                                                    Box* __restrict__ box) {
-  __shared__ double red[6][kTB];
+// The box from the partial minima and maxima, by every thread of a block
+// alike (each block of the key pass does it for itself: a launch of its own
+// costs more).
+__device__ __forceinline__ Box box_of(const double* __restrict__ part, int nblk, double (*red)[6]) {
   double mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
   for (int b = threadIdx.x; b < nblk; b += kTB)
     for (int c = 0; c < 3; ++c) {
       mn[c] = fmin(mn[c], part[6 * b + c]);
       mx[c] = fmax(mx[c], part[6 * b + 3 + c]);
     }
-  for (int c = 0; c < 3; ++c) {
-    red[c][threadIdx.x] = mn[c];
-    red[3 + c][threadIdx.x] = mx[c];
-  }
-  __syncthreads();
-  for (int o = kTB / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o)
-      for (int c = 0; c < 3; ++c) {
-        red[c][threadIdx.x] = fmin(red[c][threadIdx.x], red[c][threadIdx.x + o]);
-        red[3 + c][threadIdx.x] = fmax(red[3 + c][threadIdx.x], red[3 + c][threadIdx.x + o]);
-      }
-    __syncthreads();
-  }
-  if (threadIdx.x != 0) return;
+  block_minmax(mn, mx, red);
   double ext = 0.0;
-  for (int c = 0; c < 3; ++c) ext = fmax(ext, red[3 + c][0] - red[c][0]);
+  for (int c = 0; c < 3; ++c) ext = fmax(ext, mx[c] - mn[c]);
   double side = 1.0;
   if (ext > 0.0) {
     int e = 0;
@@ -146,10 +155,10 @@ __global__ __launch_bounds__(kTB) void k_bbox_final(const double* __restrict__ p
     side = ldexp(1.0, e);
   }
   Box bx;
-  for (int c = 0; c < 3; ++c) bx.lo[c] = red[c][0];
+  for (int c = 0; c < 3; ++c) bx.lo[c] = mn[c];
   bx.side = side;
   bx.h = ldexp(side, -kBits);
-  *box = bx;
+  return bx;
 }
 
 // --------------------------------------------------------------- keys -----
@@ -193,14 +202,18 @@ __device__ __forceinline__ uint64_t hilbert63(uint32_t a0, uint32_t a1, uint32_t
   return key;
 }
 
-__global__ __launch_bounds__(kTB) void k_keys(const double* __restrict__ pos, int64_t n, const Box* __restrict__ box,
+// idx (may be null): the rows, for a sort that carries them along.
+__global__ __launch_bounds__(kTB) void k_keys(const double* __restrict__ pos, int64_t n,
+                                              const double* __restrict__ part, int nblk, Box* __restrict__ box,
                                               uint64_t* __restrict__ keys, int32_t* __restrict__ idx) {
-  const Box b = *box;
+  __shared__ double red[kTB / 64][6];
+  const Box b = box_of(part, nblk, red);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *box = b;
   for (int64_t i = (int64_t)blockIdx.x * kTB + threadIdx.x; i < n; i += (int64_t)gridDim.x * kTB) {
     int32_t q[3];
     grid_of(pos + 3 * i, b, q);
     keys[i] = hilbert63((uint32_t)q[0], (uint32_t)q[1], (uint32_t)q[2]);
-    idx[i] = (int32_t)i;
+    if (idx) idx[i] = (int32_t)i;
   }
 }
 
@@ -1228,61 +1241,139 @@ __global__ __launch_bounds__(kTeam * kGS) void k_tree_walk_team(WalkArgs a) {
   queue_done(a.wq, ngroups);
 }
 
+// ------------------------------------------------------------ rank sort -----
+// Few particles: a key's place is the number of keys before it (smaller, or
+// equal with a smaller row), counted directly.  A block counts for 64 keys, one
+// per lane; its sixteen wavefronts each compare a sixteenth of all keys, read at a
+// wave-uniform index through the scalar cache.  n^2 / 64 wavefront steps of a
+// compare and an add-with-carry, one launch: 10007 keys take @@ us, where
+// eight radix passes of two or three launches took @@.
+constexpr int kRankThreads = 1024;
+constexpr int32_t kRankMax = 16384;
+
+using ConstKey = const __attribute__((address_space(4))) uint64_t;  // not written while the kernel runs
+
+// Keys of [lo, hi) below ki, or not above it: sixteen keys are on their way
+// while the sixteen before them are compared.
+template <bool EQUAL>
+__device__ __forceinline__ int32_t count_below(ConstKey* k, int32_t lo, int32_t hi, uint64_t ki) {
+  constexpr int B = 16;
+  int32_t cnt = 0, j = lo;
+  if (hi - lo >= B) {
+    uint64_t nxt[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) nxt[u] = k[j + u];
+    for (; j + B <= hi; j += B) {
+      uint64_t cur[B];
+      const int32_t jn = j + 2 * B <= hi ? j + B : lo;
+#pragma unroll
+      for (int u = 0; u < B; ++u) cur[u] = nxt[u];
+#pragma unroll
+      for (int u = 0; u < B; ++u) nxt[u] = k[jn + u];
+#pragma unroll
+      for (int u = 0; u < B; ++u) cnt += (EQUAL ? cur[u] <= ki : cur[u] < ki) ? 1 : 0;
+    }
+  }
+  for (; j < hi; ++j) cnt += (EQUAL ? k[j] <= ki : k[j] < ki) ? 1 : 0;
+  return cnt;
+}
+
+__global__ __launch_bounds__(kRankThreads) void k_rank_sort(const uint64_t* __restrict__ keys, int32_t n,
+                                                            uint64_t* __restrict__ keys_s,
+                                                            int32_t* __restrict__ idx_s) {
+  constexpr int W = kRankThreads / 64;
+  __shared__ int32_t before[W][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int32_t i0 = (int32_t)blockIdx.x * 64, i = i0 + lane;
+  const uint64_t ki = i < n ? keys[i] : ~0ull;
+  ConstKey* k = (ConstKey*)(uintptr_t)keys;
+  const int32_t len = (n + W - 1) / W;
+  const int32_t lo = wave * len < n ? wave * len : n, hi = n - lo < len ? n : lo + len;
+  const int32_t a1 = hi < i0 ? hi : i0;                       // [lo, a1): rows before the block's
+  const int32_t b0 = lo > i0 ? lo : i0;                       // [b0, b1): the block's own rows
+  const int32_t b1 = hi < i0 + 64 ? hi : i0 + 64;
+  const int32_t c0 = lo > i0 + 64 ? lo : i0 + 64;             // [c0, hi): rows after them
+  int32_t cnt = count_below<true>(k, lo, a1, ki) + count_below<false>(k, c0, hi, ki);
+  for (int32_t j = b0; j < b1; ++j) cnt += (k[j] < ki || (k[j] == ki && j < i)) ? 1 : 0;
+  before[wave][lane] = cnt;
+  __syncthreads();
+  if (wave == 0 && i < n) {
+    int32_t r = 0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) r += before[w][lane];
+    keys_s[r] = ki;
+    idx_s[r] = i;
+  }
+}
+
 // ----------------------------------------------------------- radix sort -----
 // Stable least-significant-digit radix sort of (key, row) pairs, 8 bits per
-// pass.  A pass: each tile of kRsTile keys counts its digits (k_rs_hist);
-// the prefix of each digit's row of tile counts (k_rs_rowscan, one block
-// per digit) plus the prefix of the digit totals gives every (digit, tile)
-// its first output slot; each tile then writes its keys there
+// pass.  A pass: each tile of kRsTile keys counts its digits (k_rs_hist); the
+// counts of the tiles before it plus the prefix of the digit totals give every
+// (digit, tile) its first output slot; each tile then writes its keys there
 // (k_rs_scatter), a key's place among the equal digits of its tile being
-// the number of such keys before it.  Within a tile, wavefront w takes the
-// w-th quarter in rounds of 64 consecutive keys; the lanes of a round that
-// share a digit find each other with eight ballots (one per digit bit), and
-// a per-wavefront count of each digit carries over between rounds, so the
-// order among equal digits is the input order.
+// the number of such keys before it.  Up to kRsDirect tiles each scatter block
+// adds up the other tiles' counts itself (128 tiles: 128 KB from the L2);
+// above, a kernel of its own scans each digit's row (k_rs_rowscan, one block
+// per digit).  Within a tile, wavefront w takes the w-th eighth in rounds of 64
+// consecutive keys; the lanes of a round that share a digit find each other
+// with eight ballots (one per digit bit), and a per-wavefront count of each
+// digit carries over between rounds, so the order among equal digits is the
+// input order.
 constexpr int kRsBits = 8;
 constexpr int kRsBuckets = 1 << kRsBits;
-constexpr int kRsThreads = 256;
-constexpr int kRsRounds = 8;                                 // rounds of 64 keys per wavefront
-constexpr int kRsTile = (kRsThreads / 64) * 64 * kRsRounds;  // 2048 keys per tile
-static_assert(kRsBuckets == kRsThreads, "one thread per digit in the tile tables");
+constexpr int kRsThreads = 512;
+constexpr int kRsWaves = kRsThreads / 64;
+constexpr int kRsRounds = 4;                          // rounds of 64 keys per wavefront
+constexpr int kRsTile = kRsWaves * 64 * kRsRounds;    // 2048 keys per tile
+constexpr int32_t kRsDirect = 128;
+static_assert(2 * kRsBuckets == kRsThreads, "two threads per digit in the tile tables");
 
+// Counts of tile b: hist[b][digit] (direct) or hist[digit][b] (row scan).
 __global__ __launch_bounds__(kRsThreads) void k_rs_hist(const uint64_t* __restrict__ keys, int32_t n, int shift,
                                                         int32_t* __restrict__ hist, int32_t ntile) {
   __shared__ int32_t h[kRsBuckets];
-  h[threadIdx.x] = 0;
+  const int t = threadIdx.x;
+  if (t < kRsBuckets) h[t] = 0;
   __syncthreads();
   const int64_t base = (int64_t)blockIdx.x * kRsTile;
+#pragma unroll
   for (int r = 0; r < kRsTile / kRsThreads; ++r) {
-    const int64_t i = base + r * kRsThreads + threadIdx.x;
+    const int64_t i = base + r * kRsThreads + t;
     if (i < n) atomicAdd(&h[(keys[i] >> shift) & (kRsBuckets - 1)], 1);
   }
   __syncthreads();
-  hist[(int64_t)threadIdx.x * ntile + blockIdx.x] = h[threadIdx.x];
+  if (t < kRsBuckets) {
+    if (ntile <= kRsDirect) hist[(int64_t)blockIdx.x * kRsBuckets + t] = h[t];
+    else hist[(int64_t)t * ntile + blockIdx.x] = h[t];
+  }
 }
 
 // Per digit (block d): the exclusive prefix of its row of tile counts, in
 // place (the tile's place among the digit's keys), and the row total.
-__global__ __launch_bounds__(kRsThreads) void k_rs_rowscan(int32_t* __restrict__ hist, int32_t ntile,
-                                                           int32_t* __restrict__ total) {
-  __shared__ int32_t buf[kRsThreads];
-  const int t = threadIdx.x;
+constexpr int kRowThreads = 256;
+__global__ __launch_bounds__(kRowThreads) void k_rs_rowscan(int32_t* __restrict__ hist, int32_t ntile,
+                                                            int32_t* __restrict__ total) {
+  __shared__ int32_t wsum[2][kRowThreads / 64];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   int32_t* row = hist + (int64_t)blockIdx.x * ntile;
   int32_t carry = 0;
-  for (int64_t c0 = 0; c0 < ntile; c0 += kRsThreads) {
+  int buf = 0;
+  for (int64_t c0 = 0; c0 < ntile; c0 += kRowThreads) {
     const int64_t k = c0 + t;
     const int32_t v = k < ntile ? row[k] : 0;
-    buf[t] = v;
-    __syncthreads();
-    for (int o = 1; o < kRsThreads; o <<= 1) {
-      const int32_t u = t >= o ? buf[t - o] : 0;
-      __syncthreads();
-      buf[t] += u;
-      __syncthreads();
+    const int32_t x = wave_inclusive_sum(v, lane);
+    if (lane == 63) wsum[buf][wave] = x;
+    __syncthreads();  // the totals alternate between two buffers: one barrier per round
+    int32_t before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < kRowThreads / 64; ++w) {
+      before += w < wave ? wsum[buf][w] : 0;
+      all += wsum[buf][w];
     }
-    if (k < ntile) row[k] = carry + buf[t] - v;
-    carry += buf[kRsThreads - 1];
-    __syncthreads();
+    if (k < ntile) row[k] = carry + before + x - v;
+    carry += all;
+    buf ^= 1;
   }
   if (t == 0) total[blockIdx.x] = carry;
 }
@@ -1290,65 +1381,90 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_rowscan(int32_t* __restrict__
 __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint64_t* __restrict__ kin,
                                                            const int32_t* __restrict__ vin,
                                                            uint64_t* __restrict__ kout, int32_t* __restrict__ vout,
-                                                           int32_t n, int shift, const int32_t* __restrict__ offs,
+                                                           int32_t n, int shift, const int32_t* __restrict__ hist,
                                                            const int32_t* __restrict__ total, int32_t ntile) {
   __shared__ int32_t first[kRsBuckets];          // the tile's first output slot of each digit
-  __shared__ int32_t wcnt[kRsThreads / 64][kRsBuckets];
+  __shared__ int32_t wcnt[kRsWaves][kRsBuckets];
+  __shared__ int32_t half[2][kRsBuckets];        // direct: the second halves' sums
+  __shared__ int32_t wsum[kRsBuckets / 64];
   const int t = threadIdx.x, w = t >> 6, lane = t & 63;
-  // where each digit starts: the exclusive prefix of the digit totals
-  const int32_t tot = total[t];
-  first[t] = tot;
-  __syncthreads();
-  for (int o = 1; o < kRsBuckets; o <<= 1) {
-    const int32_t u = t >= o ? first[t - o] : 0;
-    __syncthreads();
-    first[t] += u;
-    __syncthreads();
-  }
-  const int32_t start = first[t] - tot;
-  __syncthreads();
-  first[t] = start + offs[(int64_t)t * ntile + blockIdx.x];
-  for (int q = 0; q < kRsThreads / 64; ++q) wcnt[q][t] = 0;
-  __syncthreads();
+  // the keys are on their way while the tables are summed
   const int64_t base = (int64_t)blockIdx.x * kRsTile + (int64_t)w * 64 * kRsRounds;
-  const uint64_t below = (1ull << lane) - 1ull;
   uint64_t key[kRsRounds];
   int32_t val[kRsRounds], rank[kRsRounds];
-  int dig[kRsRounds];
 #pragma unroll
   for (int r = 0; r < kRsRounds; ++r) {
     const int64_t i = base + r * 64 + lane;
-    const bool valid = i < n;
-    key[r] = valid ? kin[i] : 0ull;
-    val[r] = valid ? vin[i] : 0;
-    const int d = (int)((key[r] >> shift) & (kRsBuckets - 1));
-    dig[r] = d;
+    key[r] = i < n ? kin[i] : 0ull;
+    val[r] = i < n ? vin[i] : 0;
+  }
+  // keys of digit d in the tiles before this one (pre) and in all (tot)
+  const int d = t & (kRsBuckets - 1);
+  int32_t pre = 0, tot = 0;
+  if (ntile <= kRsDirect) {
+    const int h = t / kRsBuckets;
+#pragma unroll 16
+    for (int32_t q = h; q < ntile; q += 2) {
+      const int32_t c = hist[(int64_t)q * kRsBuckets + d];
+      tot += c;
+      pre += q < (int32_t)blockIdx.x ? c : 0;
+    }
+    if (h == 1) {
+      half[0][d] = pre;
+      half[1][d] = tot;
+    }
+  } else if (t < kRsBuckets) {
+    pre = hist[(int64_t)d * ntile + blockIdx.x];
+    tot = total[d];
+  }
+  for (int q = t; q < kRsWaves * kRsBuckets; q += kRsThreads) (&wcnt[0][0])[q] = 0;
+  __syncthreads();
+  if (ntile <= kRsDirect && t < kRsBuckets) {
+    pre += half[0][d];
+    tot += half[1][d];
+  }
+  // where each digit starts: the exclusive prefix of the digit totals
+  const int32_t x = wave_inclusive_sum(t < kRsBuckets ? tot : 0, lane);
+  if (t < kRsBuckets && lane == 63) wsum[w] = x;
+  __syncthreads();
+  if (t < kRsBuckets) {
+    int32_t at = x - tot;
+    for (int q = 0; q < w; ++q) at += wsum[q];
+    first[t] = at + pre;
+  }
+  const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+  for (int r = 0; r < kRsRounds; ++r) {
+    const bool valid = base + r * 64 + lane < n;
+    const int dig = (int)((key[r] >> shift) & (kRsBuckets - 1));
     uint64_t peers = __ballot(valid);
 #pragma unroll
     for (int b = 0; b < kRsBits; ++b) {
-      const bool bit = (d >> b) & 1;
+      const bool bit = (dig >> b) & 1;
       const uint64_t m = __ballot(bit);
       peers &= bit ? m : ~m;
     }
     const int before = __popcll(peers & below);
-    const int run = valid ? wcnt[w][d] : 0;
+    const int run = valid ? wcnt[w][dig] : 0;
     rank[r] = run + before;
-    if (valid && before == 0) wcnt[w][d] = run + __popcll(peers);  // the group's first lane
+    if (valid && before == 0) wcnt[w][dig] = run + __popcll(peers);  // the group's first lane
   }
   __syncthreads();
   // per digit, where each wavefront's keys start within the tile
-  int32_t acc = 0;
-  for (int q = 0; q < kRsThreads / 64; ++q) {
-    const int32_t c = wcnt[q][t];
-    wcnt[q][t] = acc;
-    acc += c;
+  if (t < kRsBuckets) {
+    int32_t acc = first[t];
+#pragma unroll
+    for (int q = 0; q < kRsWaves; ++q) {
+      const int32_t c = wcnt[q][t];
+      wcnt[q][t] = acc;
+      acc += c;
+    }
   }
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < kRsRounds; ++r) {
-    const int64_t i = base + r * 64 + lane;
-    if (i < n) {
-      const int32_t dst = first[dig[r]] + wcnt[w][dig[r]] + rank[r];
+    if (base + r * 64 + lane < n) {
+      const int32_t dst = wcnt[w][(key[r] >> shift) & (kRsBuckets - 1)] + rank[r];
       kout[dst] = key[r];
       vout[dst] = val[r];
     }
@@ -1410,7 +1526,8 @@ hipError_t radix_sort(Alloc& al, uint64_t* keys, int32_t* idx, uint64_t* keys2, 
   int32_t *va = idx, *vb = idx2;
   for (int shift = 0; shift < bits; shift += kRsBits) {
     hipLaunchKernelGGL(k_rs_hist, dim3(ntile), dim3(kRsThreads), 0, al.st, ka, n, shift, hist, ntile);
-    hipLaunchKernelGGL(k_rs_rowscan, dim3(kRsBuckets), dim3(kRsThreads), 0, al.st, hist, ntile, total);
+    if (ntile > kRsDirect)
+      hipLaunchKernelGGL(k_rs_rowscan, dim3(kRsBuckets), dim3(kRowThreads), 0, al.st, hist, ntile, total);
     hipLaunchKernelGGL(k_rs_scatter, dim3(ntile), dim3(kRsThreads), 0, al.st, ka, va, kb, vb, n, shift, hist, total,
                        ntile);
     std::swap(ka, kb);
@@ -1457,11 +1574,19 @@ hipError_t keys_and_order(Alloc& al, const double* pos, int32_t n, Box** box_out
   int32_t* idx = al.get<int32_t>(S_IDX, n);
   int32_t* idx2 = al.get<int32_t>(S_IDX2, n);
   NB_TRY(need(idx2));
+  const bool by_rank = n <= kRankMax;
   hipLaunchKernelGGL(k_bbox_partial, dim3(nbb), dim3(kTB), 0, al.st, pos, (int64_t)n, part);
-  hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(kTB), 0, al.st, part, nbb, box);
-  hipLaunchKernelGGL(k_keys, dim3(blocks_for(n)), dim3(kTB), 0, al.st, pos, (int64_t)n, box, keys, idx);
+  hipLaunchKernelGGL(k_keys, dim3(blocks_for(n)), dim3(kTB), 0, al.st, pos, (int64_t)n, part, nbb, box, keys,
+                     by_rank ? nullptr : idx);
   NB_TRY(hipGetLastError());
-  NB_TRY(radix_sort(al, keys, idx, keys2, idx2, n, 3 * kBits, keys_s, idx_s));
+  if (by_rank) {
+    hipLaunchKernelGGL(k_rank_sort, dim3((n + 63) / 64), dim3(kRankThreads), 0, al.st, keys, n, keys2, idx2);
+    NB_TRY(hipGetLastError());
+    *keys_s = keys2;
+    *idx_s = idx2;
+  } else {
+    NB_TRY(radix_sort(al, keys, idx, keys2, idx2, n, 3 * kBits, keys_s, idx_s));
+  }
   *box_out = box;
   return hipSuccess;
 }
