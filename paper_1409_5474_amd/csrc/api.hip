@@ -196,6 +196,19 @@ const Regime kDefaultRegimes[5] = {{0, 127, Launch{1, 64, 0, 0}},
                                    {8192, 65535, Launch{1, 1, 0, 0}},
                                    {65536, INT64_MAX, Launch{2, 1, 0, 0}}};
 
+// Whether a tuned table entry of this precision applies to N.
+bool tuned_for(const nb_ctx* c, int64_t n) {
+  for (const nb::TuneEntry& e : c->table)
+    if (e.prec == c->prec && n >= e.n_min) return true;
+  return false;
+}
+
+// The small-system kernel (k_forces_small) for every count of such a system,
+// host and device alike.
+bool takes_small(const nb_ctx* c, int64_t n, int64_t n_act) {
+  return !c->have_forced && !c->split_atomic && nb::small_direct(n, n_act) && !tuned_for(c, n);
+}
+
 // The active-count regimes of this context and precision: the tuned table
 // entries that apply to N (later entries override earlier ones on their
 // range), else the built-in breakpoints.  Regimes tile [0, inf).  A system
@@ -206,10 +219,7 @@ const Regime kDefaultRegimes[5] = {{0, 127, Launch{1, 64, 0, 0}},
 // N = 3899 and 16384); host-count launches use the same rule, so both paths
 // split the work identically.
 std::vector<Regime> regimes(const nb_ctx* c, int64_t n) {
-  bool tuned = false;
-  for (const nb::TuneEntry& e : c->table)
-    if (e.prec == c->prec && n >= e.n_min) tuned = true;
-  if (!tuned && n <= kSmallSystem) return {Regime{0, INT64_MAX, Launch{1, 16, 0, 0}}};
+  if (!tuned_for(c, n) && n <= kSmallSystem) return {Regime{0, INT64_MAX, Launch{1, 16, 0, 0}}};
   std::vector<Regime> r(std::begin(kDefaultRegimes), std::end(kDefaultRegimes));
   for (const nb::TuneEntry& e : c->table) {
     if (e.prec != c->prec || n < e.n_min) continue;
@@ -233,6 +243,11 @@ std::vector<Regime> regimes(const nb_ctx* c, int64_t n) {
 // saturation rule unless a forced configuration fixes it.
 Launch choose(const nb_ctx* c, int64_t n, int64_t n_act) {
   Launch cfg;
+  if (takes_small(c, n, n_act)) {
+    cfg = Launch{1, 16, 1, 0};
+    cfg.small = true;
+    return cfg;
+  }
   if (c->have_forced) {
     cfg = c->forced;
   } else {
@@ -265,6 +280,7 @@ Launch choose_batch(const nb_ctx* c, int kind, int64_t key, int64_t n_total, int
   for (auto it = c->batch_table.rbegin(); it != c->batch_table.rend(); ++it)
     if (it->prec == c->prec && it->kind == kind && key >= it->key_min && key <= it->key_max) return it->cfg;
   Launch cfg = choose(c, n_total, mean_size);
+  cfg.small = false;
   cfg.K = 1;
   if (cfg.L != 1 && cfg.L != 4 && cfg.L != 16 && cfg.L != 64)
     cfg.L = cfg.L >= 64 ? 64 : cfg.L >= 16 ? 16 : cfg.L >= 4 ? 4 : 1;
@@ -336,6 +352,10 @@ int run_forces(nb_ctx* c, const Launch& cfg, const double* pos, const double* ve
   a.acc = acc; a.jerk = jerk; a.pot = pot; a.part = nullptr; a.s_dev = nullptr; a.wq = c->wq;
   a.row_lo = 0; a.row_hi = n_rows >= 0 ? n_rows : N; a.err = c->wq + nb::kErrorWord;
   const bool mask = kernel_mask(c->prec, eps2);
+  if (cfg.small) {
+    hipError_t e = nb::launch_forces_small(c->prec, mask, a, nullptr, c->stream);
+    return e == hipSuccess ? NB_OK : hip_fail(c, e, "small force launch");
+  }
   const Launch eff = mask ? nb::masked(cfg) : cfg;
   const int max_grid = resident_grid(c, eff, mask);
   if (eff.L <= 0) {
@@ -720,15 +740,26 @@ namespace {
 
 // The device-count force launches; with `reduce` also the shared reduce,
 // otherwise its arguments go to *red for a caller that fuses it with the
-// next pass (the block step).
+// next pass (the block step).  A small system's one launch also corrects when
+// `step` is set; red->n stays 0 then.
 int devcount_forces(nb_ctx* c, const double* pos, const double* vel, const double* mass, int64_t N,
                     const int32_t* active, const int32_t* n_active_dev, int64_t max_active, double eps2,
-                    double* acc, double* jerk, double* pot, bool reduce, nb::ForceArgs* red_out) {
+                    double* acc, double* jerk, double* pot, bool reduce, nb::ForceArgs* red_out,
+                    const nb::StepArgs* step) {
   int rc = check_forces_args(c, pos, vel, mass, N, active, max_active, eps2, acc, jerk, pot);
   if (rc) return rc;
   if (!n_active_dev) return fail(c, NB_EINVAL, "n_active_dev is null%s");
   if (max_active == 0) return NB_OK;
   const bool mask = kernel_mask(c->prec, eps2);
+  if (takes_small(c, N, max_active)) {
+    nb::ForceArgs a{};
+    a.pos = pos; a.vel = vel; a.mass = mass; a.n = N;
+    a.active = active; a.n_active = max_active; a.n_active_dev = n_active_dev;
+    a.eps2 = eps2; a.S = 1; a.acc = acc; a.jerk = jerk; a.pot = pot;
+    a.row_lo = 0; a.row_hi = N; a.err = c->wq + nb::kErrorWord;
+    hipError_t e = nb::launch_forces_small(c->prec, mask, a, step, c->stream);
+    return e == hipSuccess ? NB_OK : hip_fail(c, e, "small force launch (device count)");
+  }
   // One fixed launch per group of regimes; the count decides on the device
   // which one works.  Every launch, empty or not, costs a few microseconds
   // in each block step, so adjacent regimes share a launch: those of one
@@ -895,7 +926,7 @@ int nbody_forces_devcount(nb_ctx* c, const double* pos, const double* vel, const
                           const int32_t* active, const int32_t* n_active_dev, int64_t max_active, double eps2,
                           double* acc, double* jerk, double* pot) {
   return devcount_forces(c, pos, vel, mass, N, active, n_active_dev, max_active, eps2, acc, jerk, pot, true,
-                         nullptr);
+                         nullptr, nullptr);
 }
 
 int hermite_predict(nb_ctx* c, const double* pos, const double* vel, const double* acc, const double* jerk,
@@ -1159,16 +1190,18 @@ int nb_block_step(nb_ctx* c, int64_t N, double eps2, double eta, double dt_max, 
                                      c->nact32, t_stop_tick, c->stop_dev, c->stream, &pred);
   if (e != hipSuccess) return hip_fail(c, e, "schedule launch");
   phase_mark(c, 1);
-  nb::ForceArgs red{};
-  rc = devcount_forces(c, pos_p, vel_p, mass, N, active, c->nact32, N, eps2, acc1, jerk1, pot1, false, &red);
-  if (rc) return rc;
-  phase_mark(c, 2);
-  // the partial sums' reduce and the corrector in one pass
   const nb::StepArgs st{pos_p, vel_p, pos, vel, acc, jerk, t_tick, dt_level, eta, dt_max, max_level,
                         reinterpret_cast<unsigned long long*>(sched + 3),
                         reinterpret_cast<unsigned long long*>(sched + 2)};
-  e = nb::launch_reduce_correct(c->prec, red, st, c->stream);
-  if (e != hipSuccess) return hip_fail(c, e, "reduce and correct launch");
+  nb::ForceArgs red{};
+  rc = devcount_forces(c, pos_p, vel_p, mass, N, active, c->nact32, N, eps2, acc1, jerk1, pot1, false, &red, &st);
+  if (rc) return rc;
+  phase_mark(c, 2);
+  if (red.n > 0) {
+    // the partial sums' reduce and the corrector in one pass
+    e = nb::launch_reduce_correct(c->prec, red, st, c->stream);
+    if (e != hipSuccess) return hip_fail(c, e, "reduce and correct launch");
+  }
   phase_mark(c, 3);
   return NB_OK;
 }

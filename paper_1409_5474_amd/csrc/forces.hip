@@ -845,6 +845,128 @@ __global__ __launch_bounds__(kReduceCorrectThreads) void k_reduce_correct(ForceA
   }
 }
 
+// ------------------------------------------------------- small systems -----
+// Systems of up to kSmallDirect particles: their force work is a few
+// microseconds, so what counts is launches and latency.  A workgroup takes
+// kSmallRows rows; 16 lanes share a row (lane `sub` takes j = sub, sub + 16,
+// ... of each 256-j tile: the pairs and the float runs of the LDS kernel's
+// L = 16 shape), and the W wavefronts take the tiles in turn, each staging its
+// own in LDS without a barrier.  The lanes are folded by a butterfly and the
+// wavefronts through LDS in their order, so the workgroup has its rows' whole
+// sums: no partial sums in memory, no second launch, and in a block step
+// (STEP) it corrects its particles itself.
+// Measured in replayed graphs, us per double evaluation, against the L = 16
+// shape with its j-split and reduce: 300 all active 4.8 (7.9), 1024: 5.7 (8.6),
+// 2048: 11.6 (20.8), 3899: 41 (58), 10 of 3899: 10.5 (8.2, but a block step
+// also saves the corrector's launch).  (Lanes reading their j straight from
+// the caller's arrays, 24 bytes apart, were bound by address processing: 3899
+// took 75 us.)
+// What one lane of a wavefront has written to LDS is read by others of the
+// same wavefront after this.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+}
+
+constexpr int kSmallL = 16;
+constexpr int kSmallRows = 64 / kSmallL;
+// Four wavefronts up to this many particles, eight above (2048 all active:
+// 11.6 us with four, 14.5 with eight; 10 of 3899: 11.8 and 10.5).
+constexpr int64_t kSmallNarrow = 2048;
+
+template <class P, bool MASK, int W, bool STEP>
+__global__ __launch_bounds__(64 * W) void k_forces_small(ForceArgs a, StepArgs s) {
+  __shared__ typename P::JTile tiles[W];
+  __shared__ double red[W][kSmallRows][7];
+  __shared__ double sum[kSmallRows][8];
+  int64_t n_act = a.n_active;
+  if (a.n_active_dev) {
+    const int64_t d = *a.n_active_dev;
+    n_act = d < n_act ? (d < 0 ? 0 : d) : n_act;
+  }
+  if (STEP && s.step_dev && n_act > 0 && blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(s.step_dev, 1ull);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int slot = lane / kSmallL, sub = lane % kSmallL;
+  const double* ipos = a.ipos ? a.ipos : a.pos;
+  const double* ivel = a.ivel ? a.ivel : a.vel;
+  const typename P::T e2 = in_vgpr(P::eps(a.eps2));
+  for (int64_t k0 = (int64_t)blockIdx.x * kSmallRows; k0 < n_act; k0 += (int64_t)gridDim.x * kSmallRows) {
+    const int64_t k = k0 + slot;
+    const int64_t row = k < n_act ? checked_row(a.active, k, a.row_lo, a.row_hi, a.err) : -1;
+    const typename P::IPart I = P::load_i(ipos, ivel, row >= 0 ? row : 0);
+    typename P::T A[1][7];
+    typename P::Tot Tt;
+    P::zero(Tt);
+#pragma unroll
+    for (int c = 0; c < 7; ++c) A[0][c] = 0;
+    for (int64_t base = (int64_t)wave * kTile; base < a.n; base += (int64_t)W * kTile) {
+      typename P::JReg r[kTile / 64];
+#pragma unroll
+      for (int u = 0; u < kTile / 64; ++u) {
+        const int64_t j = base + u * 64 + lane;
+        r[u] = P::load(a.pos, a.vel, a.mass, j, j < a.n);
+      }
+#pragma unroll
+      for (int u = 0; u < kTile / 64; ++u) P::store(tiles[wave], u * 64 + lane, r[u]);
+      wave_sync();
+#pragma unroll 4
+      for (int jj = sub; jj < kTile; jj += kSmallL) P::template pair_tile<MASK>(tiles[wave], jj, &I, e2, A, 1);
+      P::fold(Tt, A[0]);
+      wave_sync();
+    }
+    double v[7];
+#pragma unroll
+    for (int c = 0; c < 7; ++c) v[c] = P::value(Tt, c);
+#pragma unroll
+    for (int o = kSmallL / 2; o > 0; o >>= 1) {
+#pragma unroll
+      for (int c = 0; c < 7; ++c) v[c] += __shfl_xor(v[c], o, 64);
+    }
+    if (sub == 0) {
+#pragma unroll
+      for (int c = 0; c < 7; ++c) red[wave][slot][c] = v[c];
+    }
+    __syncthreads();
+    const int t = threadIdx.x;
+    if (t < kSmallRows * 8 && (t & 7) < 7) {
+      const int r = t >> 3, c = t & 7;
+      double x = red[0][r][c];
+#pragma unroll
+      for (int w = 1; w < W; ++w) x += red[w][r][c];
+      if constexpr (STEP) {
+        sum[r][c] = x;
+      } else if (k0 + r < n_act) {
+        const int64_t i = a.active[k0 + r];
+        if (row_in_range(i, a.row_lo, a.row_hi)) {
+          if (c < 3) a.acc[3 * (k0 + r) + c] = x;
+          else if (c < 6) a.jerk[3 * (k0 + r) + c - 3] = x;
+          else a.pot[k0 + r] = -(x - ((e2 > 0 && !a.no_self) ? P::self_term(a.mass[i], a.eps2) : 0.0));
+        }
+      }
+    }
+    if constexpr (STEP) {
+      __syncthreads();
+      if (t < kSmallRows && k0 + t < n_act) {
+        const int64_t i = a.active[k0 + t];
+        if (row_in_range(i, a.row_lo, a.row_hi)) {
+          double a1[3], j1[3];
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            a1[c] = sum[t][c];
+            j1[c] = sum[t][3 + c];
+            a.acc[3 * (k0 + t) + c] = a1[c];
+            a.jerk[3 * (k0 + t) + c] = j1[c];
+          }
+          a.pot[k0 + t] = -(sum[t][6] - (e2 > 0 ? P::self_term(a.mass[i], a.eps2) : 0.0));
+          correct_particle(i, a1, j1, s.pos_p, s.vel_p, s.pos, s.vel, s.acc, s.jerk, s.t_tick, s.level, s.eta,
+                           s.dt_max, s.max_level, s.clamp_dev);
+        }
+      }
+    }
+    __syncthreads();  // red and sum are free for the next rows
+  }
+}
+
 // ------------------------------------------------------- scalar j-path -----
 // Variant of the i-parallel layout (L = 1) without LDS: the j-records are
 // first converted once per call into the kernel's layout (a mirror array),
@@ -1762,6 +1884,29 @@ hipError_t launch_forces(int prec, const Launch& cfg_in, bool mask, const ForceA
   } else {
     hipLaunchKernelGGL(fn, dim3(grid), dim3(cfg.WG), 0, st, a);
   }
+  return hipGetLastError();
+}
+
+template <class P, bool MASK, int W>
+static void launch_small_p(const ForceArgs& a, const StepArgs* s, int grid, hipStream_t st) {
+  if (s)
+    hipLaunchKernelGGL((k_forces_small<P, MASK, W, true>), dim3(grid), dim3(64 * W), 0, st, a, *s);
+  else
+    hipLaunchKernelGGL((k_forces_small<P, MASK, W, false>), dim3(grid), dim3(64 * W), 0, st, a, StepArgs{});
+}
+
+hipError_t launch_forces_small(int prec, bool mask, const ForceArgs& a, const StepArgs* s, hipStream_t st) {
+  int64_t grid = (a.n_active + kSmallRows - 1) / kSmallRows;
+  if (grid > 4096) grid = 4096;
+  if (grid < 1) grid = 1;
+  const bool wide = a.n > kSmallNarrow;
+#define NB_SMALL(P)                                                                                   \
+  (wide ? (mask ? launch_small_p<P, true, 8>(a, s, (int)grid, st) : launch_small_p<P, false, 8>(a, s, (int)grid, st)) \
+        : (mask ? launch_small_p<P, true, 4>(a, s, (int)grid, st) : launch_small_p<P, false, 4>(a, s, (int)grid, st)))
+  if (prec == NB_PREC_FP64) NB_SMALL(F64);
+  else if (prec == NB_PREC_MIXED_DS) NB_SMALL(MixedDS);
+  else NB_SMALL(Mixed);
+#undef NB_SMALL
   return hipGetLastError();
 }
 

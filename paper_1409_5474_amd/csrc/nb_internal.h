@@ -37,7 +37,15 @@ struct Launch {
                   // shape and, in device-count mode, every shape of the call
   int T = kTile;  // j-particles per LDS tile (L >= 1), also the j-chunk quantum
   int WG = kWG;   // threads per workgroup
+  bool small = false;  // the small-system kernel (K = 1, L = 16, S = 1)
 };
+
+// Up to this many j-particles an untuned system takes the small-system
+// kernel, unless the i-set is many times larger than the j-set: a workgroup
+// reads all j for four rows, which pays while the launch is latency-bound
+// (100000 rows on 1024 j: 247 us against 166 us of the L = 16 shape).
+constexpr int64_t kSmallDirect = 4096;
+inline bool small_direct(int64_t n, int64_t n_act) { return n <= kSmallDirect && n_act <= 4 * n; }
 
 // The LDS tile length and workgroup size every kernel family, the masked
 // (eps2 = 0) kernels and the hybrid path are built for.
@@ -268,6 +276,9 @@ struct StepArgs {
   unsigned long long* clamp_dev;
   unsigned long long* step_dev;
 };
+// Small systems: forces (s null) or forces and corrector of a block step in
+// one launch (k_forces_small); the count from the host or the device.
+hipError_t launch_forces_small(int prec, bool mask, const ForceArgs& a, const StepArgs* s, hipStream_t st);
 hipError_t launch_reduce_correct(int prec, const ForceArgs& a, const StepArgs& s, hipStream_t st);
 // the same for a batched block step (rows of every system, device count)
 hipError_t launch_batch_reduce_correct(int prec, const BatchSys* sys, const int32_t* chunks_per_sys, int C,

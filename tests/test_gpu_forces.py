@@ -69,6 +69,30 @@ def test_small_plummer_all_active(ctx, prec):
         check_mixed(res, ref)
 
 
+@pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("n,na,eps2", [(1, 1, 1e-3), (255, 3, 1e-3), (256, 4, 0.0), (257, 5, 1e-3), (2048, 17, 1e-3),
+                                       (2049, 18, 0.0), (4096, 35, 1e-3), (4097, 33, 1e-3)])
+def test_small_system_kernel_edges(ctx, prec, n, na, eps2):
+    # one launch up to 4096 particles: row blocks of four, tiles of 256, four
+    # wavefronts up to 2048 particles and eight above; its pairs and float runs
+    # are the (K, L) = (1, 16) shape's, so the two differ by the order of the
+    # double sums of at most 17 tiles and 16 lanes: 33 ulps of the row's terms
+    p = _case(n, 40 + n)
+    act = np.sort(np.random.default_rng(n).choice(n, na, replace=False)).astype(np.int32)
+    if na > 2:
+        act[1] = act[0]
+    ref = oracle.forces_ld(p.pos, p.vel, p.mass, eps2, act)
+    res = run_gpu(ctx, prec, p, eps2, act)
+    split = run_gpu(ctx, prec, p, eps2, act, launch=(1, 16, 0))
+    for name, x, y in zip(("acc", "jerk", "pot"), res, split):
+        d = np.linalg.norm((x - y).reshape(na, -1), axis=1)
+        assert np.all(d <= 33 * 2.0 ** -53 * ref["abs_" + name]), name
+    if prec == "fp64":
+        check_fp64(res, ref)
+    elif eps2 > 0 and n > 1:
+        check_mixed(res, ref)
+
+
 # (K, L, S); L = 0 is the scalar j-path
 LAUNCHES = [(1, 1, 1), (2, 1, 1), (4, 1, 1), (1, 1, 3), (2, 1, 5), (1, 2, 1), (1, 4, 2), (2, 8, 3), (4, 16, 1),
             (1, 32, 2), (2, 64, 4), (1, 128, 1), (1, 256, 7), (4, 4, 4), (2, 32, 2), (1, 0, 1), (2, 0, 3), (3, 0, 2), (1, -1, 1), (2, -1, 3), (3, -1, 2),

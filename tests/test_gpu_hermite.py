@@ -129,6 +129,63 @@ def test_schedule_exact(ctx, n):
     assert np.array_equal(N(active)[:expect.size], expect)
 
 
+@pytest.mark.parametrize("n", [255, 256, 257, 4096, 16383, 16384, 16385])
+def test_one_launch_scheduler_and_predictor(ctx, n):
+    # blocks of 256 particles, up to 16 per thread read by every block: t_next,
+    # the ascending active list and every particle's prediction of one block
+    # step, whose stop tick lies before t_next so that nothing is corrected
+    import torch
+    ML, dt_max = 30, 1.0 / 16
+    rng = np.random.default_rng(n)
+    p = synth.plummer(n, 5)
+    level = rng.integers(3, 12, n).astype(np.int32)
+    ticks = (np.int64(1) << (ML - level.astype(np.int64)))
+    t_tick = rng.integers(0, 3, n).astype(np.int64) * ticks
+    t_end = t_tick + ticks
+    pos, vel, mass = T(p.pos), T(p.vel), T(p.mass)
+    acc, jerk = T(rng.standard_normal((n, 3))), T(rng.standard_normal((n, 3)))
+    t, lev = T(t_tick), T(level)
+    new = lambda: torch.full((n, 3), -7.0, dtype=torch.float64, device="cuda")
+    pp, vp, a1, j1, p1 = new(), new(), new(), new(), torch.empty(n, dtype=torch.float64, device="cuda")
+    active = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    sched = torch.zeros(4, dtype=torch.int64, device="cuda")
+    t_next = int(t_end.min())
+    ctx.block_step(n, 1e-3, 0.01, dt_max, ML, mass, pos, vel, acc, jerk, t, lev, pp, vp, active, a1, j1, p1, sched,
+                   t_next - 1)
+    expect = np.nonzero(t_end == t_next)[0].astype(np.int32)
+    assert N(sched).tolist() == [t_next, 0, 0, 0]
+    assert np.array_equal(N(active)[:expect.size], expect)
+    assert np.array_equal(N(t), t_tick) and np.array_equal(N(lev), level) and np.array_equal(N(pos), p.pos)
+    pq, vq = new(), new()
+    ctx.predict(pos, vel, acc, jerk, t, t_next, dt_max * 2.0 ** -ML, pq, vq)
+    assert torch.equal(pp, pq) and torch.equal(vp, vq)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed", "mixed_ds"])
+@pytest.mark.parametrize("n", [3, 700, 2048, 2049, 4096])
+def test_fused_small_step_equals_split_step(ctx, prec, n):
+    # forces and corrector in one launch against the L = 16 shape with its
+    # reduce-and-correct kernel, over twenty block steps: integers equal,
+    # positions within the rounding the two summation orders may leave
+    import torch
+    from paper_1409_5474_amd.integrator import BlockIntegrator
+    p = synth.plummer(n, 6)
+    ctx.set_precision(prec)
+    runs = []
+    for launch in ((0,), (1, 16, 0)):
+        ctx.set_launch(*launch)
+        bi = BlockIntegrator(ctx, T(p.pos), T(p.vel), T(p.mass), 1e-3)
+        for _ in range(20):
+            bi.step()
+        runs.append(bi)
+    ctx.set_launch(0)
+    ctx.set_precision("fp64")
+    a, b = runs
+    assert torch.equal(a.t_tick, b.t_tick) and torch.equal(a.level, b.level) and torch.equal(a.sched, b.sched)
+    assert torch.linalg.norm(a.pos - b.pos) <= 1e-13 * torch.linalg.norm(b.pos)
+    assert torch.linalg.norm(a.vel - b.vel) <= 1e-13 * torch.linalg.norm(b.vel)
+
+
 def test_energy(ctx):
     import torch
     p = synth.plummer(5000, 4)
