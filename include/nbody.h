@@ -154,8 +154,10 @@ int nb_set_launch(nb_ctx *ctx, int K, int L, int S, int T, int WG);
 int nb_get_launch(nb_ctx *ctx, int64_t N, int64_t n_active, int *K, int *L, int *S, int *T, int *WG);
 /* Install one entry of the automatic table: for this precision, N >= n_min
  * and n_active in [act_min, act_max], use the shape (K, L, T, WG), and
- * choose S by the saturation rule aiming at `items` work items (i-blocks x
- * j-subsets; 0 = 4 per compute unit).  The same entry drives host-count and
+ * choose S for about `items` work items (i-blocks x j-subsets; 0 = 4 per
+ * resident workgroup): the split at or just above the target whose items
+ * share out over the compute units more evenly, at most one j-tile per
+ * subset.  The same entry drives host-count and
  * device-count launches, so both split the work identically.  Later
  * entries take precedence on their range.  Used by the autotuner front end
  * to load its cache. */

@@ -220,10 +220,10 @@ bool takes_small(const nb_ctx* c, int64_t n, int64_t n_act) {
 // split the work identically.
 std::vector<Regime> regimes(const nb_ctx* c, int64_t n) {
   if (!tuned_for(c, n) && n <= kSmallSystem) return {Regime{0, INT64_MAX, Launch{1, 16, 0, 0}}};
-  std::vector<Regime> r(std::begin(kDefaultRegimes), std::end(kDefaultRegimes));
+  std::vector<Regime> r(std::begin(kDefaultRegimes), std::end(kDefaultRegimes)), out;
   for (const nb::TuneEntry& e : c->table) {
     if (e.prec != c->prec || n < e.n_min) continue;
-    std::vector<Regime> out;
+    out.clear();
     for (const Regime& g : r) {
       if (g.hi < e.act_min || g.lo > e.act_max) {
         out.push_back(g);
@@ -239,6 +239,17 @@ std::vector<Regime> regimes(const nb_ctx* c, int64_t n) {
   return r;
 }
 
+// The regime of regimes() that holds n_act, found without building the list
+// (this runs in every host-count call): the last table entry that holds it.
+Launch regime_of(const nb_ctx* c, int64_t n, int64_t n_act) {
+  for (auto e = c->table.rbegin(); e != c->table.rend(); ++e)
+    if (e->prec == c->prec && n >= e->n_min && n_act >= e->act_min && n_act <= e->act_max) return e->cfg;
+  Launch cfg;
+  for (const Regime& g : regimes(c, n))
+    if (n_act >= g.lo && n_act <= g.hi) cfg = g.cfg;
+  return cfg;
+}
+
 // Resolve K, L and the work-item target for an active count; S is then the
 // saturation rule unless a forced configuration fixes it.
 Launch choose(const nb_ctx* c, int64_t n, int64_t n_act) {
@@ -251,8 +262,7 @@ Launch choose(const nb_ctx* c, int64_t n, int64_t n_act) {
   if (c->have_forced) {
     cfg = c->forced;
   } else {
-    for (const Regime& g : regimes(c, n))
-      if (n_act >= g.lo && n_act <= g.hi) cfg = g.cfg;
+    cfg = regime_of(c, n, n_act);
   }
   if (cfg.items <= 0) cfg.items = default_items(c, cfg);
   const int IB = nb::ib_of(cfg);

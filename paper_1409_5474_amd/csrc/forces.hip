@@ -451,16 +451,51 @@ struct MixedDS {
   }
 };
 
+// The j-axis of n particles cut into S chunks of whole tiles, as even as
+// tiles allow: the first `extra` chunks hold base + 1 tiles, the others base.
+// The queue hands out the longer chunks first, so the compute units end
+// within about a tile of each other.  Chunks of one common length made the
+// last ones short or empty: FP64 with N = 40009 all active cuts 157 tiles
+// into 19 chunks of 8 or 9 instead of 18 of 9 (1841 -> 1775 us with the split
+// rule below, MI355X).
+struct Chunks {
+  int64_t n, base, extra;
+  int tile;
+  __host__ __device__ Chunks(int64_t n_, int S, int tile_ = kTile) : n(n_), tile(tile_) {
+    const int64_t nt = (n + tile - 1) / tile;
+    base = nt / S;
+    extra = nt - base * S;
+  }
+  __host__ __device__ int64_t begin(int64_t c) const { return (c * base + (c < extra ? c : extra)) * tile; }
+  __host__ __device__ int64_t end(int64_t c) const {
+    const int64_t e = begin(c + 1);
+    return e < n ? e : n;
+  }
+};
+
+// Compute units that share a launch's items.
+constexpr int kShare = 256;
+
 // The j-split chosen on the device (device-count mode) and on the host
-// alike: enough work items to fill the chip, chunks of at least one tile.
+// alike: about target_items work items, chunks of at least one tile.  A
+// compute unit is busy with its share of the items to the end, so the time
+// goes with the rounds ceil(items / kShare) over S: of the two splits around
+// the target the one with fewer rounds per chunk is taken, the smaller where
+// they tie.  Always rounding up put a few items into a round of their own
+// (FP64, shape (2, 1), N = 65536, 19484 active: S = 65, 9.9 rounds, 1446 us;
+// S = 66, 10.05 rounds, 1509 us; N = 40009 all active: S = 32, 1790 us;
+// S = 33, 1886 us).  A target that the i-blocks divide is met exactly.
 __host__ __device__ inline int choose_S(int64_t n_act, int IB, int target_items, int64_t n, int tile = kTile) {
   const int64_t n_iblk = (n_act + IB - 1) / IB;
   if (n_iblk <= 0) return 1;
-  int64_t s = (target_items + n_iblk - 1) / n_iblk;
   const int64_t max_s = (n + tile - 1) / tile;
-  if (s > max_s) s = max_s;
+  int64_t s = target_items / n_iblk;
   if (s < 1) s = 1;
-  return (int)s;
+  if (s * n_iblk != target_items) {
+    const int64_t lo = (s * n_iblk + kShare - 1) / kShare, hi = ((s + 1) * n_iblk + kShare - 1) / kShare;
+    if (hi * s < lo * (s + 1)) ++s;
+  }
+  return (int)(s < max_s ? s : max_s);
 }
 
 // The work-item target of a device-count launch for count d (see n_sub).
@@ -484,11 +519,6 @@ __device__ __forceinline__ int64_t checked_row(const int32_t* active, int64_t k,
   if (row_in_range(r, lo, hi)) return r;
   if (err) atomicOr(err, kErrActiveRange);
   return -1;
-}
-
-__host__ __device__ inline int64_t chunk_len(int64_t n, int S, int tile = kTile) {
-  const int64_t per = (n + S - 1) / S;
-  return ((per + tile - 1) / tile) * tile;
 }
 
 // Shared body: one workgroup processes one (i-block, j-chunk) item.
@@ -626,14 +656,13 @@ __device__ __forceinline__ void run_items(typename P::template JTileT<T>& tile, 
   constexpr int IB = (WG / L) * K;
   const int64_t n_iblk = (n_act + IB - 1) / IB;
   const int64_t items = n_iblk * S;
-  const int64_t clen = chunk_len(a.n, S, T);
+  const Chunks cut(a.n, S, T);
   if (!queue_member(items)) return;
   int64_t w = queue_first(a.wq, items);
   while (w < items) {
     const int64_t chunk = w / n_iblk;
     const int64_t iblk = w - chunk * n_iblk;
-    const int64_t jb = chunk * clen;
-    const int64_t je = jb + clen < a.n ? jb + clen : a.n;
+    const int64_t jb = cut.begin(chunk), je = cut.end(chunk);
     process_item<P, K, L, MASK, T, WG, ATOMIC>(tile, red, a.pos, a.vel, a.mass, a.ipos ? a.ipos : a.pos,
                                 a.ivel ? a.ivel : a.vel, a.no_self ? nullptr : a.mass, jb, je, a.active, n_act, iblk * IB,
                                 a.eps2, S == 1, a.acc, a.jerk, a.pot, a.part + chunk * 7 * n_act, a.row_lo, a.row_hi,
@@ -1098,15 +1127,14 @@ __global__ __launch_bounds__(WG, (SjWaves<P, K>::value)) void k_forces_sj(ForceA
   }
   const int64_t n_iblk = (n_act + IB - 1) / IB;
   const int64_t items = n_iblk * S;
-  const int64_t clen = chunk_len(a.n, S);
+  const Chunks cut(a.n, S);
   __shared__ unsigned int slot;
   if (!queue_member(items)) return;
   int64_t w = queue_first(a.wq, items);
   while (w < items) {
     const int64_t chunk = w / n_iblk;
     const int64_t iblk = w - chunk * n_iblk;
-    const int64_t jb = chunk * clen;
-    const int64_t je = jb + clen < a.n ? jb + clen : a.n;
+    const int64_t jb = cut.begin(chunk), je = cut.end(chunk);
     process_item_sj<P, K, MASK, WG>(rec, a.ipos ? a.ipos : a.pos, a.ivel ? a.ivel : a.vel, a.no_self ? nullptr : a.mass,
                                 jb, je, a.active, n_act, iblk * IB, a.eps2, S == 1,
                                 a.acc, a.jerk, a.pot, a.part + chunk * 7 * n_act, a.row_lo, a.row_hi, a.err);
@@ -1238,15 +1266,14 @@ __global__ __launch_bounds__(kWG, (K == 2 ? 5 : 1)) void k_forces_hy(ForceArgs a
   }
   const int64_t n_iblk = (n_act + IB - 1) / IB;
   const int64_t items = n_iblk * S;
-  const int64_t clen = chunk_len(a.n, S);
+  const Chunks cut(a.n, S);
   __shared__ unsigned int slot;
   if (!queue_member(items)) return;
   int64_t w = queue_first(a.wq, items);
   while (w < items) {
     const int64_t chunk = w / n_iblk;
     const int64_t iblk = w - chunk * n_iblk;
-    const int64_t jb = chunk * clen;
-    const int64_t je = jb + clen < a.n ? jb + clen : a.n;
+    const int64_t jb = cut.begin(chunk), je = cut.end(chunk);
     process_item_hy<K>(rec, vm_tile, a.ipos ? a.ipos : a.pos, a.ivel ? a.ivel : a.vel,
                        a.no_self ? nullptr : a.mass, jb, je, a.active, n_act, iblk * IB, a.eps2, S == 1,
                        a.acc, a.jerk, a.pot, a.part + chunk * 7 * n_act, a.row_lo, a.row_hi, a.err);
@@ -1274,9 +1301,8 @@ __global__ __launch_bounds__(kWG) void k_forces_batch(const BatchItem* __restric
     const BatchSys sy = sys[it.sys];
     const int64_t nj = sy.j1 - sy.j0;
     const int64_t n_act = sy.a1 - sy.a0;
-    const int64_t clen = chunk_len(nj, it.nchunk);
-    const int64_t jb = sy.j0 + (int64_t)it.chunk * clen;
-    const int64_t je = jb + clen < sy.j1 ? jb + clen : sy.j1;
+    const Chunks cut(nj, it.nchunk);
+    const int64_t jb = sy.j0 + cut.begin(it.chunk), je = sy.j0 + cut.end(it.chunk);
     process_item<P, K, L, MASK>(sm.tile, sm.red, pos, vel, mass, pos, vel, mass, jb, je, active + sy.a0, n_act,
                                 (int64_t)it.iblk * IB, sy.eps2, it.nchunk == 1, acc + 3 * sy.a0,
                                 jerk + 3 * sy.a0, pot + sy.a0,
@@ -1303,9 +1329,8 @@ __global__ __launch_bounds__(kBatchSjWG, (SjWaves<P, K>::value)) void k_forces_b
     const BatchSys sy = sys[it.sys];
     const int64_t nj = sy.j1 - sy.j0;
     const int64_t n_act = sy.a1 - sy.a0;
-    const int64_t clen = chunk_len(nj, it.nchunk);
-    const int64_t jb = sy.j0 + (int64_t)it.chunk * clen;
-    const int64_t je = jb + clen < sy.j1 ? jb + clen : sy.j1;
+    const Chunks cut(nj, it.nchunk);
+    const int64_t jb = sy.j0 + cut.begin(it.chunk), je = sy.j0 + cut.end(it.chunk);
     process_item_sj<P, K, MASK, kBatchSjWG>(rec, pos, vel, mass, jb, je, active + sy.a0, n_act, (int64_t)it.iblk * IB, sy.eps2,
                                 it.nchunk == 1, acc + 3 * sy.a0, jerk + 3 * sy.a0, pot + sy.a0,
                                 part + (sy.part_off + (int64_t)it.chunk * n_act) * 7, sy.j0, sy.j1, err);

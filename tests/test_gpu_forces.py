@@ -215,6 +215,20 @@ def test_split_sum_over_many_blocks(ctx, prec, n, S):
 
 
 @pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("S", [1, 2, 3, 4, 7, 8, 9])
+def test_every_split_of_a_ragged_tile_count(ctx, prec, S):
+    # nine tiles, the last of one particle, cut into chunks of base or base + 1
+    # tiles: each pair once, on the LDS and the scalar j-path
+    n = 2049
+    p = _case(n, 32)
+    act = np.arange(0, n, 5, dtype=np.int32)
+    ref = oracle.forces_ld(p.pos, p.vel, p.mass, 2.0 ** -16, act)
+    for shape in [(1, 4), (2, 1), (2, 0)]:
+        res = run_gpu(ctx, prec, p, 2.0 ** -16, act, shape + (S,))
+        (check_fp64 if prec == "fp64" else check_mixed)(res, ref)
+
+
+@pytest.mark.parametrize("prec", PRECS)
 @pytest.mark.parametrize("launch", [(1, 4, 3), (2, 0, 2)])
 def test_bitwise_deterministic(ctx, prec, launch):
     p = _case(5000, 6)
