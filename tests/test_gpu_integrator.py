@@ -264,3 +264,40 @@ def test_batch_with_empty_systems_and_inactive_systems(shape):
     for k in ("pos", "vel", "t_tick", "level"):
         assert torch.equal(getattr(runs[0], k), getattr(runs[1], k)), k
     ctx.close()
+
+
+@pytest.mark.parametrize("C", [1022, 1023, 1024, 2047])
+def test_batch_plan_at_the_edges_of_its_rounds(C):
+    # 1023 systems are planned at a time, and more than 16384 active rows take
+    # searches in global memory first: three systems among empty ones, at the
+    # ends and on both sides of a round's edge, give the bits of the three alone
+    import torch
+    import paper_1409_5474_amd as nb
+    from paper_1409_5474_amd.integrator import BlockIntegrator
+    b = synth.cluster_batch(seed=13, n_clusters=3, n_min=6000, n_max=9000)
+    sizes = np.diff(b.offsets)
+    n = int(b.offsets[-1])
+    assert n > 16384
+    ctx = nb.Context(0, "mixed")
+    ctx.tune_add_batch("mixed", 2, 1, 2 ** 40, 1, 16)
+    runs = []
+    for at in (None, (0, 1022, C - 1), (1, 1021, min(1023, C - 2))):
+        offs, eps = b.offsets, b.eps2
+        if at is not None:
+            at = sorted({min(a, C - 1) for a in at})
+            if len(at) < 3:
+                at = [at[0], C - 2, C - 1]
+            full = np.zeros(C, dtype=np.int64)
+            full[at] = sizes
+            offs = np.concatenate([[0], np.cumsum(full)]).astype(np.int64)
+            eps = np.full(C, 1e-3)
+            eps[at] = b.eps2
+        bi = BlockIntegrator(ctx, T(b.pos), T(b.vel), T(b.mass), eps, 0.02, 1.0 / 64, 30, offsets=offs)
+        bi.run_until(1.0 / 64, graph_steps=8)
+        runs.append(bi)
+    ctx.sync()
+    for r in runs[1:]:
+        assert r.steps == runs[0].steps > 0
+        for k in ("pos", "vel", "t_tick", "level"):
+            assert torch.equal(getattr(r, k), getattr(runs[0], k)), k
+    ctx.close()
