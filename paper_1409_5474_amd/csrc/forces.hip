@@ -1138,7 +1138,7 @@ __global__ __launch_bounds__(WG, (SjWaves<P, K>::value)) void k_forces_sj(ForceA
     process_item_sj<P, K, MASK, WG>(rec, a.ipos ? a.ipos : a.pos, a.ivel ? a.ivel : a.vel, a.no_self ? nullptr : a.mass,
                                 jb, je, a.active, n_act, iblk * IB, a.eps2, S == 1,
                                 a.acc, a.jerk, a.pot, a.part + chunk * 7 * n_act, a.row_lo, a.row_hi, a.err);
-    w = queue_next(a.wq, slot, items, w + gridDim.x);
+    w = queue_next<true>(a.wq, slot, items, w + gridDim.x);
   }
   queue_done(a.wq, items);
 }

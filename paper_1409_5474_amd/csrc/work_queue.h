@@ -72,7 +72,21 @@ __device__ __forceinline__ int64_t interleaved(int64_t w, int64_t items) {
 // atomics cost about a microsecond each, so the ranges are not visited one
 // by one) and takes from the first range with items left, in the order
 // x0 + 1, x0 + 2, ...  Returns the item, or `items` once all are exhausted.
+//
+// The compiler computes the ranges' bounds before the item loop and keeps
+// them in registers.  With FRESH the number of items is opaque here, so they
+// are computed at each pick instead: for the scalar j-path, which runs close
+// to its register limit (mixed, K = 2: 92 -> 28 B of scratch per lane; 262144
+// all active 39.14 -> 38.85 ms).  The LDS kernels have registers to spare and
+// were slower that way (mixed, K = 1, 3899 rows and 1000003 sources: 2651 us,
+// FRESH 2714 us).
+template <bool FRESH>
 __device__ __forceinline__ int64_t queue_pick(unsigned int* wq, int64_t items, unsigned int own) {
+  if constexpr (FRESH) {
+    unsigned int n = (unsigned int)items;
+    asm volatile("" : "+v"(n));
+    items = n;
+  }
   const int x0 = blockIdx.x % kXcd;
   const int64_t members = queue_members(items);
   const int64_t k0 = range_len(members, x0) + own;
@@ -99,12 +113,13 @@ __device__ __forceinline__ int64_t queue_pick(unsigned int* wq, int64_t items, u
 }
 
 // A member's next item (w_stride: its next item without a queue).
+template <bool FRESH = false>
 __device__ __forceinline__ int64_t queue_next(unsigned int* wq, unsigned int& slot, int64_t items, int64_t w_stride) {
   if (!wq) return w_stride;
   if (items <= (int64_t)gridDim.x) return items;  // every item was some member's first
   __syncthreads();  // every thread has read `slot` before it is replaced
   if (threadIdx.x == 0)
-    slot = (unsigned int)queue_pick(wq, items, atomicAdd(queue_range(wq, blockIdx.x % kXcd), 1u));
+    slot = (unsigned int)queue_pick<FRESH>(wq, items, atomicAdd(queue_range(wq, blockIdx.x % kXcd), 1u));
   __syncthreads();
   // one value for the whole wave: read into a scalar register, so everything
   // derived from the item (chunk bounds, record addresses) stays uniform
