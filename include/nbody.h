@@ -138,8 +138,8 @@ const char *nb_version(void);
  * S = j-subsets, one work item each per i-block, whose partial sums a second
  * kernel adds in fixed order (>= 1).  The paper's rule is that the device is
  * saturated once N_i times the number of j-subsets exceeds the number of
- * threads.  T = j-particles per LDS tile, also the length a j-subset is
- * rounded up to (S <= ceil(N / T)); WG = threads per workgroup, so an
+ * threads.  T = j-particles per LDS tile; the j-subsets are whole
+ * tiles and differ by at most one (S <= ceil(N / T)); WG = threads per workgroup, so an
  * i-block holds (WG / L) K i-particles (L = 0: WG K).  T and WG = 0 mean
  * 256, the size every shape is built for; besides that the library builds
  * (T, WG) = (128, 256), (128, 128) and (64, 64) for (K, L) in {(1, 1),
@@ -148,7 +148,9 @@ const char *nb_version(void);
  * nb_set_launch forces one configuration for every later force call
  * (K = 0 returns to automatic choice); nb_get_launch reports the
  * configuration the context would use for (N, n_active) (T and WG may be
- * NULL).  Errors: NB_EINVAL for values outside the ranges above,
+ * NULL).  Up to 4096 particles without a tuned entry or a forced
+ * configuration one launch computes whole rows (no j-split); it is
+ * reported as the shape whose sums it forms, K = 1, L = 16, S = 1.  Errors: NB_EINVAL for values outside the ranges above,
  * NB_ENOTSUP for a combination the library does not build. */
 int nb_set_launch(nb_ctx *ctx, int K, int L, int S, int T, int WG);
 int nb_get_launch(nb_ctx *ctx, int64_t N, int64_t n_active, int *K, int *L, int *S, int *T, int *WG);
@@ -376,7 +378,7 @@ int nb_block_step6(nb_ctx *ctx, int64_t N, double eps2, double eta, double dt_ma
  * are double for an NB_PREC_FP64 context and otherwise float terms from
  * double separations, summed in double per staged chunk of up to 64 cells or
  * 64 leaf particles.  The walk and the force evaluation are one kernel (one
- * wavefront per group); no interaction list is stored.
+ * wavefront per group, or a team of eight while groups are few); no interaction list is stored.
  * theta = 0 opens every leaf: the direct sum.  pos [N][3], mass [N] in,
  * acc [N][3], pot [N] out, all in the caller's order (device pointers).
  * stats (host array of 5, may be NULL): cells, groups, accepted (group, cell)
@@ -441,7 +443,9 @@ int nb_set_stop_source(nb_ctx *ctx, const int64_t *t_stop_dev);
  * on this context (nb_block_step, nb_block_step_batch, nb_block_step6)
  * that is not being captured into a graph records four HIP events on the
  * context stream: at its start, after the scheduler with the predictor (and
- * the batch plan), after the force launches and after the corrector.  The
+ * the batch plan), after the force launches and after the corrector (up to
+ * 4096 particles the force launch also corrects, and the last phase is
+ * empty).  The
  * events cost a few microseconds per step; steps captured into a graph
  * record none.  Switching on creates the events (NB_EDEVICE if that fails);
  * switching on or off forgets the last step's times. */
