@@ -854,10 +854,10 @@ int devcount_forces(nb_ctx* c, const double* pos, const double* vel, const doubl
     if (g.r.lo > max_active) break;
     for (int k = 0; k < g.n_sub; ++k) {
       if (g.sub_lo[k] > max_active) break;
-      const int IB = nb::ib_of(g.sub_cfg[k]);
-      const int64_t n_iblk_max = (sub_top(g, k) + IB - 1) / IB;
-      const size_t rows = (size_t)(g.sub_items[k] + n_iblk_max) * IB;
-      const size_t need = rows * 7 * sizeof(double);
+      const Launch& sc = g.sub_cfg[k];
+      const int tile = sc.L > 0 ? sc.T : nb::kTile;
+      const int64_t rows = nb::host_split_rows(sub_top(g, k), nb::ib_of(sc), g.sub_items[k], N, tile);
+      const size_t need = (size_t)rows * 7 * sizeof(double);
       if (need > ws_need) ws_need = need;
     }
   }

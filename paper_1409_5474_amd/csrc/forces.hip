@@ -484,13 +484,15 @@ constexpr int kShare = 256;
 // they tie.  Always rounding up put a few items into a round of their own
 // (FP64, shape (2, 1), N = 65536, 19484 active: S = 65, 9.9 rounds, 1446 us;
 // S = 66, 10.05 rounds, 1509 us; N = 40009 all active: S = 32, 1790 us;
-// S = 33, 1886 us).  A target that the i-blocks divide is met exactly.
+// S = 33, 1886 us).  A target that the i-blocks divide is met exactly, and
+// more i-blocks than the target are not split at all: they are the items.
+// host_split_rows below relies on both: S is at most one above target /
+// i-blocks, and 1 from there on.
 __host__ __device__ inline int choose_S(int64_t n_act, int IB, int target_items, int64_t n, int tile = kTile) {
   const int64_t n_iblk = (n_act + IB - 1) / IB;
-  if (n_iblk <= 0) return 1;
+  if (n_iblk <= 0 || n_iblk > target_items) return 1;
   const int64_t max_s = (n + tile - 1) / tile;
   int64_t s = target_items / n_iblk;
-  if (s < 1) s = 1;
   if (s * n_iblk != target_items) {
     const int64_t lo = (s * n_iblk + kShare - 1) / kShare, hi = ((s + 1) * n_iblk + kShare - 1) / kShare;
     if (hi * s < lo * (s + 1)) ++s;
@@ -2167,6 +2169,18 @@ hipError_t launch_batch_plan(const int64_t* off, const double* eps2, int C, cons
 
 int host_choose_S(int64_t n_act, int IB, int target_items, int64_t n, int tile) {
   return choose_S(n_act, IB, target_items, n, tile);
+}
+
+// The most partial-sum rows, S n_act, that choose_S takes for any count up to
+// `top`: a count of b <= target i-blocks gets S b <= target + b items of at
+// most IB rows, and S <= the number of tiles; more i-blocks, and a target of
+// one item, are not split and write no partial sums.
+int64_t host_split_rows(int64_t top, int IB, int target_items, int64_t n, int tile) {
+  if (target_items <= 1 || top < 1) return 0;
+  const int64_t n_iblk = (top + IB - 1) / IB;
+  const int64_t by_items = ((int64_t)target_items + (n_iblk < target_items ? n_iblk : target_items)) * IB;
+  const int64_t by_tiles = (n + tile - 1) / tile * top;
+  return by_items < by_tiles ? by_items : by_tiles;
 }
 
 }  // namespace nb

@@ -1,0 +1,99 @@
+"""The j-split rule of the force launches against the space reserved for its
+partial sums, on the library's own host functions (no GPU call): a
+device-count launch reserves host_split_rows for every count up to its
+regime's top before it knows the count, and the kernels then write
+S x n_active rows.  A split of more i-blocks than the item target would write
+past them."""
+import ctypes
+
+import numpy as np
+import pytest
+
+
+def _functions():
+    import paper_1409_5474_amd as nb
+    lib = nb.library()
+    choose, rows = lib._ZN2nb13host_choose_SEliili, lib._ZN2nb15host_split_rowsEliili
+    for f, res in ((choose, ctypes.c_int), (rows, ctypes.c_int64)):
+        f.restype = res
+        f.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_int]
+    return choose, rows
+
+
+def _counts(top, IB, target, rng):
+    """Every kind of count up to top: the smallest, around whole i-blocks, around
+    as many i-blocks as the target has items, and the largest."""
+    near = [1, 2, IB - 1, IB, IB + 1, (target - 1) * IB, target * IB, target * IB + 1, (target + 1) * IB,
+            target * IB * 5 // 3, 2 * target * IB, 3 * target * IB + 1, top - 1, top]
+    near += [int(x) for x in np.exp(rng.uniform(0, np.log(max(top, 2)), 40))]
+    return sorted({d for d in near if 1 <= d <= top})
+
+
+@pytest.mark.parametrize("tile", [64, 128, 256])
+@pytest.mark.parametrize("IB", [1, 4, 16, 64, 128, 256, 512, 1024])
+def test_partial_sums_fit_the_reserved_rows(IB, tile):
+    choose, rows = _functions()
+    rng = np.random.default_rng(IB * 1000 + tile)
+    for _ in range(60):
+        n = int(np.exp(rng.uniform(0, np.log(4e6))))
+        target = int(rng.choice([1, 2, 3, 255, 256, 257, 1024, 4096, 8192, 24576, int(np.exp(rng.uniform(0, 11)))]))
+        top = max(1, int(n * rng.choice([1.0, 1.0, 0.3, 2.0])))
+        room = rows(top, IB, target, n, tile)
+        for d in _counts(top, IB, target, rng):
+            S = choose(d, IB, target, n, tile)
+            assert 1 <= S <= max(1, -(-n // tile))
+            assert S == 1 or S * d <= room, (d, IB, target, n, tile, S, room)
+
+
+def test_more_blocks_than_the_target_are_not_split():
+    # the split's items already exceed the target: no partial sums, no second kernel
+    choose, rows = _functions()
+    for IB in (1, 4, 256, 512):
+        for target in (1, 256, 1024, 8192):
+            for blocks in (target + 1, target + 100, 2 * target, 5 * target + 3):
+                assert choose(blocks * IB, IB, target, 10 ** 7, 256) == 1
+    assert rows(10 ** 6, 256, 1, 10 ** 6, 256) == 0
+
+
+def test_split_stays_at_or_below_the_saturation_rule():
+    # ceil(target / i-blocks) chunks saturate the device; the rule takes that
+    # many or one fewer, so it never needs more space than it
+    choose, _ = _functions()
+    rng = np.random.default_rng(3)
+    for _ in range(3000):
+        IB, target = int(rng.choice([4, 64, 256, 512])), int(np.exp(rng.uniform(0, 10)))
+        n = int(np.exp(rng.uniform(0, np.log(4e6))))
+        d = int(np.exp(rng.uniform(0, np.log(4e6))))
+        b, tiles = -(-d // IB), -(-n // 256)
+        up = max(1, min(-(-target // b), tiles))
+        assert up - 1 <= choose(d, IB, target, n, 256) <= up, (d, IB, target, n)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,items", [((1, 64), 300), ((1, 256), 700), ((2, 4), 20)])
+def test_device_count_with_more_blocks_than_items(shape, items):
+    # counts below and above `items` i-blocks: the device-count launch gives the
+    # bits of the host-count one
+    import torch
+    import paper_1409_5474_amd as nb
+    import synth
+    n = 5000
+    ib = 256 // shape[1] * shape[0]
+    p = synth.plummer(n, 12)
+    t = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    P, V, M, act = t(p.pos), t(p.vel), t(p.mass), t(np.arange(n, dtype=np.int32))
+    with_table = nb.Context(0, "fp64", load_tuning=False)
+    with_table.tune_add("fp64", 1, 0, 2 ** 31 - 1, *shape, items)
+    for na in (ib * items // 2, ib * items, ib * items + 1, min(n, 2 * ib * items + 3), n):
+        if na > n:
+            continue
+        ref = with_table.forces(P, V, M, act[:na].contiguous(), 1e-3)
+        out = (torch.empty((n, 3), dtype=torch.float64, device="cuda"),
+               torch.empty((n, 3), dtype=torch.float64, device="cuda"),
+               torch.empty(n, dtype=torch.float64, device="cuda"))
+        with_table.forces_devcount(P, V, M, act, torch.tensor([na], dtype=torch.int32, device="cuda"), n, 1e-3, *out)
+        torch.cuda.synchronize()
+        for a, b in zip(ref, out):
+            assert torch.equal(a, b[:na]), na
+    with_table.sync()
+    with_table.close()
