@@ -43,9 +43,13 @@
  *  - The context owns only its launch table, a workspace for j-split
  *    partial sums (grown on demand with hipMalloc outside any stream capture)
  *    and a few bytes of device scratch.  If the environment variable
- *    NB_MAX_WORKSPACE_BYTES holds a decimal byte count, a call whose j-split
- *    (or scalar-path mirror) workspace would exceed it fails with NB_ENOMEM
- *    before anything is launched, leaving every output untouched.  The tree
+ *    NB_MAX_WORKSPACE_BYTES holds a decimal byte count, the workspace stays
+ *    within it: an automatic launch of nbody_forces, nbody_forces_ij,
+ *    nbody_forces_devcount or nb_block_step takes the largest j-split whose
+ *    partial sums fit (the results then differ in the order of the sums only),
+ *    and a call that cannot (a forced launch, the scalar-path mirror, a
+ *    batch) fails with NB_ENOMEM before anything is launched, leaving every
+ *    output untouched.  The tree
  *    code keeps its own buffers (about 200 bytes per particle plus its
  *    interaction lists), which the cap does not cover.
  *  - NB_LOG, read by nb_create: 1 prints every error a call on the context

@@ -112,6 +112,9 @@ int ensure_ws(nb_ctx* c, size_t bytes) {
   return NB_OK;
 }
 
+// Bytes the workspace may hold: its cap, or what it already has.
+size_t workspace_room(const nb_ctx* c) { return std::max(workspace_cap(), c->ws_bytes); }
+
 // The j-record mirror of the scalar j-path (L = 0), grown on demand.
 int ensure_mirror(nb_ctx* c, int64_t n) {
   const size_t bytes = nb::mirror_bytes(c->prec, n);
@@ -270,6 +273,22 @@ Launch choose(const nb_ctx* c, int64_t n, int64_t n_act) {
   if (cfg.S <= 0) cfg.S = nb::host_choose_S(n_act, IB, cfg.items, n, tile);
   const int64_t max_s = (n + tile - 1) / tile;
   if (cfg.S > max_s) cfg.S = (int)max_s;
+  return cfg;
+}
+
+// Bytes of one j-chunk's partial sums for a row.
+constexpr size_t kPartRow = 7 * sizeof(double);
+
+// choose(), with an automatic j-split lowered to what the workspace cap
+// allows: the table's entries are made without a cap, so one must not turn a
+// call away that a smaller split serves (the sums then differ only in their
+// order).  A forced launch keeps its S and is refused.
+Launch choose_capped(const nb_ctx* c, int64_t n, int64_t n_act) {
+  Launch cfg = choose(c, n, n_act);
+  if (cfg.S > 1 && !c->have_forced && !c->split_atomic && (size_t)cfg.S * kPartRow * n_act > c->ws_bytes) {
+    const size_t fit = workspace_room(c) / (kPartRow * (size_t)n_act);
+    if (fit < (size_t)cfg.S) cfg.S = fit >= 2 ? (int)fit : 1;
+  }
   return cfg;
 }
 
@@ -649,7 +668,7 @@ int nbody_forces(nb_ctx* c, const double* pos, const double* vel, const double* 
   int rc = check_forces_args(c, pos, vel, mass, N, active, n_active, eps2, acc, jerk, pot);
   if (rc) return rc;
   if (n_active == 0) return NB_OK;
-  const Launch cfg = choose(c, N, n_active);
+  const Launch cfg = choose_capped(c, N, n_active);
   return run_forces(c, cfg, pos, vel, mass, N, active, n_active, eps2, acc, jerk, pot);
 }
 
@@ -664,7 +683,7 @@ int nbody_forces_noalloc(nb_ctx* c, const double* pos, const double* vel, const 
   if (!base) return hip_fail(c, se, "address of the fixed scratch");
   // the launch nbody_forces would take, so the two give identical results
   Launch cfg = choose(c, N, n_active);
-  const size_t row_bytes = 7 * sizeof(double) * (size_t)n_active;  // one j-chunk's partial sums
+  const size_t row_bytes = kPartRow * (size_t)n_active;  // one j-chunk's partial sums
   auto part_bytes = [&](int S) { return S > 1 ? align256((size_t)S * row_bytes) : (size_t)0; };
   const size_t rec = cfg.L <= 0 ? nb::mirror_bytes(c->prec, N) : 0;
   if (part_bytes(cfg.S) + rec > kScratchBytes) {
@@ -699,7 +718,7 @@ int nbody_forces_ij(nb_ctx* c, const double* pos_j, const double* vel_j, const d
   if (n_active > 0 && (N_i < 1 || !pos_i || !vel_i))
     return fail(c, NB_EINVAL, "i-particle arrays are empty or null%s");
   if (n_active == 0) return NB_OK;
-  const Launch cfg = choose(c, N_j, n_active);
+  const Launch cfg = choose_capped(c, N_j, n_active);
   return run_forces(c, cfg, pos_j, vel_j, mass_j, N_j, active, n_active, eps2, acc, jerk, pot, pos_i, vel_i, true,
                     nullptr, N_i);
 }
@@ -796,13 +815,16 @@ int devcount_forces(nb_ctx* c, const double* pos, const double* vel, const doubl
     return resident_grid(c, o, mask);
   };
   std::vector<Group> groups;
+  const size_t room_rows = std::min(workspace_room(c) / kPartRow, (size_t)INT64_MAX);
   for (const Regime& r : regimes(c, N)) {
     Launch cfg = c->have_forced ? c->forced : r.cfg;
     if (mask) cfg = nb::masked(cfg);
     cfg.fam = 0;
-    const int items = cfg.items > 0 ? cfg.items : default_items(c, cfg);
+    int items = cfg.items > 0 ? cfg.items : default_items(c, cfg);
     const int64_t top = r.hi < max_active ? r.hi : max_active;
     const int IB = nb::ib_of(cfg);
+    if (!c->have_forced)  // as in choose_capped
+      items = nb::host_fit_items(top, IB, items, N, cfg.L > 0 ? cfg.T : nb::kTile, (int64_t)room_rows);
     const int64_t grid = items + (top > 0 ? (top + IB - 1) / IB : 0);
     bool join = false;
     int fam = 0;
@@ -857,7 +879,7 @@ int devcount_forces(nb_ctx* c, const double* pos, const double* vel, const doubl
       const Launch& sc = g.sub_cfg[k];
       const int tile = sc.L > 0 ? sc.T : nb::kTile;
       const int64_t rows = nb::host_split_rows(sub_top(g, k), nb::ib_of(sc), g.sub_items[k], N, tile);
-      const size_t need = (size_t)rows * 7 * sizeof(double);
+      const size_t need = (size_t)rows * kPartRow;
       if (need > ws_need) ws_need = need;
     }
   }

@@ -2183,4 +2183,14 @@ int64_t host_split_rows(int64_t top, int IB, int target_items, int64_t n, int ti
   return by_items < by_tiles ? by_items : by_tiles;
 }
 
+// The largest item target, at most target_items, whose partial sums stay
+// within max_rows (1 -- no split -- fits any).
+int host_fit_items(int64_t top, int IB, int target_items, int64_t n, int tile, int64_t max_rows) {
+  if (host_split_rows(top, IB, target_items, n, tile) <= max_rows) return target_items;
+  // t + min(i-blocks, t) <= room, with either side of the minimum the smaller
+  const int64_t room = max_rows / IB, n_iblk = (top + IB - 1) / IB;
+  const int64_t t = room - n_iblk >= n_iblk ? room - n_iblk : room / 2;
+  return t > 1 ? (int)t : 1;
+}
+
 }  // namespace nb

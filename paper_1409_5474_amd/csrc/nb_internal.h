@@ -224,6 +224,8 @@ hipError_t launch_reduce_ib(int prec, const ForceArgs& a, int S, int IB, hipStre
 int host_choose_S(int64_t n_act, int IB, int target_items, int64_t n, int tile);
 // The rows of partial sums that split needs at most for any count up to `top`.
 int64_t host_split_rows(int64_t top, int IB, int target_items, int64_t n, int tile);
+// The largest item target (at most target_items) that needs no more than max_rows of them.
+int host_fit_items(int64_t top, int IB, int target_items, int64_t n, int tile, int64_t max_rows);
 bool launch_supported(const Launch& cfg);
 int items_for(const Launch& cfg, int64_t n_active, int S);
 hipError_t launch_batch(int prec, const Launch& cfg, const BatchItem* items, int n_items, const int* n_items_dev,

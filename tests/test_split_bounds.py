@@ -69,6 +69,78 @@ def test_split_stays_at_or_below_the_saturation_rule():
         assert up - 1 <= choose(d, IB, target, n, 256) <= up, (d, IB, target, n)
 
 
+def test_capped_target_is_the_largest_that_fits():
+    import paper_1409_5474_amd as nb
+    fit = nb.library()._ZN2nb14host_fit_itemsEliilil
+    fit.restype, fit.argtypes = ctypes.c_int, [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int64,
+                                               ctypes.c_int, ctypes.c_int64]
+    _, rows = _functions()
+    rng = np.random.default_rng(8)
+    for _ in range(3000):
+        IB, target = int(rng.choice([1, 4, 64, 256, 512])), int(np.exp(rng.uniform(0, 10)))
+        n = int(np.exp(rng.uniform(0, np.log(4e6))))
+        top = max(1, int(n * rng.uniform(0.01, 1)))
+        cap = int(np.exp(rng.uniform(0, 18))) if rng.random() < 0.9 else 2 ** 62
+        t = fit(top, IB, target, n, 256, cap)
+        assert 1 <= t <= target and rows(top, IB, t, n, 256) <= cap
+        # the next target reserves more, unless the number of tiles bounds both
+        assert t == target or rows(top, IB, t + 1, n, 256) > cap or rows(top, IB, target, n, 256) <= cap
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("prec,n,cap", [("fp64", 9620, 6 << 20), ("fp64", 22000, 1 << 20), ("mixed_ds", 65536, 4 << 20),
+                                        ("mixed", 16384, 0)])
+def test_automatic_splits_fit_the_workspace_cap(prec, n, cap):
+    # under NB_MAX_WORKSPACE_BYTES every automatic call of the fourth-order
+    # forces runs with the split that fits, from the host's count and the
+    # device's; the sums differ from an uncapped context's in their order only
+    import os
+    import subprocess
+    import sys
+    code = r"""
+import os, sys, numpy as np, torch
+sys.path.insert(0, %r)
+import paper_1409_5474_amd as nb, synth
+prec, n, cap = %r, %d, %d
+p = synth.plummer(n, 3)
+t = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
+P, V, M = t(p.pos), t(p.vel), t(p.mass)
+sets = [t(np.arange(0, n, max(1, n // k), dtype=np.int32)) for k in (3, 500, 2000)]
+def go():
+    c = nb.Context(0, prec)
+    out = []
+    for act in sets:
+        out.append(c.forces(P, V, M, act, 1e-4))
+        out.append(c.forces_ij(P, V, M, P, V, act, 1e-4))
+        full = torch.zeros(n, dtype=torch.int32, device="cuda")
+        full[:len(act)] = act
+        o = (torch.empty((n, 3), dtype=torch.float64, device="cuda"), torch.empty((n, 3), dtype=torch.float64, device="cuda"),
+             torch.empty(n, dtype=torch.float64, device="cuda"))
+        c.forces_devcount(P, V, M, full, torch.tensor([len(act)], dtype=torch.int32, device="cuda"), n, 1e-4, *o)
+        out.append([x[:len(act)] for x in o])
+    torch.cuda.synchronize()
+    c.sync()
+    return out, c.workspace_bytes()
+free, _ = go()
+os.environ["NB_MAX_WORKSPACE_BYTES"] = str(cap)
+capped, used = go()
+worst = 0.0
+for a, b in zip(free, capped):
+    for x, y in zip(a, b):
+        worst = max(worst, float(torch.linalg.norm(x - y) / torch.linalg.norm(x)))
+# beside the capped workspace: the scalar path's j-records (up to 48 bytes), under a cap of their own
+print("USED", used, used <= cap + (0 if prec == "fp64" else 48 * (n + 1)), worst)
+""" % (os.path.dirname(os.path.dirname(os.path.abspath(__file__))), prec, n, cap)
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=100)
+    assert "USED" in r.stdout, (r.stdout, r.stderr[-2000:])
+    used, ok, worst = r.stdout.split("USED")[1].split()
+    assert ok == "True", r.stdout
+    # double sums of at most 256 chunks in another order (the pairs and, in the
+    # mixed policies, the float runs are the same), of terms that cancel to no
+    # less than a hundredth
+    assert float(worst) <= 100 * 256 * 2.0 ** -53, r.stdout
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("shape,items", [((1, 64), 300), ((1, 256), 700), ((2, 4), 20)])
 def test_device_count_with_more_blocks_than_items(shape, items):
