@@ -45,10 +45,10 @@
  *    and a few bytes of device scratch.  If the environment variable
  *    NB_MAX_WORKSPACE_BYTES holds a decimal byte count, the workspace stays
  *    within it: an automatic launch of nbody_forces, nbody_forces_ij,
- *    nbody_forces_devcount or nb_block_step takes the largest j-split whose
- *    partial sums fit (the results then differ in the order of the sums only),
- *    and a call that cannot (a forced launch, the scalar-path mirror, a
- *    batch) fails with NB_ENOMEM before anything is launched, leaving every
+ *    nbody_forces_devcount, nbody_forces6 or a (sixth-order) block step takes
+ *    the largest j-split whose partial sums fit (the results then differ in
+ *    the order of the sums only), and a call that cannot (a forced launch, the
+ *    scalar-path mirror, a batch) fails with NB_ENOMEM before anything is launched, leaving every
  *    output untouched.  The tree
  *    code keeps its own buffers (about 200 bytes per particle plus its
  *    interaction lists), which the cap does not cover.

@@ -983,13 +983,18 @@ static int run_forces6(nb_ctx* c, const double* pos, const double* vel, const do
   a.pos = pos; a.vel = vel; a.accj = accj; a.mass = mass; a.n = N;
   a.active = active; a.n_active = n_max; a.n_active_dev = n_active_dev; a.eps2 = eps2;
   a.slots = grid;
-  a.S = nb::forces6_split(n_max, grid, N);
+  // the workspace cap lowers the split as in choose_capped
+  constexpr size_t row = 10 * sizeof(double);
+  const size_t room_rows = std::min(workspace_room(c) / row, (size_t)INT64_MAX);
+  a.target_items = nb::host_fit_items(n_max, nb::kWG, nb::forces6_target(grid), N, nb::kTile, (int64_t)room_rows);
+  a.S = nb::forces6_split(n_max, grid, a.target_items, N);
   a.acc = acc; a.jerk = jerk; a.snap = snap; a.pot = pot;
   a.wq = c->wq;
   a.err = c->wq + nb::kErrorWord;
-  const int64_t rows = n_active_dev ? nb::forces6_workspace_rows(n_max, grid, N) : (int64_t)a.S * n_max;
+  const int64_t rows = n_active_dev ? nb::host_split_rows(n_max, nb::kWG, a.target_items, N, nb::kTile)
+                                    : (int64_t)a.S * n_max;
   if (n_active_dev || a.S > 1) {
-    int rc = ensure_ws(c, (size_t)rows * 10 * sizeof(double));
+    int rc = ensure_ws(c, (size_t)rows * row);
     if (rc) return rc;
     a.part = static_cast<double*>(c->ws);
   }

@@ -68,11 +68,14 @@ __host__ __device__ inline int64_t chunk6(int64_t n, int S) {
 }
 
 // How an active count is cut: L lanes per i-particle (an i-block holds
-// kWG6 / L rows) and S j-chunks.
+// kWG6 / L rows) and S j-chunks, about target_items items.  host_split_rows
+// with (kWG6, kT6) bounds the partial sums of every count for both L: four
+// times the i-blocks of a quarter of the rows, and no split from target_items
+// i-blocks on.
 struct Split6 {
   int L, S;
 };
-__host__ __device__ inline Split6 split6(int64_t n_act, int slots, int64_t n) {
+__host__ __device__ inline Split6 split6(int64_t n_act, int slots, int target_items, int64_t n) {
   Split6 r{1, 1};
   if (n_act <= 0) return r;
   const int64_t max_s = (n + kT6 - 1) / kT6;
@@ -85,7 +88,7 @@ __host__ __device__ inline Split6 split6(int64_t n_act, int slots, int64_t n) {
   if ((n_act + kWG6 - 1) / kWG6 * max_s * 4 <= 2 * (int64_t)slots) r.L = 4;
   const int64_t ib = kWG6 / r.L;
   const int64_t n_iblk = (n_act + ib - 1) / ib;
-  int64_t s = ((int64_t)kItems6 * slots + n_iblk - 1) / n_iblk;
+  int64_t s = (target_items + n_iblk - 1) / n_iblk;
   if (s > max_s) s = max_s;
   if (s < 1) s = 1;
   const int64_t c = chunk6(n, (int)s);  // whole tiles, so fewer chunks may cover n
@@ -235,7 +238,7 @@ __global__ __launch_bounds__(kWG6) void k_forces6(Force6Args a) {
   __shared__ Tile6 tile;
   __shared__ unsigned int slot;
   const int64_t n_act = active_count6(a);
-  const Split6 sp = split6(n_act, a.slots, a.n);
+  const Split6 sp = split6(n_act, a.slots, a.target_items, a.n);
   if (sp.L == 1) run_items6<1, MASK>(tile, slot, a, n_act, sp.S);
   else run_items6<4, MASK>(tile, slot, a, n_act, sp.S);
 }
@@ -243,7 +246,7 @@ __global__ __launch_bounds__(kWG6) void k_forces6(Force6Args a) {
 // Fixed-order sum of the S partial blocks, self-term removal, output.
 __global__ __launch_bounds__(256) void k_reduce6(Force6Args a) {
   const int64_t n_act = active_count6(a);
-  const int S = split6(n_act, a.slots, a.n).S;
+  const int S = split6(n_act, a.slots, a.target_items, a.n).S;
   if (S <= 1) return;
   const int64_t total = kC6 * n_act;
   const int g = chunk_lanes(S);
@@ -287,15 +290,10 @@ int forces6_resident_wgs(bool mask) {
   return nblk;
 }
 
-int forces6_split(int64_t n_act, int slots, int64_t n) { return split6(n_act, slots, n).S; }
+int forces6_target(int slots) { return kItems6 * slots; }
 
-int64_t forces6_workspace_rows(int64_t n_max, int slots, int64_t n) {
-  // S * n_act over every count up to n_max: S <= kItems6 slots / n_iblk + 1
-  // with i-blocks of at most kWG6 rows, so
-  // S * n_act <= (kItems6 slots + n_iblk) * IB <= kItems6 slots kWG6 + n_max + kWG6
-  const int64_t bound = (int64_t)kItems6 * slots * kWG6 + n_max + kWG6;
-  const int64_t max_s = (n + kT6 - 1) / kT6;
-  return bound < max_s * n_max ? bound : max_s * n_max;
+int forces6_split(int64_t n_act, int slots, int target_items, int64_t n) {
+  return split6(n_act, slots, target_items, n).S;
 }
 
 hipError_t launch_forces6(const Force6Args& a, bool mask, int grid, hipStream_t st) {

@@ -185,7 +185,8 @@ struct Force6Args {
   const int32_t* n_active_dev;  // optional device count
   double eps2;
   int S;                        // j-chunks (host count only: sizes the reduce)
-  int slots;                    // workgroups the chip holds at once; the split follows from them and the count
+  int slots;                    // workgroups the chip holds at once and
+  int target_items;             // work items aimed at: the split follows from them and the count
   double* acc;
   double* jerk;
   double* snap;
@@ -336,8 +337,8 @@ void tree_scratch_free(TreeScratch& s);
 
 // Sixth-order force kernel (forces6.hip).
 int forces6_resident_wgs(bool mask);
-int forces6_split(int64_t n_act, int slots, int64_t n);
-int64_t forces6_workspace_rows(int64_t n_max, int slots, int64_t n);
+int forces6_target(int slots);
+int forces6_split(int64_t n_act, int slots, int target_items, int64_t n);
 hipError_t launch_forces6(const Force6Args& a, bool mask, int grid, hipStream_t st);
 
 // Sixth-order Hermite passes (hermite6.hip).

@@ -87,6 +87,58 @@ def test_capped_target_is_the_largest_that_fits():
         assert t == target or rows(top, IB, t + 1, n, 256) > cap or rows(top, IB, target, n, 256) <= cap
 
 
+def test_sixth_order_partial_sums_fit_the_reserved_rows():
+    # both lane splits (one and four lanes per row), at every target the cap may leave
+    import paper_1409_5474_amd as nb
+    split = nb.library()._ZN2nb13forces6_splitEliil
+    split.restype, split.argtypes = ctypes.c_int, [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int64]
+    _, rows = _functions()
+    rng = np.random.default_rng(6)
+    for _ in range(1500):
+        n = int(np.exp(rng.uniform(0, np.log(1e6))))
+        top = max(1, int(n * rng.choice([1.0, 0.2])))
+        slots = int(rng.choice([32, 768, 1024]))
+        target = int(rng.choice([1, 2, 5, 64, slots, 4 * slots, 8 * slots]))
+        room = rows(top, 256, target, n, 256)
+        for d in _counts(top, 64, target, rng):
+            S = split(d, slots, target, n)
+            assert S == 1 or S * d <= room, (d, slots, target, n, S, room)
+            assert S == 1 or target > 1
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,cap", [(1000, 100000), (20011, 1 << 20), (20011, 0)])
+def test_sixth_order_splits_fit_the_workspace_cap(monkeypatch, n, cap):
+    # forces and block steps run under a cap with the split that fits it
+    import torch
+    import paper_1409_5474_amd as nb
+    import synth
+    from paper_1409_5474_amd.integrator import BlockIntegrator6
+    p = synth.plummer(n, 4)
+    t = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    P, V, M = t(p.pos), t(p.vel), t(p.mass)
+    act = t(np.arange(0, n, 7, dtype=np.int32))
+    results = []
+    for limit in (None, cap):
+        if limit is not None:
+            monkeypatch.setenv("NB_MAX_WORKSPACE_BYTES", str(limit))
+        c = nb.Context(0, "fp64")
+        r = list(c.forces6(P, V, -P, M, act, 1e-3))
+        bi = BlockIntegrator6(c, P.clone(), V.clone(), M, 1e-3, 0.15, 1.0 / 16, 24, 0.01)
+        for _ in range(3):
+            bi.step()
+        c.sync()
+        used = c.workspace_bytes()
+        results.append((r + [bi.pos, bi.vel], [bi.t_tick, bi.level]))
+        c.close()
+    assert used <= cap
+    for a, b in zip(results[0][0], results[1][0]):
+        # as above: the order of at most 80 chunks' double sums
+        assert torch.linalg.norm(a - b) <= 100 * 80 * 2.0 ** -53 * torch.linalg.norm(a)
+    for a, b in zip(results[0][1], results[1][1]):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("prec,n,cap", [("fp64", 9620, 6 << 20), ("fp64", 22000, 1 << 20), ("mixed_ds", 65536, 4 << 20),
                                         ("mixed", 16384, 0)])
