@@ -207,9 +207,11 @@ bool tuned_for(const nb_ctx* c, int64_t n) {
 }
 
 // The small-system kernel (k_forces_small) for every count of such a system,
-// host and device alike.
-bool takes_small(const nb_ctx* c, int64_t n, int64_t n_act) {
-  return !c->have_forced && !c->split_atomic && nb::small_direct(n, n_act) && !tuned_for(c, n);
+// host and device alike.  `atomic`: a call that adds the j-split's partial
+// sums with atomics (nb_set_split_sum mode 1: nbody_forces and
+// nbody_forces_ij only) takes the split shapes.
+bool takes_small(const nb_ctx* c, int64_t n, int64_t n_act, bool atomic) {
+  return !c->have_forced && !atomic && nb::small_direct(n, n_act) && !tuned_for(c, n);
 }
 
 // The active-count regimes of this context and precision: the tuned table
@@ -255,9 +257,9 @@ Launch regime_of(const nb_ctx* c, int64_t n, int64_t n_act) {
 
 // Resolve K, L and the work-item target for an active count; S is then the
 // saturation rule unless a forced configuration fixes it.
-Launch choose(const nb_ctx* c, int64_t n, int64_t n_act) {
+Launch choose(const nb_ctx* c, int64_t n, int64_t n_act, bool atomic) {
   Launch cfg;
-  if (takes_small(c, n, n_act)) {
+  if (takes_small(c, n, n_act, atomic)) {
     cfg = Launch{1, 16, 1, 0};
     cfg.small = true;
     return cfg;
@@ -284,7 +286,7 @@ constexpr size_t kPartRow = 7 * sizeof(double);
 // call away that a smaller split serves (the sums then differ only in their
 // order).  A forced launch keeps its S and is refused.
 Launch choose_capped(const nb_ctx* c, int64_t n, int64_t n_act) {
-  Launch cfg = choose(c, n, n_act);
+  Launch cfg = choose(c, n, n_act, c->split_atomic);
   if (cfg.S > 1 && !c->have_forced && !c->split_atomic && (size_t)cfg.S * kPartRow * n_act > c->ws_bytes) {
     const size_t fit = workspace_room(c) / (kPartRow * (size_t)n_act);
     if (fit < (size_t)cfg.S) cfg.S = fit >= 2 ? (int)fit : 1;
@@ -308,7 +310,7 @@ Launch make_shape(int K, int L, int S, int items, int T, int WG) {
 Launch choose_batch(const nb_ctx* c, int kind, int64_t key, int64_t n_total, int64_t mean_size) {
   for (auto it = c->batch_table.rbegin(); it != c->batch_table.rend(); ++it)
     if (it->prec == c->prec && it->kind == kind && key >= it->key_min && key <= it->key_max) return it->cfg;
-  Launch cfg = choose(c, n_total, mean_size);
+  Launch cfg = choose(c, n_total, mean_size, false);
   cfg.small = false;
   cfg.K = 1;
   if (cfg.L != 1 && cfg.L != 4 && cfg.L != 16 && cfg.L != 64)
@@ -576,7 +578,7 @@ int nb_set_launch(nb_ctx* c, int K, int L, int S, int T, int WG) {
 
 int nb_get_launch(nb_ctx* c, int64_t N, int64_t n_active, int* K, int* L, int* S, int* T, int* WG) {
   if (!c || !K || !L || !S || N < 1 || n_active < 0) return NB_EINVAL;
-  const Launch cfg = choose(c, N, n_active < 1 ? 1 : n_active);
+  const Launch cfg = choose(c, N, n_active < 1 ? 1 : n_active, c->split_atomic);
   *K = cfg.K; *L = cfg.L; *S = cfg.S;
   if (T) *T = cfg.T;
   if (WG) *WG = cfg.WG;
@@ -681,8 +683,9 @@ int nbody_forces_noalloc(nb_ctx* c, const double* pos, const double* vel, const 
   hipError_t se = hipSuccess;
   unsigned char* base = static_cast<unsigned char*>(scratch_address(c->device, &se));
   if (!base) return hip_fail(c, se, "address of the fixed scratch");
-  // the launch nbody_forces would take, so the two give identical results
-  Launch cfg = choose(c, N, n_active);
+  // the launch nbody_forces would take with sums in fixed order, so the two
+  // give identical results
+  Launch cfg = choose(c, N, n_active, false);
   const size_t row_bytes = kPartRow * (size_t)n_active;  // one j-chunk's partial sums
   auto part_bytes = [&](int S) { return S > 1 ? align256((size_t)S * row_bytes) : (size_t)0; };
   const size_t rec = cfg.L <= 0 ? nb::mirror_bytes(c->prec, N) : 0;
@@ -780,7 +783,7 @@ int devcount_forces(nb_ctx* c, const double* pos, const double* vel, const doubl
   if (!n_active_dev) return fail(c, NB_EINVAL, "n_active_dev is null%s");
   if (max_active == 0) return NB_OK;
   const bool mask = kernel_mask(c->prec, eps2);
-  if (takes_small(c, N, max_active)) {
+  if (takes_small(c, N, max_active, false)) {
     nb::ForceArgs a{};
     a.pos = pos; a.vel = vel; a.mass = mass; a.n = N;
     a.active = active; a.n_active = max_active; a.n_active_dev = n_active_dev;

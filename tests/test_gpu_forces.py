@@ -484,3 +484,40 @@ def test_atomic_split_sum_equals_the_fixed_order_sum(nb, prec, launch):
     c.set_split_sum(0)
     c.sync()
     c.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("n", [300, 4096, 5000])
+def test_atomic_split_sum_leaves_the_other_calls_alone(nb, prec, n):
+    # device-count calls, block steps and nbody_forces_noalloc add in fixed
+    # order whatever the mode: the same launches, so the same bits
+    import torch
+    from paper_1409_5474_amd.integrator import BlockIntegrator
+    p = synth.plummer(n, 23)
+    P, V, M = _dev(p.pos), _dev(p.vel), _dev(p.mass)
+    act = _dev(np.arange(0, n, 3, dtype=np.int32))
+    na = act.shape[0]
+    runs = []
+    for mode in (0, 1):
+        c = nb.Context(0, prec)
+        c.set_split_sum(mode)
+        new = lambda: (torch.zeros((n, 3), dtype=torch.float64, device="cuda"),
+                       torch.zeros((n, 3), dtype=torch.float64, device="cuda"),
+                       torch.zeros(n, dtype=torch.float64, device="cuda"))
+        fixed = [x[:na] for x in new()]
+        c.forces_noalloc(P, V, M, act, 1e-3, *fixed)
+        dev = new()
+        full = torch.zeros(n, dtype=torch.int32, device="cuda")
+        full[:na] = act
+        c.forces_devcount(P, V, M, full, torch.tensor([na], dtype=torch.int32, device="cuda"), n, 1e-3, *dev)
+        # (the integrator's own start-up forces are nbody_forces: mode 0)
+        c.set_split_sum(0)
+        bi = BlockIntegrator(c, P.clone(), V.clone(), M, 1e-3)
+        c.set_split_sum(mode)
+        for _ in range(4):
+            bi.step()
+        c.sync()
+        runs.append([*fixed, *dev, bi.pos, bi.vel, bi.acc, bi.jerk, bi.t_tick, bi.level])
+        c.close()
+    for a, b in zip(*runs):
+        assert torch.equal(a, b)
