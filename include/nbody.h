@@ -37,7 +37,7 @@
  *    device: they share the context's work-queue counters and workspace, so
  *    every call -- and every replay of a graph that captured calls -- goes to
  *    one stream, or to streams ordered with events.  Overlapping calls give
- *    wrong results; nb_sync detects the counters they leave behind.
+ *    wrong results; nb_sync detects what they leave behind.
  *  - Index arrays are int32; an index outside [0, N) is an error only where
  *    stated (device-resident indices cannot be checked without a copy).
  *  - The context owns only its launch table, a workspace for j-split
@@ -108,9 +108,8 @@ int nb_set_stream(nb_ctx *ctx, void *hip_stream);
  * memory, so no call has to copy active_idx to the host.  Returns
  * NB_EINVAL (message in nb_last_error) once for any such entries and clears
  * the bit; NB_OK otherwise; NB_EDEVICE on a failed synchronisation.
- * It also checks the context's work-queue counters, which every force
- * launch leaves at zero (launches of no more work items than workgroups do
- * not use them): non-zero counters mean that calls overlapped on the
+ * It also checks the context's work-queue words, which every force call
+ * leaves at zero: non-zero words mean that calls overlapped on the
  * device (see the conventions above).  They are then cleared, so later calls
  * are correct again, and NB_EINVAL reports that results since the last
  * nb_sync cannot be trusted. */

@@ -659,6 +659,8 @@ __device__ __forceinline__ void run_items(typename P::template JTileT<T>& tile, 
   const int64_t n_iblk = (n_act + IB - 1) / IB;
   const int64_t items = n_iblk * S;
   const Chunks cut(a.n, S, T);
+  const bool flight = !ATOMIC && (a.n_active_dev || S > 1);  // k_reduce or k_reduce_correct follows
+  if (flight) flight_begin_beside(a.wq, items);
   if (!queue_member(items)) return;
   int64_t w = queue_first(a.wq, items);
   while (w < items) {
@@ -671,7 +673,7 @@ __device__ __forceinline__ void run_items(typename P::template JTileT<T>& tile, 
                                 a.err);
     w = queue_next(a.wq, slot, items, w + gridDim.x);
   }
-  queue_done(a.wq, items);
+  queue_done(a.wq, items, flight);
 }
 
 // One shape (those outside the families below), with its j-tile length T
@@ -741,11 +743,17 @@ __global__ __launch_bounds__(kWG) void k_forces_fam(ForceArgs a) {
 
 // Fixed-order sum of the S partial blocks, self-term removal, output.
 // With a device count and s_dev set, one reduce serves every regime of the
-// call: the regime that worked left its S in *s_dev.
+// call: the regime that worked left its S in *s_dev.  Block 0 takes no
+// outputs: it steps the in-flight word back (a negative count started no force
+// kernel).
 template <class P>
 __global__ __launch_bounds__(256) void k_reduce(ForceArgs a, int S_host, int IB) {
   int64_t n_act = a.n_active;
   int S = S_host;
+  if (blockIdx.x == 0) {
+    if (threadIdx.x == 0 && (!a.n_active_dev || *a.n_active_dev >= 0)) flight_end(a.wq);
+    return;
+  }
   if (a.n_active_dev) {
     const int64_t d = *a.n_active_dev;
     if (a.s_dev) {
@@ -765,8 +773,8 @@ __global__ __launch_bounds__(256) void k_reduce(ForceArgs a, int S_host, int IB)
   const int g = chunk_lanes(S);
   const int lg = __builtin_ctz(g);
   const int lane = threadIdx.x & (g - 1);
-  for (int64_t idx = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> lg; idx < total;
-       idx += ((int64_t)gridDim.x * blockDim.x) >> lg) {
+  for (int64_t idx = ((int64_t)(blockIdx.x - 1) * blockDim.x + threadIdx.x) >> lg; idx < total;
+       idx += ((int64_t)(gridDim.x - 1) * blockDim.x) >> lg) {
     const int64_t c = idx / n_act;
     const int64_t k = idx - c * n_act;
     const double s = sum_blocks(a.part + c * n_act + k, 7 * n_act, S, lane, g);
@@ -803,6 +811,8 @@ __global__ __launch_bounds__(kReduceCorrectThreads) void k_reduce_correct(ForceA
     const int64_t d = *a.n_active_dev;
     n_act = d < n_act ? (d < 0 ? 0 : d) : n_act;
     S = a.s_dev ? *a.s_dev : 1;
+    // a wavefront that is dealt rows late steps the in-flight word back
+    if (blockIdx.x == 0 && threadIdx.x == kReduceCorrectThreads - 64 && d >= 0) flight_end(a.wq);
   }
   if (s.step_dev && n_act > 0 && blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(s.step_dev, 1ull);
   const bool self_on = P::eps(a.eps2) > 0;
@@ -915,6 +925,8 @@ __global__ __launch_bounds__(64 * W) void k_forces_small(ForceArgs a, StepArgs s
     const int64_t d = *a.n_active_dev;
     n_act = d < n_act ? (d < 0 ? 0 : d) : n_act;
   }
+  // the scheduler stepped the in-flight word; a block beyond the rows steps it back
+  if (STEP && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) flight_end(a.wq);
   if (STEP && s.step_dev && n_act > 0 && blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(s.step_dev, 1ull);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int slot = lane / kSmallL, sub = lane % kSmallL;
@@ -1131,6 +1143,8 @@ __global__ __launch_bounds__(WG, (SjWaves<P, K>::value)) void k_forces_sj(ForceA
   const int64_t items = n_iblk * S;
   const Chunks cut(a.n, S);
   __shared__ unsigned int slot;
+  const bool flight = a.n_active_dev || S > 1;
+  if (flight) flight_begin_beside(a.wq, items);
   if (!queue_member(items)) return;
   int64_t w = queue_first(a.wq, items);
   while (w < items) {
@@ -1142,7 +1156,7 @@ __global__ __launch_bounds__(WG, (SjWaves<P, K>::value)) void k_forces_sj(ForceA
                                 a.acc, a.jerk, a.pot, a.part + chunk * 7 * n_act, a.row_lo, a.row_hi, a.err);
     w = queue_next<true>(a.wq, slot, items, w + gridDim.x);
   }
-  queue_done(a.wq, items);
+  queue_done(a.wq, items, flight);
 }
 
 
@@ -1270,6 +1284,8 @@ __global__ __launch_bounds__(kWG, (K == 2 ? 5 : 1)) void k_forces_hy(ForceArgs a
   const int64_t items = n_iblk * S;
   const Chunks cut(a.n, S);
   __shared__ unsigned int slot;
+  const bool flight = a.n_active_dev || S > 1;
+  if (flight) flight_begin_beside(a.wq, items);
   if (!queue_member(items)) return;
   int64_t w = queue_first(a.wq, items);
   while (w < items) {
@@ -1281,7 +1297,7 @@ __global__ __launch_bounds__(kWG, (K == 2 ? 5 : 1)) void k_forces_hy(ForceArgs a
                        a.acc, a.jerk, a.pot, a.part + chunk * 7 * n_act, a.row_lo, a.row_hi, a.err);
     w = queue_next(a.wq, slot, items, w + gridDim.x);
   }
-  queue_done(a.wq, items);
+  queue_done(a.wq, items, flight);
 }
 
 // ---------------------------------------------------------------- batch ----
@@ -1761,6 +1777,9 @@ SjFn<P, MASK> pick_sj(int K, int WG = kWG) {
   return nullptr;
 }
 
+// One workgroup more than the items, for the in-flight word, where a reduce follows.
+int beside(const ForceArgs& a) { return a.S > 1 ? 1 : 0; }
+
 template <class P, bool MASK>
 hipError_t launch_sj_p(int K, int WG, const ForceArgs& a, hipStream_t st, int grid_override, int max_grid) {
   SjFn<P, MASK> fn = pick_sj<P, MASK>(K, WG);
@@ -1771,7 +1790,7 @@ hipError_t launch_sj_p(int K, int WG, const ForceArgs& a, hipStream_t st, int gr
   hipLaunchKernelGGL(k_mirror<P>, dim3((int)mg), dim3(256), 0, st, a.pos, a.vel, a.mass, a.n, rec);
   Launch shape{K, 1, a.S};
   shape.WG = WG;
-  int grid = grid_override > 0 ? grid_override : items_for(shape, a.n_active, a.S);
+  int grid = grid_override > 0 ? grid_override : items_for(shape, a.n_active, a.S) + beside(a);
   if (max_grid > 0 && grid > max_grid) grid = max_grid;
   if (grid <= 0) return hipGetLastError();
   hipLaunchKernelGGL(fn, dim3(grid), dim3(WG), 0, st, a, rec);
@@ -1907,7 +1926,7 @@ hipError_t launch_forces(int prec, const Launch& cfg_in, bool mask, const ForceA
     int64_t mg = (a.n + 256) / 256;
     if (mg > 8192) mg = 8192;
     hipLaunchKernelGGL(k_mirror<Mixed>, dim3((int)mg), dim3(256), 0, st, a.pos, a.vel, a.mass, a.n, rec);
-    int grid = grid_override > 0 ? grid_override : items_for(Launch{K, 1, a.S}, a.n_active, a.S);
+    int grid = grid_override > 0 ? grid_override : items_for(Launch{K, 1, a.S}, a.n_active, a.S) + beside(a);
     if (max_grid > 0 && grid > max_grid) grid = max_grid;
     if (grid <= 0) return hipGetLastError();
     hipLaunchKernelGGL(fn, dim3(grid), dim3(kWG), 0, st, a, rec);
@@ -1934,7 +1953,7 @@ hipError_t launch_forces(int prec, const Launch& cfg_in, bool mask, const ForceA
   if (!fn) return hipErrorInvalidValue;
   Launch shape = cfg;
   shape.S = a.S;
-  int grid = grid_override > 0 ? grid_override : items_for(shape, a.n_active, a.S);
+  int grid = grid_override > 0 ? grid_override : items_for(shape, a.n_active, a.S) + beside(a);
   if (max_grid > 0 && grid > max_grid) grid = max_grid;
   if (grid <= 0) return hipSuccess;
   if (a.n_sub == 0 && a.shape == 0) {
@@ -1960,6 +1979,7 @@ hipError_t launch_forces_small(int prec, bool mask, const ForceArgs& a, const St
   int64_t grid = (a.n_active + kSmallRows - 1) / kSmallRows;
   if (grid > 4096) grid = 4096;
   if (grid < 1) grid = 1;
+  if (s) ++grid;  // a block for the in-flight word
   const bool wide = a.n > kSmallNarrow;
 #define NB_SMALL(P)                                                                                   \
   (wide ? (mask ? launch_small_p<P, true, 8>(a, s, (int)grid, st) : launch_small_p<P, false, 8>(a, s, (int)grid, st)) \
@@ -2040,6 +2060,7 @@ hipError_t launch_reduce_ib(int prec, const ForceArgs& a, int S, int IB, hipStre
   int64_t grid = (threads + 255) / 256;
   if (grid > 4096) grid = 4096;
   if (grid < 1) grid = 1;
+  ++grid;  // block 0: the in-flight word
   if (prec == NB_PREC_FP64)
     hipLaunchKernelGGL(k_reduce<F64>, dim3((unsigned)grid), dim3(256), 0, st, a, S, IB);
   else if (prec == NB_PREC_MIXED_DS)

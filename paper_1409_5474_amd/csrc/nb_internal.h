@@ -17,7 +17,7 @@ constexpr int kWG = 256;    // threads per workgroup of the force kernels unless
 constexpr int kBatchSjWG = 128;
 constexpr int kTile = 256;  // j-particles staged in LDS per tile
 constexpr int kQueueLine = 64;       // words from one counter of a work queue to the next (256 bytes)
-constexpr int kWorkQueueWords = 18 * kQueueLine;  // words of a context's work queue (17 counters, the error word)
+constexpr int kWorkQueueWords = 18 * kQueueLine;  // words of a context's work queue (17 counters, the in-flight and the error word)
 constexpr int kMaxSubRegimes = 16;   // active-count regimes one device-count launch can serve
 constexpr int kErrorWord = kWorkQueueWords - 1;  // word of that buffer holding the device error bits
 constexpr unsigned int kErrActiveRange = 1u;     // an active_idx entry outside its valid range was skipped
@@ -302,10 +302,11 @@ struct PredictArgs {
   double* pos_p;
   double* vel_p;
 };
+// wq (one-launch scheduler only): its in-flight word is stepped.
 hipError_t launch_schedule(const int64_t* t_tick, const int32_t* level, int64_t n, int max_level,
                            int32_t* active, int64_t* sched, int64_t* block_min, int32_t* block_cnt,
                            int32_t* n_active32, int64_t t_stop, const int64_t* t_stop_dev, hipStream_t st,
-                           const PredictArgs* pred = nullptr);
+                           const PredictArgs* pred = nullptr, unsigned int* wq = nullptr);
 int schedule_blocks(int64_t n);
 hipError_t launch_energy(const double* pos, const double* vel, const double* mass, const double* pot,
                          int64_t n, double* part, double* out, hipStream_t st);

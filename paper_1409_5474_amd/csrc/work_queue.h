@@ -25,16 +25,34 @@
 //
 // Lines: [0, kXcd) the range counters (items taken beyond the members' first
 // ones), [kXcd, 2 kXcd) the finished members of each XCD, 2 kXcd the XCDs
-// whose members have all finished.  All are zero before a launch, and the
-// last member to finish sets them back to zero.  Without a queue (wq null)
-// the grid strides over the items in the same order.
+// whose members have all finished, 2 kXcd + 1 the in-flight word.  All are
+// zero before a launch, and the last member to finish sets the counters back
+// to zero.  Without a queue (wq null) the grid strides over the items in the
+// same order.
+//
+// The in-flight word lets nb_sync see calls that overlapped on the device also
+// where their launches touch no counter.  What such calls share is written by
+// one kernel and read by the next (the partial sums of a j-split, a small
+// block step's active count), so the first steps the word (wrapping increment
+// of limit 1: 0 becomes 1, anything else 0) and the last steps it back
+// (wrapping decrement: 1 becomes 0, 0 becomes kOverlapped, n becomes n - 1).
+// One call after another leaves 0.  Two first steps without a step back
+// between them leave a value that no later sequence of calls brings to 0: the
+// step back that closes a stretch of overlapping calls finds the word at 0 or
+// far above 1, and from there a call leads to 0 and then to kOverlapped.
+// Neither step returns a value, and both are made early, by workgroups or
+// wavefronts without other work: a wavefront's later loads, and the end of the
+// kernel, wait for an atomic's completion (made by workgroup 0 of a small
+// system's force kernel they cost a block step 0.6 us, MI355X; as they are,
+// 0.1 us).
 #pragma once
 #include "nb_internal.h"
 
 namespace nb {
 
 constexpr int kXcd = 8;
-static_assert((2 * kXcd + 1) * kQueueLine <= kErrorWord, "work queue larger than its buffer");
+constexpr unsigned int kOverlapped = 0xffff0000u;
+static_assert((2 * kXcd + 1) * kQueueLine < kErrorWord, "work queue larger than its buffer");
 
 __device__ __forceinline__ unsigned int* queue_range(unsigned int* wq, int x) { return wq + x * kQueueLine; }
 
@@ -49,6 +67,23 @@ __device__ __forceinline__ int64_t queue_members(int64_t items) {
   return items < (int64_t)gridDim.x ? items : (int64_t)gridDim.x;
 }
 __device__ __forceinline__ bool queue_member(int64_t items) { return (int64_t)blockIdx.x < items; }
+
+// The steps of the in-flight word, by one thread of a launch.
+__device__ __forceinline__ void flight_begin(unsigned int* wq) {
+  if (wq) (void)atomicInc(queue_range(wq, 2 * kXcd + 1), 1u);
+}
+__device__ __forceinline__ void flight_end(unsigned int* wq) {
+  if (wq) (void)atomicDec(queue_range(wq, 2 * kXcd + 1), kOverlapped);
+}
+// The first step for a launch that a second kernel follows, by the first
+// workgroup without an item; with as many items as workgroups by workgroup 0,
+// and with more by the first one of XCD 0 to finish, which the counters tell
+// (queue_done).
+__device__ __forceinline__ void flight_begin_beside(unsigned int* wq, int64_t items) {
+  if (items <= (int64_t)gridDim.x && (int64_t)blockIdx.x == (items < (int64_t)gridDim.x ? items : 0) &&
+      threadIdx.x == 0)
+    flight_begin(wq);
+}
 
 // The first item of a member (members <= items, so range x has an item for
 // each of its members).
@@ -128,12 +163,14 @@ __device__ __forceinline__ int64_t queue_next(unsigned int* wq, unsigned int& sl
 
 // Every member calls queue_done once, after its last queue_next; the last
 // member of the last XCD resets the queue (each member's own takes are
-// complete by then).
-__device__ __forceinline__ void queue_done(unsigned int* wq, int64_t items) {
+// complete by then).  flight: the launch steps the in-flight word.
+__device__ __forceinline__ void queue_done(unsigned int* wq, int64_t items, bool flight = false) {
   if (!wq || items <= (int64_t)gridDim.x || threadIdx.x != 0) return;
   const int64_t members = gridDim.x;  // fewer than the items
   const int x = blockIdx.x % kXcd;
-  if (atomicAdd(queue_range(wq, kXcd + x), 1u) != range_len(members, x) - 1) return;
+  const unsigned int before = atomicAdd(queue_range(wq, kXcd + x), 1u);
+  if (flight && x == 0 && before == 0) flight_begin(wq);
+  if (before != range_len(members, x) - 1) return;
   const unsigned int xcds = members < kXcd ? (unsigned int)members : kXcd;
   if (atomicAdd(queue_range(wq, 2 * kXcd), 1u) != xcds - 1) return;
   for (int k = 0; k <= 2 * kXcd; ++k) atomicExch(queue_range(wq, k), 0u);
