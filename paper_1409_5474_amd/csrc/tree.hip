@@ -243,6 +243,14 @@ __device__ __forceinline__ void set_geometry(TreeCell& c, int level, const int32
 }
 
 constexpr int kCtrWords = 256;      // the walk's counters (kCtrLine words per XCD)
+// What the caller's counts are made of, in one block of memory so that one
+// copy brings it to the host: the walk's counters, where each level's cells
+// start (and the last ends), and the number of groups.
+struct Counts {
+  unsigned long long ctr[kCtrWords];
+  int32_t lvl[kLevels + 1];
+  int32_t ngroups;
+};
 constexpr int kRows = kLevels + 1;  // per-tile counts: cells starting on each level, then groups
 constexpr int kMaxWindow = 256;     // n_crit + 1 up to which the window maximum runs in LDS
 
@@ -1511,7 +1519,7 @@ struct Alloc {
 
 enum Slot {
   S_BOXPART, S_BOX, S_KEYS, S_KEYS2, S_IDX, S_IDX2, S_PART, S_MOM, S_SPAN, S_CELLS, S_CNT,
-  S_GB, S_GE, S_GN, S_GBOX, S_STACK, S_CTR, S_LVL, S_HIST, S_TILE
+  S_GB, S_GE, S_GBOX, S_STACK, S_COUNTS, S_HIST, S_TILE
 };
 
 // Sort (keys, idx) by the low `bits` bits of the keys; returns the buffers
@@ -1536,17 +1544,6 @@ hipError_t radix_sort(Alloc& al, uint64_t* keys, int32_t* idx, uint64_t* keys2, 
   *keys_out = ka;
   *idx_out = va;
   return hipGetLastError();
-}
-
-// the entries at `pos`... of a device array, read to the host (synchronises)
-template <class T>
-hipError_t read_entries(TreeScratch& s, hipStream_t st, const T* a, int64_t count, T* out) {
-  T* h = static_cast<T*>(s.host);
-  hipError_t e = hipMemcpyAsync(h, a, count * sizeof(T), hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
-  if (e == hipSuccess)
-    for (int64_t k = 0; k < count; ++k) out[k] = h[k];
-  return e;
 }
 
 }  // namespace
@@ -1612,7 +1609,7 @@ hipError_t tree_forces_run(TreeScratch& s, hipStream_t st, const double* pos, co
                            double* pot, TreeStats* stats, bool capturing, unsigned int* wq, unsigned int* err,
                            const char** msg) {
   *msg = "";
-  if (!capturing && !s.host) NB_TRY(hipHostMalloc(&s.host, 64 * sizeof(int64_t), hipHostMallocDefault));
+  if (!capturing && !s.host) NB_TRY(hipHostMalloc(&s.host, sizeof(Counts), hipHostMallocDefault));
   Alloc al{s, st, capturing};
   auto need = [&](void* p) -> hipError_t { return p ? hipSuccess : (al.err != hipSuccess ? al.err : hipErrorOutOfMemory); };
 
@@ -1637,15 +1634,15 @@ hipError_t tree_forces_run(TreeScratch& s, hipStream_t st, const double* pos, co
   uint16_t* span = al.get<uint16_t>(S_SPAN, n);
   const int32_t ntile = (n + kTB - 1) / kTB;
   int32_t* cnt = al.get<int32_t>(S_CNT, (int64_t)kRows * ntile + kRows);
-  int32_t* lvl = al.get<int32_t>(S_LVL, kLevels + 1);
   TileMoments* tiles = al.get<TileMoments>(S_TILE, ntile);
   const int32_t nchunk = (n + kGS - 1) / kGS;
   int32_t* gb = al.get<int32_t>(S_GB, n);
   int32_t* ge = al.get<int32_t>(S_GE, n);
-  int32_t* gn = al.get<int32_t>(S_GN, 1);
   double* gbox = al.get<double>(S_GBOX, 6 * (int64_t)n);
-  unsigned long long* ctr = al.get<unsigned long long>(S_CTR, kCtrWords);
-  NB_TRY(need(ctr));
+  Counts* counts = al.get<Counts>(S_COUNTS, 1);
+  NB_TRY(need(counts));
+  unsigned long long* ctr = counts->ctr;  // device addresses
+  int32_t *lvl = counts->lvl, *gn = &counts->ngroups;
   int32_t* total = cnt + (int64_t)kRows * ntile;
   hipLaunchKernelGGL(k_cell_starts, dim3(ntile), dim3(kTB), 0, st, keys_s, idx_s, pos, mass, n, n_crit, box, g_frac,
                      part, span, cnt, ntile, tiles);
@@ -1681,26 +1678,24 @@ hipError_t tree_forces_run(TreeScratch& s, hipStream_t st, const double* pos, co
   NB_TRY(hipGetLastError());
   if (!stats) return hipSuccess;
   // counts for the caller (synchronises)
+  Counts* h = static_cast<Counts*>(s.host);
+  NB_TRY(hipMemcpyAsync(h, counts, sizeof(Counts), hipMemcpyDeviceToHost, st));
+  NB_TRY(hipStreamSynchronize(st));
   unsigned long long c[3] = {0, 0, 0};
   for (int x = 0; x < kXcd; ++x) {
-    unsigned long long cx[3];
-    NB_TRY(read_entries(s, st, ctr + x * kCtrLine, 3, cx));
-    c[0] += cx[0];
-    c[1] += cx[1];
-    c[2] |= cx[2];
+    c[0] += h->ctr[x * kCtrLine];
+    c[1] += h->ctr[x * kCtrLine + 1];
+    c[2] |= h->ctr[x * kCtrLine + 2];
   }
   if (c[2]) {
     *msg = "tree walk stack exceeded its bound";
     return hipErrorInvalidValue;
   }
-  int32_t lv[kLevels + 1], ng = 0;
-  NB_TRY(read_entries(s, st, lvl, kLevels + 1, lv));
-  NB_TRY(read_entries(s, st, gn, 1, &ng));
   int depth = 0;
   for (int l = 0; l < kLevels; ++l)
-    if (lv[l + 1] > lv[l]) depth = l;
-  stats->cells = lv[kLevels];
-  stats->groups = ng;
+    if (h->lvl[l + 1] > h->lvl[l]) depth = l;
+  stats->cells = h->lvl[kLevels];
+  stats->groups = h->ngroups;
   stats->accepted = (int64_t)c[0];
   stats->opened_leaves = (int64_t)c[1];
   stats->depth = depth;

@@ -304,3 +304,28 @@ def test_tree_forces_replay_from_a_graph(ctx):
         ctx.tree_forces(P, M, 1e-4, 0.7)                      # other eager work between replays
     ctx.set_stream(None)
     ctx.sync()
+
+
+def test_counts_come_in_one_round_trip(ctx):
+    # the counts of a call cost about one copy and one wait, not one for each
+    # of the walk's counter lines: less than four reads of a small tensor
+    import time
+    import torch
+    p = synth.plummer(3000, 9)
+    x, m = T(p.pos), T(p.mass)
+    small = torch.zeros(300, dtype=torch.int64, device="cuda")
+
+    def best(fn):
+        t = []
+        for _ in range(40):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            fn()
+            torch.cuda.synchronize()
+            t.append(time.perf_counter() - t0)
+        return min(t)
+
+    with_counts = best(lambda: ctx.tree_forces(x, m, 1e-3, 0.5))
+    without = best(lambda: ctx.tree_forces(x, m, 1e-3, 0.5, stats=False))
+    read = best(lambda: small.cpu())
+    assert with_counts - without < 4 * read, (with_counts, without, read)
