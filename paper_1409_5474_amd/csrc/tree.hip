@@ -354,9 +354,11 @@ __device__ __forceinline__ Piece group_of(int lane, int m, const double* x, doub
   return p;
 }
 
-// Mass, centre of mass and traceless quadrupole of a tile's particles.
+// Mass, centre of mass X and traceless quadrupole about it of a tile's
+// particles.  Without a positive mass (masses of both signs) X is the tile's
+// first particle instead and D the first moment about it (otherwise zero).
 struct TileMoments {
-  double M, X[3], Q[6];
+  double M, X[3], Q[6], D[3];
 };
 
 template <int G>
@@ -375,6 +377,17 @@ __device__ __forceinline__ void add_quad(double* Q, double m, double e0, double 
   Q[3] += m * (3.0 * (e0 * e1));
   Q[4] += m * (3.0 * (e0 * e2));
   Q[5] += m * (3.0 * (e1 * e2));
+}
+
+// Q += what a first moment D about X adds to the quadrupole about X - e
+__device__ __forceinline__ void add_dipole(double* Q, const double* D, double e0, double e1, double e2) {
+  const double de = 2.0 * (D[0] * e0 + D[1] * e1 + D[2] * e2);
+  Q[0] += 6.0 * D[0] * e0 - de;
+  Q[1] += 6.0 * D[1] * e1 - de;
+  Q[2] += 6.0 * D[2] * e2 - de;
+  Q[3] += 3.0 * (D[0] * e1 + D[1] * e0);
+  Q[4] += 3.0 * (D[0] * e2 + D[2] * e0);
+  Q[5] += 3.0 * (D[1] * e2 + D[2] * e1);
 }
 
 // Sums of N values over the block's threads, in a fixed order; red is free
@@ -419,8 +432,16 @@ __global__ __launch_bounds__(kTB) void k_cell_starts(const uint64_t* __restrict_
   {
     double v[4] = {pm, pm * x[0], pm * x[1], pm * x[2]}, q[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     block_fold<4>(v, red[0]);
-    double X[3];
-    for (int k = 0; k < 3; ++k) X[k] = v[0] > 0.0 ? v[1 + k] / v[0] : 0.0;
+    double X[3], D[3] = {0.0, 0.0, 0.0};
+    if (v[0] > 0.0) {
+      for (int k = 0; k < 3; ++k) X[k] = v[1 + k] / v[0];
+    } else {
+      const int64_t o = idx[tile0];
+      for (int k = 0; k < 3; ++k) {
+        X[k] = pos[3 * o + k];
+        D[k] = v[1 + k] - v[0] * X[k];
+      }
+    }
     if (valid) add_quad(q, pm, x[0] - X[0], x[1] - X[1], x[2] - X[2]);
     block_fold<6>(q, red[1]);
     if (t == 0) {
@@ -428,6 +449,7 @@ __global__ __launch_bounds__(kTB) void k_cell_starts(const uint64_t* __restrict_
       tm.M = v[0];
       for (int k = 0; k < 3; ++k) tm.X[k] = X[k];
       for (int k = 0; k < 6; ++k) tm.Q[k] = q[k];
+      for (int k = 0; k < 3; ++k) tm.D[k] = D[k];
     }
   }
   int e = -1;
@@ -642,6 +664,8 @@ __device__ __forceinline__ void moments_of(const TreeCell& c, CellMom* __restric
   for (int32_t u = tm0 + t; u < tm1; u += G) {
     M += tiles[u].M;
     for (int k = 0; k < 3; ++k) S[k] += tiles[u].M * tiles[u].X[k];
+    if (!(tiles[u].M > 0.0))
+      for (int k = 0; k < 3; ++k) S[k] += tiles[u].D[k];
   }
   M = fold_lanes<G>(M);
   for (int k = 0; k < 3; ++k) {
@@ -654,7 +678,9 @@ __device__ __forceinline__ void moments_of(const TreeCell& c, CellMom* __restric
   }
   for (int32_t u = tm0 + t; u < tm1; u += G) {
     for (int k = 0; k < 6; ++k) Q[k] += tiles[u].Q[k];
-    add_quad(Q, tiles[u].M, tiles[u].X[0] - X[0], tiles[u].X[1] - X[1], tiles[u].X[2] - X[2]);
+    const double e[3] = {tiles[u].X[0] - X[0], tiles[u].X[1] - X[1], tiles[u].X[2] - X[2]};
+    add_quad(Q, tiles[u].M, e[0], e[1], e[2]);
+    if (!(tiles[u].M > 0.0)) add_dipole(Q, tiles[u].D, e[0], e[1], e[2]);
   }
   for (int k = 0; k < 6; ++k) Q[k] = fold_lanes<G>(Q[k]);
   if (t != 0) return;

@@ -329,3 +329,24 @@ def test_counts_come_in_one_round_trip(ctx):
     without = best(lambda: ctx.tree_forces(x, m, 1e-3, 0.5, stats=False))
     read = best(lambda: small.cpu())
     assert with_counts - without < 4 * read, (with_counts, without, read)
+
+
+def test_masses_of_both_signs(ctx):
+    # clusters of negative, of positive and of mixed masses, far enough apart
+    # that cells holding whole tiles of the curve are accepted: as near to the
+    # direct sum as the oracle's tree, whose cells without a positive mass
+    # expand about the cube centre too (their dipole is left out by both)
+    import torch
+    rng = np.random.default_rng(40)
+    n1 = 2000
+    centres = np.array([[0.0, 0.0, 0.0], [9.0, 1.0, 0.5], [3.0, 8.0, -4.0]])
+    pos = np.concatenate([c + rng.uniform(-0.5, 0.5, (n1, 3)) for c in centres])
+    third = np.where(pos[2 * n1:, 0] < 3.0, -0.4, 1.0)
+    mass = np.concatenate([np.full(n1, -1.0), np.full(n1, 1.0), third]) * rng.uniform(0.5, 1.5, 3 * n1) / n1
+    acc, pot, _ = _gpu(ctx, pos, mass, 1e-3, 0.6, 16)
+    ra, rp, _, _ = _oracle(pos, mass, 1e-3, 0.6, 16)
+    act = T(np.arange(3 * n1, dtype=np.int32))
+    x = T(pos)
+    a, _, w = ctx.forces(x, torch.zeros_like(x), T(mass), act, 1e-3)
+    for got, ref, exact in ((acc, ra, a.cpu().numpy()), (pot, rp, w.cpu().numpy())):
+        assert np.linalg.norm(got - exact) <= 2.0 * np.linalg.norm(ref - exact)
