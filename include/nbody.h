@@ -164,8 +164,9 @@ int nb_get_launch(nb_ctx *ctx, int64_t N, int64_t n_active, int *K, int *L, int 
  * share out over the compute units more evenly, at most one j-tile per
  * subset.  The same entry drives host-count and
  * device-count launches, so both split the work identically.  Later
- * entries take precedence on their range.  Used by the autotuner front end
- * to load its cache. */
+ * entries take precedence on their range.  An entry with n_min <= 4096
+ * switches the small-system launch off, for every active count, from n_min
+ * particles on.  Used by the autotuner front end to load its cache. */
 int nb_tune_add(nb_ctx *ctx, int precision, int64_t n_min, int64_t act_min, int64_t act_max,
                 int K, int L, int items, int T, int WG);
 /* One entry of the batched kernel's table (nbody_forces_batch and

@@ -23,6 +23,10 @@ apart).
 
     python -m paper_1409_5474_amd.autotune --n 65536 262144 --out tuning.json
 
+Entries tuned on up to 4096 particles hold for such systems only where they
+beat the library's small-system launch at every bucket; otherwise they start
+at N = 4097.
+
 ``load(ctx, path)`` installs a saved table into a context.
 """
 import argparse
@@ -41,6 +45,10 @@ SHAPES = [(1, 1), (1, 4), (1, 16), (1, 64), (1, 256), (2, 1), (2, 4), (2, 16), (
 BUCKETS = [1, 8, 64, 256, 1024, 4096, 16384, 65536, 262144]
 DEFAULT_TABLE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tuning_gfx950.json")
 TILE, WG = 256, 256
+# Up to this many particles a system without a table entry takes one launch of
+# its own (the library's kSmallDirect), which no (K, L) names: any entry that
+# holds for such a system switches it off for every active count.
+SMALL_SYSTEM = 4096
 # Second stage: the j-tile length T and workgroup size WG the library builds
 # besides (256, 256), per (K, L) (see nb_set_launch).
 TILE_WG = {(1, 1): [(128, 256), (128, 128), (64, 64)], (1, 4): [(128, 256), (128, 128), (64, 64)],
@@ -191,6 +199,36 @@ def _merge_runs(choice, times, launch_ms):
             choice[b] = best[2]
 
 
+def _graph_ms(ctx, call, calls=20, replays=8):
+    """Milliseconds of one call, replayed back to back from a graph (short
+    launches issued one by one are timed at the host's rate)."""
+    call()
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    ctx.set_stream(stream)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        for _ in range(calls):
+            call()
+    best = math.inf
+    for _ in range(replays):
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        with torch.cuda.stream(stream):
+            graph.replay()
+        torch.cuda.synchronize()
+        best = min(best, (time.perf_counter() - t0) * 1e3 / calls)
+    ctx.set_stream(None)
+    return best
+
+
+def _small_n_min(n, default_ms, shape_ms):
+    """The smallest N that entries tuned on n <= SMALL_SYSTEM particles should
+    hold for: n when their shapes beat the small-system launch at every bucket,
+    else the first N that does not take it."""
+    return n if all(s < d for d, s in zip(default_ms, shape_ms)) else SMALL_SYSTEM + 1
+
+
 def tune(ctx, n, precisions=("fp64", "mixed", "mixed_ds"), buckets=BUCKETS, seed=2, reps=3, log=print,
          launch_ms=LAUNCH_MS):
     import synth
@@ -243,12 +281,33 @@ def tune(ctx, n, precisions=("fp64", "mixed", "mixed_ds"), buckets=BUCKETS, seed
             log(f"# {prec} N={n} n_active={b}: fastest {_shape_str(sh)} S={v[1]} {v[0]:.5f} ms")
         fastest = [min(t, key=t.get) for t in times]
         choice = _merge_shapes(fastest, times, launch_ms)
+        n_min = n
+        if n <= SMALL_SYSTEM:
+            plain = type(ctx)(dev.index or 0, prec, load_tuning=False)
+            default_ms, shape_ms = [], []
+            for i, b in enumerate(bks):
+                act = torch.from_numpy(np.linspace(0, n - 1, b).astype(np.int32)).to(dev)
+                out = (torch.empty((b, 3), dtype=torch.float64, device=dev),
+                       torch.empty((b, 3), dtype=torch.float64, device=dev),
+                       torch.empty(b, dtype=torch.float64, device=dev))
+                call = lambda: plain.forces(P, V, M, act, eps2, *out)
+                plain.set_launch(0)
+                default_ms.append(_graph_ms(plain, call))
+                K, L, tl, wg = _full(choice[i])
+                plain.set_launch(K, L, best_of[i][choice[i]][1], tl, wg)
+                shape_ms.append(_graph_ms(plain, call))
+            plain.close()
+            n_min = _small_n_min(n, default_ms, shape_ms)
+            log(f"# {prec} N={n}: small-system launch {[round(x, 5) for x in default_ms]} ms, "
+                f"tuned shapes {[round(x, 5) for x in shape_ms]} ms: entries from N = {n_min}")
         for i, (b, (lo, hi)) in enumerate(zip(bks, ranges)):
             K, L, tl, wg = _full(choice[i])
             ms, S, n_iblk = best_of[i][choice[i]]
             items = S * n_iblk if S else 0
-            e = dict(prec=prec, n_min=n, act_min=lo, act_max=hi, K=K, L=L, T=tl, WG=wg, items=items,
+            e = dict(prec=prec, n_min=n_min, act_min=lo, act_max=hi, K=K, L=L, T=tl, WG=wg, items=items,
                      ms=round(ms, 5), rep_n_active=b, gint=round(b * n / ms / 1e6, 2))
+            if n_min != n:
+                e["rep_n"] = n
             if choice[i] != fastest[i]:
                 fK, fL, fT, fW = _full(fastest[i])
                 e["fastest"] = dict(K=fK, L=fL, T=fT, WG=fW, ms=round(times[i][fastest[i]], 5))
@@ -442,7 +501,9 @@ def main():
         args.batch = True
     else:
         for n in sorted(args.n):
-            entries = [e for e in entries if not (e.get("kind", 0) == 0 and e["n_min"] == n)]
+            # an earlier run's entries for this N
+            entries = [e for e in entries if e.get("kind", 0) != 0 or
+                       not (e["n_min"] == n or (e["n_min"] > n and e.get("rep_n") == n))]
             entries += tune(ctx, n, args.prec, buckets=buckets, reps=args.reps, log=say)
             checkpoint()
             print(f"# N={n} done after {time.time() - t0:.0f} s", flush=True)

@@ -139,6 +139,48 @@ def test_shipped_table_covers_every_tuned_workload():
                        if e.get("kind", 0) == 1 and e["prec"] == prec)
 
 
+def test_entries_of_a_small_system_start_above_its_own_launch():
+    # the small-system launch has no (K, L): entries that do not beat it at
+    # every bucket must not switch it off
+    import os
+    import re
+    from paper_1409_5474_amd import autotune as at
+    src = open(os.path.join(os.path.dirname(at.__file__), "csrc", "nb_internal.h")).read()
+    assert int(re.search(r"kSmallDirect = (\d+);", src).group(1)) == at.SMALL_SYSTEM
+    assert at._small_n_min(2048, [9.0, 8.0], [8.0, 7.0]) == 2048
+    assert at._small_n_min(2048, [9.0, 8.0], [8.0, 9.0]) == 4097
+    assert at._small_n_min(2048, [9.0], [9.0]) == 4097
+
+
+@pytest.mark.gpu
+def test_tuning_a_small_system_keeps_its_launch(tmp_path):
+    import torch
+    import paper_1409_5474_amd as nb
+    import synth
+    from paper_1409_5474_amd import autotune as at
+    n = 2048
+    ctx = nb.Context(0, "fp64", load_tuning=False)
+    entries = at.tune(ctx, n, precisions=("fp64",), buckets=[1, 64, 2048], reps=1, log=print)
+    assert len(entries) == 3
+    path = tmp_path / "tuning.json"
+    at.save(entries, str(path))
+    tuned, plain = nb.Context(0, "fp64", load_tuning=False), nb.Context(0, "fp64", load_tuning=False)
+    at.load(tuned, str(path))
+    p = synth.plummer(n, 2)
+    T = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    # all active: the small-system launch takes half the time of any split shape
+    act = T(np.arange(n, dtype=np.int32))
+    out = (torch.empty((n, 3), dtype=torch.float64, device="cuda"), torch.empty((n, 3), dtype=torch.float64, device="cuda"),
+           torch.empty(n, dtype=torch.float64, device="cuda"))
+    args = (T(p.pos), T(p.vel), T(p.mass), act, 2.0 ** -16)
+    ms = [at._graph_ms(c, lambda: c.forces(*args, *out)) for c in (plain, tuned)]
+    assert ms[1] < 1.3 * ms[0], ms
+    for a, b in zip(plain.forces(*args), tuned.forces(*args)):
+        assert torch.equal(a, b)
+    # and the entries serve the systems above it
+    assert tuned.get_launch(5000, 5000) == (entries[2]["K"], entries[2]["L"], tuned.get_launch(5000, 5000)[2])
+
+
 @pytest.mark.gpu
 def test_small_tuning_run_keeps_parity(tmp_path):
     import torch
