@@ -23,6 +23,10 @@ apart).
 
     python -m paper_1409_5474_amd.autotune --n 65536 262144 --out tuning.json
 
+``--rounds`` (``tune_rounds``) instead times every range of active counts on
+two systems with whole numbers of work items per compute unit; the shipped
+table's entries with ``rep_n`` come from it.
+
 Entries tuned on up to 4096 particles hold for such systems only where they
 beat the library's small-system launch at every bucket; otherwise they start
 at N = 4097.
@@ -316,6 +320,133 @@ def tune(ctx, n, precisions=("fp64", "mixed", "mixed_ds"), buckets=BUCKETS, seed
     return entries
 
 
+# Tables in whole rounds: the smallest N of each table and the two systems it
+# is timed on, the work items tried (per compute unit: a unit is busy to the end
+# with its share, so what counts is how many whole items that is), and the
+# active counts at which a new range may start.
+ROUND_TABLES = {4097: (6000, 13000), 16385: (22000, 50000), 65536: (65536, 150000), 262144: (262144, 600000)}
+ROUND_ITEMS = [1, 2, 3, 4, 5, 6, 8, 10, 12, 14, 16, 20, 24, 32, 48, 64, 96]
+ROUND_EDGES = [0, 3, 23, 61, 128, 256, 513, 1024, 2049, 4096, 8193, 16384, 32769, 65536, 131073]
+# all-active counts from here on keep the entry of the table they start from:
+# few, large items win in sustained runs, which one timed call does not show
+ROUND_KEEP = 65536
+PARTIAL_ROWS = 16384 * 256  # S x rows that stay within the fixed scratch (56 bytes a row)
+
+
+def _round_ranges(points, starts=()):
+    """Ranges of active counts: those that start where the present entries do,
+    and others where ROUND_EDGES are a third away from all of them."""
+    lo = sorted({0, *starts} | {c for c in ROUND_EDGES
+                                if all(max(c, b, 1) > 1.35 * max(min(c, b), 1) for b in starts)})
+    lo = [c for c in lo if c < points[-1]]
+    return list(zip(lo, [c - 1 for c in lo[1:]] + [2 ** 31 - 1]))
+
+
+def _round_counts(lo, hi, points):
+    """The (N, active count) a range is timed at: a quarter and three quarters of
+    its way on a logarithmic scale; all particles in the last range."""
+    out = []
+    for n, f in zip(points, (0.25, 0.75)):
+        a, b = max(lo, 1), min(hi, n)
+        if b >= a:
+            out.append((n, n if hi == 2 ** 31 - 1 else max(1, int(round(a * (b / a) ** f)))))
+    return out
+
+
+def _round_pick(times):
+    """The entry of a range from {(K, L, T, items): [ms, ...]}: the smallest
+    geometric mean; a shape of a kernel family (which shares a device-count
+    launch) within 2 %, and of these the fewest partial sums within 0.7 %."""
+    mean = {k: math.exp(sum(map(math.log, v)) / len(v)) for k, v in times.items()}
+    fam = {k: m for k, m in mean.items() if _family((k[0], k[1], k[2], WG))}
+    pool = fam if fam and min(fam.values()) < 1.02 * min(mean.values()) else mean
+    top = 1.007 * min(pool.values())
+    return min((k for k in pool if pool[k] <= top), key=lambda k: (k[3] * (WG // max(k[1], 1)) * k[0], pool[k]))
+
+
+def _round_merge(times, loss=1.015):
+    """Neighbouring ranges share an entry where that costs none of them more than
+    `loss`: [(first, last, entry)]."""
+    mean = lambda r, k: math.exp(sum(map(math.log, times[r][k])) / len(times[r][k]))
+    own = [_round_pick(t) for t in times]
+    out, i = [], 0
+    while i < len(times):
+        j, entry = i, own[i]
+        while j + 1 < len(times):
+            span = range(i, j + 2)
+            fits = [k for k in times[i] if all(k in times[r] and mean(r, k) <= loss * mean(r, own[r]) for r in span)]
+            if not fits:
+                break
+            entry, j = min(fits, key=lambda k: sum(math.log(mean(r, k)) for r in span)), j + 1
+        out.append((i, j, entry))
+        i = j + 1
+    return out
+
+
+def tune_rounds(ctx, n_min, points, old, precisions=("fp64", "mixed", "mixed_ds"), log=print):
+    """Entries from N = n_min on in whole rounds of work items per compute unit.
+    FP64 takes any shape; the mixed policies keep the lane split and the tile of
+    the context's present choice, so that the composition of their float sums
+    stays.  The context holds the table to start from, `old` its entries."""
+    import synth
+    dev = ctx.device
+    cus = torch.cuda.get_device_properties(dev).multi_processor_count
+    put = lambda x: torch.from_numpy(np.ascontiguousarray(x)).to(dev)
+    bodies = {n: synth.plummer(n, 2) for n in points}
+    bodies = {n: (put(p.pos), put(p.vel), put(p.mass)) for n, p in bodies.items()}
+    eps2, entries = 2.0 ** -16, []
+    lanes = lambda K, L, T: (max(L, 1), T if L >= 1 else TILE)
+    for prec in precisions:
+        ctx.set_precision(prec)
+        ranges, times, kept = [], [], []
+        mine = [o for o in old if o.get("kind", 0) == 0 and o["prec"] == prec and o["n_min"] == n_min]
+        for lo, hi in _round_ranges(points, [o["act_min"] for o in mine]):
+            held = [o for o in mine if o["act_min"] <= lo <= o["act_max"]]
+            if min(n_min, lo) >= ROUND_KEEP and held:
+                kept.append(dict(held[-1], act_min=lo, act_max=hi))
+                continue
+            at = _round_counts(lo, hi, points)
+            K0, L0, _, T0, _ = ctx.get_shape(max(at[0][0], n_min), at[0][1])
+            t = {}
+            for n, a in at:
+                act = torch.from_numpy(np.linspace(0, n - 1, a).astype(np.int32)).to(dev)
+                out = (torch.empty((a, 3), dtype=torch.float64, device=dev),
+                       torch.empty((a, 3), dtype=torch.float64, device=dev),
+                       torch.empty(a, dtype=torch.float64, device=dev))
+                done = {}
+                reps = max(2, int(2 ** 33 / (n * a)) if n * a > 2 ** 26 else 20)
+                for K, L in SHAPES:
+                    T = TILE if prec == "fp64" else T0
+                    if (prec != "fp64" and lanes(K, L, T) != lanes(K0, L0, T0)) or (K > 1 and a < 32 * K):
+                        continue
+                    if (T != TILE and (T, WG) not in TILE_WG.get((K, L), [])) or (L <= 0 and L0 > 0):
+                        continue
+                    if prec == "fp64" and L > 4 and n * a > 2 ** 30:
+                        continue
+                    ib = (WG // max(L, 1)) * K
+                    blocks, tiles = -(-a // ib), -(-n // T)
+                    for g in ROUND_ITEMS:
+                        S = max(1, min(tiles, g * cus // blocks))
+                        if g * cus * ib > PARTIAL_ROWS or (g > 4 and blocks > 2 * cus * g):
+                            continue
+                        if (K, L, S) not in done:
+                            done[K, L, S] = ctx.time_forces(K, L, S, *bodies[n], act, eps2, *out, reps=reps, T=T, WG=WG)
+                        t.setdefault((K, L, T, g * cus), []).append(done[K, L, S])
+            t = {k: v for k, v in t.items() if len(v) == len(at)}
+            ranges.append((lo, hi, at))
+            times.append(t)
+            best = _round_pick(t)
+            log(f"# {prec} N >= {n_min}, {lo} to {hi} active, timed at {at}: {best} {[round(x, 5) for x in t[best]]} ms")
+        for i, j, (K, L, T, items) in _round_merge(times):
+            n, a = ranges[j][2][0]
+            ms = times[j][K, L, T, items][0]
+            entries.append(dict(prec=prec, n_min=n_min, act_min=ranges[i][0], act_max=ranges[j][1], K=K, L=L, T=T,
+                                WG=WG, items=items, ms=round(ms, 5), rep_n=n, rep_n_active=a,
+                                gint=round(a * n / ms / 1e6, 2)))
+        entries += kept
+    return entries
+
+
 # Shapes of the batched force kernel (L = 0: scalar j-path)
 BATCH_SHAPES = [(1, 1), (1, 4), (1, 16), (1, 64), (2, 1), (2, 4), (2, 16), (1, 0), (2, 0)]
 # kind 1 (nbody_forces_batch) keys: mean active rows per system, timed on
@@ -418,12 +549,18 @@ def tune_batch_steps(ctx, precisions=("fp64", "mixed", "mixed_ds"), buckets=STEP
     return entries
 
 
-def forces_source_hash():
-    """sha256 of the force kernels' source the table was measured on."""
+def forces_source_hash(files=("forces.hip",)):
+    """sha256 of the source the table was measured on: the force kernels, or
+    with KERNEL_SOURCES also the work queue and the argument structures."""
     import hashlib
-    src = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc", "forces.hip")
-    with open(src, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+    h = hashlib.sha256()
+    for name in files:
+        with open(os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc", name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
+
+
+KERNEL_SOURCES = ("forces.hip", "work_queue.h", "nb_internal.h")
 
 
 def save(entries, path, meta=None):
@@ -463,7 +600,7 @@ def load(ctx, path=DEFAULT_TABLE):
 
 def main():
     ap = argparse.ArgumentParser()
-    ap.add_argument("--n", type=int, nargs="+", default=[65536, 262144])
+    ap.add_argument("--n", type=int, nargs="+", default=None, help="system sizes to tune (default: 65536 262144)")
     ap.add_argument("--prec", nargs="+", default=["fp64", "mixed", "mixed_ds"])
     ap.add_argument("--out", default=os.environ.get("NB_TUNE_CACHE") or "tuning.json",
                     help="table to write (default: $NB_TUNE_CACHE, else tuning.json)")
@@ -471,12 +608,17 @@ def main():
     ap.add_argument("--max-active", type=int, default=0,
                     help="largest active-set bucket to time (0: up to N); the top bucket's range then covers every larger count")
     ap.add_argument("--append", default="", help="start from the entries of this table")
+    ap.add_argument("--rounds", action="store_true",
+                    help="retune the tables in whole rounds (those of --n, else all), starting from --append "
+                         "(default: the shipped table); this made the shipped table's entries with rep_n")
     ap.add_argument("--batch", action="store_true", help="also tune the batched kernel (nbody_forces_batch)")
     ap.add_argument("--batch-steps", action="store_true", help="also tune the batched block steps")
     ap.add_argument("--batch-only", action="store_true", help="tune only the batched kernel (no --n sweep)")
     ap.add_argument("--batch-forces-only", action="store_true",
                     help="retune only the batched kernel's entries (nbody_forces_batch); keep every other entry")
     args = ap.parse_args()
+    if args.n is None:
+        args.n = [] if args.rounds else [65536, 262144]
     sys.path.insert(0, os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
     import paper_1409_5474_amd as nb
     ctx = nb.Context(0, "fp64", load_tuning=False)
@@ -493,9 +635,22 @@ def main():
         # the table so far, after every stage (a long run keeps what it finished)
         save(entries, args.out, meta={"device": props.name, "gcn_arch": getattr(props, "gcnArchName", ""),
                                       "cus": props.multi_processor_count, "seconds": round(time.time() - t0, 1),
-                                      "forces_hip_sha256": forces_source_hash()})
+                                      "forces_hip_sha256": forces_source_hash(),
+                                      "kernel_sources_sha256": forces_source_hash(KERNEL_SOURCES)})
 
-    if args.batch_only:
+    if args.rounds:
+        args.append = args.append or DEFAULT_TABLE
+        with open(args.append) as f:
+            entries = json.load(f)["entries"]
+        load(ctx, args.append)
+        for n in [n for n in ROUND_TABLES if n in args.n] or list(ROUND_TABLES):
+            old = [e for e in entries if e.get("kind", 0) == 0 and e["n_min"] == n]
+            new = tune_rounds(ctx, n, ROUND_TABLES[n], old, args.prec, log=say)
+            entries = [e for e in entries if not (e.get("kind", 0) == 0 and e["n_min"] == n and e["prec"] in args.prec)]
+            entries = new + entries
+            checkpoint()
+            print(f"# table from N={n} done after {time.time() - t0:.0f} s", flush=True)
+    elif args.batch_only:
         entries = [e for e in entries if e.get("kind", 0) == 0]
     elif args.batch_forces_only:
         args.batch = True

@@ -152,6 +152,26 @@ def test_entries_of_a_small_system_start_above_its_own_launch():
     assert at._small_n_min(2048, [9.0], [9.0]) == 4097
 
 
+def test_round_ranges_pick_and_merge():
+    from paper_1409_5474_amd import autotune as at
+    for points in at.ROUND_TABLES.values():
+        r = at._round_ranges(points)
+        assert r[0][0] == 0 and r[-1][1] == 2 ** 31 - 1 and all(a[1] + 1 == b[0] for a, b in zip(r[:-1], r[1:]))
+        for lo, hi in r:
+            counts = at._round_counts(lo, hi, points)
+            assert counts and all(max(lo, 1) <= a <= min(hi, n) for n, a in counts)
+    # the present entries' starts stay, so a range lies within one of them
+    r = at._round_ranges((65536, 150000), [0, 3, 512, 2048])
+    assert {512, 2048} < {lo for lo, _ in r} and not {513, 2049} & {lo for lo, _ in r}
+    A, B, C = (1, 4, 256, 512), (2, 0, 256, 512), (1, 4, 256, 1024)
+    # a family shape within 2 % goes before the fastest, and fewer partial sums before 0.7 %
+    assert at._round_pick({A: [1.01, 1.01], B: [1.0, 1.0]}) == A
+    assert at._round_pick({A: [1.03, 1.03], B: [1.0, 1.0]}) == B
+    assert at._round_pick({A: [1.005], C: [1.0]}) == A and at._round_pick({A: [1.01], C: [1.0]}) == C
+    # neighbours share an entry within 1.5 % of each one's own
+    assert at._round_merge([{A: [1.0], C: [1.1]}, {A: [2.02], C: [2.0]}, {A: [3.2], C: [3.0]}]) == [(0, 1, A), (2, 2, C)]
+
+
 @pytest.mark.gpu
 def test_tuning_a_small_system_keeps_its_launch(tmp_path):
     import torch
