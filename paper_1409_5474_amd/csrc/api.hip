@@ -788,7 +788,6 @@ int devcount_forces(nb_ctx* c, const double* pos, const double* vel, const doubl
     a.pos = pos; a.vel = vel; a.mass = mass; a.n = N;
     a.active = active; a.n_active = max_active; a.n_active_dev = n_active_dev;
     a.eps2 = eps2; a.S = 1; a.acc = acc; a.jerk = jerk; a.pot = pot;
-    a.wq = c->wq;
     a.row_lo = 0; a.row_hi = N; a.err = c->wq + nb::kErrorWord;
     hipError_t e = nb::launch_forces_small(c->prec, mask, a, step, c->stream);
     return e == hipSuccess ? NB_OK : hip_fail(c, e, "small force launch (device count)");
@@ -1225,18 +1224,21 @@ int nb_block_step(nb_ctx* c, int64_t N, double eps2, double eta, double dt_max, 
   if (rc) return rc;
   const double dt_min = std::ldexp(dt_max, -max_level);
   phase_mark(c, 0);
+  // a small system's step reads its count from the caller's sched (the low
+  // word of the 64-bit count), so it shares no memory of the context
+  const bool small = takes_small(c, N, N, false);
+  const int32_t* count = small ? reinterpret_cast<const int32_t*>(sched + 1) : c->nact32;
   // schedule and predict (the predictor runs in the scheduler's last pass)
   const nb::PredictArgs pred{pos, vel, acc, jerk, dt_min, pos_p, vel_p};
   hipError_t e = nb::launch_schedule(t_tick, dt_level, N, max_level, active, sched, c->sched_tmp, c->sched_cnt,
-                                     c->nact32, t_stop_tick, c->stop_dev, c->stream, &pred,
-                                     takes_small(c, N, N, false) ? c->wq : nullptr);
+                                     small ? nullptr : c->nact32, t_stop_tick, c->stop_dev, c->stream, &pred);
   if (e != hipSuccess) return hip_fail(c, e, "schedule launch");
   phase_mark(c, 1);
   const nb::StepArgs st{pos_p, vel_p, pos, vel, acc, jerk, t_tick, dt_level, eta, dt_max, max_level,
                         reinterpret_cast<unsigned long long*>(sched + 3),
                         reinterpret_cast<unsigned long long*>(sched + 2)};
   nb::ForceArgs red{};
-  rc = devcount_forces(c, pos_p, vel_p, mass, N, active, c->nact32, N, eps2, acc1, jerk1, pot1, false, &red, &st);
+  rc = devcount_forces(c, pos_p, vel_p, mass, N, active, count, N, eps2, acc1, jerk1, pot1, false, &red, &st);
   if (rc) return rc;
   phase_mark(c, 2);
   if (red.n > 0) {

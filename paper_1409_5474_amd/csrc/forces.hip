@@ -936,8 +936,6 @@ __global__ __launch_bounds__(64 * W) void k_forces_small(ForceArgs a, StepArgs s
     const int64_t d = *a.n_active_dev;
     n_act = d < n_act ? (d < 0 ? 0 : d) : n_act;
   }
-  // the scheduler stepped the in-flight word; a block beyond the rows steps it back
-  if (STEP && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) flight_end(a.wq);
   if (STEP && s.step_dev && n_act > 0 && blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(s.step_dev, 1ull);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int slot = lane / kSmallL, sub = lane % kSmallL;
@@ -1990,7 +1988,6 @@ hipError_t launch_forces_small(int prec, bool mask, const ForceArgs& a, const St
   int64_t grid = (a.n_active + kSmallRows - 1) / kSmallRows;
   if (grid > 4096) grid = 4096;
   if (grid < 1) grid = 1;
-  if (s) ++grid;  // a block for the in-flight word
   const bool wide = a.n > kSmallNarrow;
 #define NB_SMALL(P)                                                                                   \
   (wide ? (mask ? launch_small_p<P, true, 8>(a, s, (int)grid, st) : launch_small_p<P, false, 8>(a, s, (int)grid, st)) \

@@ -12,7 +12,6 @@
 // described in nbody.h.
 #include "nb_internal.h"
 #include "hermite_step.h"
-#include "work_queue.h"
 
 namespace nb {
 namespace {
@@ -253,14 +252,7 @@ __global__ __launch_bounds__(kSchedOneThreads) void k_sched_one(const int64_t* _
                                                                 int64_t* __restrict__ sched,
                                                                 int32_t* __restrict__ n_active32, int64_t t_stop_host,
                                                                 const int64_t* __restrict__ t_stop_dev,
-                                                                PredictArgs pred, unsigned int* wq) {
-  // with a queue, the last block steps its in-flight word (the fused force and
-  // corrector kernel of a small system steps it back)
-  const unsigned int nblk = gridDim.x - (wq ? 1 : 0);
-  if (blockIdx.x == nblk) {
-    if (threadIdx.x == 0) flight_begin(wq);
-    return;
-  }
+                                                                PredictArgs pred) {
   constexpr int W = kSchedOneThreads / 64;
   __shared__ int64_t wbuf[W];
   __shared__ int wc[kSchedOneOwn / 64];
@@ -293,7 +285,7 @@ __global__ __launch_bounds__(kSchedOneThreads) void k_sched_one(const int64_t* _
   }
   if (flag) active[off + rank] = (int32_t)i;
   if (pred.pos) predict_range(pred, t_tick, base, kSchedOneOwn, n, t_next, kSchedOneThreads);
-  if (blockIdx.x == nblk - 1 && t == 0) {
+  if (blockIdx.x == gridDim.x - 1 && t == 0) {
     off += total;
     const int64_t t_stop = t_stop_dev ? *t_stop_dev : t_stop_host;
     const int64_t cnt = t_next <= t_stop ? off : 0;
@@ -423,13 +415,11 @@ int schedule_blocks(int64_t n) {
 
 hipError_t launch_schedule(const int64_t* t_tick, const int32_t* level, int64_t n, int max_level, int32_t* active,
                            int64_t* sched, int64_t* block_min, int32_t* block_cnt, int32_t* n_active32,
-                           int64_t t_stop, const int64_t* t_stop_dev, hipStream_t st, const PredictArgs* pred,
-                           unsigned int* wq) {
+                           int64_t t_stop, const int64_t* t_stop_dev, hipStream_t st, const PredictArgs* pred) {
   const PredictArgs p = pred ? *pred : PredictArgs{};
   if (n <= kSchedOneMax) {
-    const unsigned int nblk = (unsigned int)((n + kSchedOneOwn - 1) / kSchedOneOwn);
-    hipLaunchKernelGGL(k_sched_one, dim3(nblk + (wq ? 1 : 0)), dim3(kSchedOneThreads), 0, st, t_tick, level, n,
-                       max_level, active, sched, n_active32, t_stop, t_stop_dev, p, wq);
+    hipLaunchKernelGGL(k_sched_one, dim3((unsigned)((n + kSchedOneOwn - 1) / kSchedOneOwn)), dim3(kSchedOneThreads), 0,
+                       st, t_tick, level, n, max_level, active, sched, n_active32, t_stop, t_stop_dev, p);
     return hipGetLastError();
   }
   const int nblk = schedule_blocks(n);

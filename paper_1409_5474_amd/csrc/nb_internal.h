@@ -302,11 +302,10 @@ struct PredictArgs {
   double* pos_p;
   double* vel_p;
 };
-// wq (one-launch scheduler only): its in-flight word is stepped.
 hipError_t launch_schedule(const int64_t* t_tick, const int32_t* level, int64_t n, int max_level,
                            int32_t* active, int64_t* sched, int64_t* block_min, int32_t* block_cnt,
                            int32_t* n_active32, int64_t t_stop, const int64_t* t_stop_dev, hipStream_t st,
-                           const PredictArgs* pred = nullptr, unsigned int* wq = nullptr);
+                           const PredictArgs* pred = nullptr);
 int schedule_blocks(int64_t n);
 hipError_t launch_energy(const double* pos, const double* vel, const double* mass, const double* pot,
                          int64_t n, double* part, double* out, hipStream_t st);

@@ -32,8 +32,8 @@
 //
 // The in-flight word lets nb_sync see calls that overlapped on the device also
 // where their launches touch no counter.  What such calls share is written by
-// one kernel and read by the next (the partial sums of a j-split, a small
-// block step's active count), so the first steps the word (wrapping increment
+// one kernel and read by the next (the partial sums of a j-split and how many
+// there are), so the first steps the word (wrapping increment
 // of limit 1: 0 becomes 1, anything else 0) and the last steps it back
 // (wrapping decrement: 1 becomes 0, 0 becomes kOverlapped, n becomes n - 1).
 // One call after another leaves 0.  Two first steps without a step back
@@ -42,9 +42,9 @@
 // far above 1, and from there a call leads to 0 and then to kOverlapped.
 // Neither step returns a value, and both are made early, by workgroups or
 // wavefronts without other work: a wavefront's later loads, and the end of the
-// kernel, wait for an atomic's completion (made by workgroup 0 of a small
-// system's force kernel they cost a block step 0.6 us, MI355X; as they are,
-// 0.1 us).
+// kernel, wait for an atomic's completion (made by a working workgroup they
+// cost a launch 0.6 to 1.1 us, MI355X).  Calls of small systems
+// (k_forces_small) share nothing, and do not step the word.
 #pragma once
 #include "nb_internal.h"
 
