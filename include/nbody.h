@@ -109,7 +109,8 @@ int nb_set_stream(nb_ctx *ctx, void *hip_stream);
  * NB_EINVAL (message in nb_last_error) once for any such entries and clears
  * the bit; NB_OK otherwise; NB_EDEVICE on a failed synchronisation.
  * It also checks the context's work-queue words, which every force call
- * leaves at zero: non-zero words mean that calls overlapped on the
+ * leaves at zero: non-zero words mean that calls which share its memory
+ * (all but those of up to 4096 particles) overlapped on the
  * device (see the conventions above).  They are then cleared, so later calls
  * are correct again, and NB_EINVAL reports that results since the last
  * nb_sync cannot be trusted. */
@@ -153,16 +154,20 @@ const char *nb_version(void);
  * configuration the context would use for (N, n_active) (T and WG may be
  * NULL).  Up to 4096 particles without a tuned entry or a forced
  * configuration one launch computes whole rows (no j-split); it is
- * reported as the shape whose sums it forms, K = 1, L = 16, S = 1.  Errors: NB_EINVAL for values outside the ranges above,
- * NB_ENOTSUP for a combination the library does not build. */
+ * reported as K = 1, L = 16, S = 1, the shape whose pairs and float sums it
+ * forms.  It adds the tiles' double sums in another order, so forcing that
+ * shape agrees to their rounding, not bit for bit.  Errors: NB_EINVAL for
+ * values outside the ranges above, NB_ENOTSUP for a combination the library
+ * does not build. */
 int nb_set_launch(nb_ctx *ctx, int K, int L, int S, int T, int WG);
 int nb_get_launch(nb_ctx *ctx, int64_t N, int64_t n_active, int *K, int *L, int *S, int *T, int *WG);
 /* Install one entry of the automatic table: for this precision, N >= n_min
  * and n_active in [act_min, act_max], use the shape (K, L, T, WG), and
  * choose S for about `items` work items (i-blocks x j-subsets; 0 = 4 per
- * resident workgroup): the split at or just above the target whose items
- * share out over the compute units more evenly, at most one j-tile per
- * subset.  The same entry drives host-count and
+ * resident workgroup): of the two splits around the target the one with
+ * fewer rounds of items over the compute units per subset, the smaller on a
+ * tie; every subset holds at least one j-tile, and more i-blocks than `items`
+ * are not split.  The same entry drives host-count and
  * device-count launches, so both split the work identically.  Later
  * entries take precedence on their range.  An entry with n_min <= 4096
  * switches the small-system launch off, for every active count, from n_min

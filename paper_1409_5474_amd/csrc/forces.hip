@@ -453,8 +453,9 @@ struct MixedDS {
 
 // The j-axis of n particles cut into S chunks of whole tiles, as even as
 // tiles allow: the first `extra` chunks hold base + 1 tiles, the others base.
-// The queue hands out the longer chunks first, so the compute units end
-// within about a tile of each other.  Chunks of one common length made the
+// The queue's items are chunk-major and its ranges contiguous, so the longer
+// chunks lie in the ranges of the first XCDs; those end later by up to a tile
+// per item, and the other XCDs take their last items.  Chunks of one common length made the
 // last ones short or empty: FP64 with N = 40009 all active cuts 157 tiles
 // into 19 chunks of 8 or 9 instead of 18 of 9 (1841 -> 1775 us with the split
 // rule below, MI355X).
@@ -473,7 +474,11 @@ struct Chunks {
   }
 };
 
-// Compute units that share a launch's items.
+// Compute units that share a launch's items: those of the whole chip.  On a
+// partition of it the rule below still gives a split within one of the target,
+// but the rounds it compares are not that partition's; a constant, because
+// device-count kernels evaluate the rule in every workgroup and a division by
+// it is a shift.
 constexpr int kShare = 256;
 
 // The j-split chosen on the device (device-count mode) and on the host

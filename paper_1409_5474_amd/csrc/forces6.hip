@@ -15,9 +15,10 @@
 // enters once per component, in the accumulating multiply-add, 55 double
 // instructions per pair besides the reciprocal square root instead of 66.
 //
-// All arithmetic is double precision and the kernel is bound by it: 131072
-// all active run at 563 G pairs/s (474 G with the recursive form), 65 issue
-// slots of a SIMD per pair where the pair's instructions need 58.
+// All arithmetic is double precision and the kernel is bound by it: 262144
+// all active run at 555 to 563 G pairs/s (474 G with the recursive form).  A
+// wavefront issues 56 vector instructions per pair in 61 quad-cycles of its
+// SIMD, 91% of them busy (counters, MI355X; 66 and 86% in the recursive form).
 // Layout as the LDS path of the fourth-order kernel: j-tiles of kTile
 // particles staged in LDS as five double2 streams (x y | z m | vx vy | vz ax |
 // ay az), one or four lanes per i-particle, the j-range cut into S chunks over

@@ -240,7 +240,9 @@ __global__ __launch_bounds__(kB) void k_sched_write(const int64_t* __restrict__ 
 // other blocks, then compacts and predicts its own kSchedOneOwn particles.
 // Same t_next, same ascending active list, same predicted state as the
 // two-kernel form.  3899 particles: 6.5 us in a trace; one workgroup for
-// everything took 15.7 us, most of it predicting on one compute unit.
+// everything took 15.7 us, most of it predicting on one compute unit.  At its
+// limit of 16384 the pass takes as long as the two kernels (nb_schedule issued
+// back to back: 6.7 us, and 6.4 us for 16385) and saves a block step one launch.
 constexpr int kSchedOneThreads = 1024;
 constexpr int kSchedOneReg = 16;
 constexpr int kSchedOneOwn = 256;

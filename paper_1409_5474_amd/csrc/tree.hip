@@ -25,11 +25,13 @@
 // Structure on the chip: the build is data-parallel -- one thread per
 // particle, with the library's own stable radix sort and exclusive scans
 // placing the outputs, so every array keeps curve order and the results are
-// reproducible run to run.  All levels are built at once; the level bounds
+// reproducible run to run.  (Few particles are sorted by counting each key's
+// place instead.)  All levels are built at once; the level bounds
 // stay in device memory and the buffers are sized from bounds known up front,
 // so nothing is read on the host until the forces are written and a whole
-// evaluation can be captured in a graph.  The walk and the force evaluation are one kernel, as in the
-// paper's GPU tree code: one wavefront per group walks the tree for its 64
+// evaluation can be captured in a graph.  The walk and the force evaluation are
+// one kernel, as in the paper's GPU tree code: one wavefront per group, or a
+// team of eight while groups are few, walks the tree for the group's 64
 // particles and evaluates accepted cells and opened leaves 64 at a time from
 // LDS as it finds them, so no interaction list is written to memory.  The
 // build and the walk are double precision; the force terms are double or
@@ -1150,8 +1152,8 @@ __global__ __launch_bounds__(kGS) void k_tree_walk_forces(WalkArgs a) {
 // evaluate the last pair.  The partial sums are added in wavefront order.
 // Up to kTeamChunks chunks of 64 per compute unit (131072 particles on 256):
 // whole evaluations in us, one wavefront per group and teams, double / mixed:
-// 10007: 648 / 615 and 377 / 315; 65536: 998 / 871 and 803 / 634; 131072: 1431 /
-// 1079 and 1294 / 1059; 262144: 2378 / 1685 and 2402 / 1926.
+// 10007: 562 / 500 and 255 / 219; 65536: 924 / 823 and 734 / 578; 131072: 1366 /
+// 1062 and 1251 / 1016; 262144: 2310 / 1625 and 2354 / 1886 (MI355X).
 constexpr int kTeamChunks = 8;
 constexpr int kTeam = 8;
 constexpr int kTeamStack = 2048;                  // stack entries in LDS
@@ -1281,7 +1283,9 @@ __global__ __launch_bounds__(kTeam * kGS) void k_tree_walk_team(WalkArgs a) {
 // per lane; its sixteen wavefronts each compare a sixteenth of all keys, read at a
 // wave-uniform index through the scalar cache.  n^2 / 64 wavefront steps of a
 // compare and an add-with-carry, one launch: 10007 keys take 21 us, where the
-// 24 launches of eight radix passes took 140.
+// 24 launches of eight radix passes took 140.  The line lies where the count
+// still wins: whole evaluations of 16384 particles (counted) and 16385 (16
+// launches of radix passes) take 295 and 342 us in double, 245 and 310 mixed.
 constexpr int kRankThreads = 1024;
 constexpr int32_t kRankMax = 16384;
 
