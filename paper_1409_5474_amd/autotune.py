@@ -584,18 +584,35 @@ def table_path():
     return DEFAULT_TABLE if os.path.exists(DEFAULT_TABLE) else None
 
 
+# The last table read: (the file's path and state, its entries).  Every context
+# installs a table, and reading it takes longer than the rest of a context's
+# creation; one that is rewritten is read again.
+_last_table = (None, None)
+
+
+def _table_entries(path):
+    global _last_table
+    st = os.stat(path)
+    state = (os.path.abspath(path), st.st_ino, st.st_size, st.st_mtime_ns)
+    held, entries = _last_table
+    if held != state:
+        with open(path) as f:
+            entries = json.load(f)["entries"]
+        _last_table = (state, entries)
+    return entries
+
+
 def load(ctx, path=DEFAULT_TABLE):
     """Install a saved table into a context (entries in file order)."""
-    with open(path) as f:
-        doc = json.load(f)
-    single = [e for e in doc["entries"] if e.get("kind", 0) == 0]
+    entries = _table_entries(path)
+    single = [e for e in entries if e.get("kind", 0) == 0]
     for e in sorted(single, key=lambda e: e["n_min"]):
         ctx.tune_add(e["prec"], e["n_min"], e["act_min"], e["act_max"], e["K"], e["L"], e["items"],
                      e.get("T", 0), e.get("WG", 0))
-    for e in doc["entries"]:
+    for e in entries:
         if e.get("kind", 0) in (1, 2):
             ctx.tune_add_batch(e["prec"], e["kind"], e["key_min"], e["key_max"], e["K"], e["L"])
-    return len(doc["entries"])
+    return len(entries)
 
 
 def main():

@@ -32,6 +32,38 @@ def test_save_and_load_order(tmp_path):
     assert json.load(open(p))["meta"]["device"] == "test"
 
 
+def test_a_table_is_read_once_until_it_changes(tmp_path, monkeypatch):
+    # a process makes many contexts from one table; a rewritten or another
+    # table is read again
+    from paper_1409_5474_amd import autotune as at
+    reads = []
+    real = json.load
+    monkeypatch.setattr(at.json, "load", lambda f: reads.append(f.name) or real(f))
+
+    class FakeCtx:
+        def __init__(self):
+            self.calls = []
+
+        def tune_add(self, *a):
+            self.calls.append(a)
+
+    def entry(K):
+        return dict(prec="mixed", n_min=65536, act_min=0, act_max=10, K=K, L=1, items=0)
+
+    def loaded(path):
+        c = FakeCtx()
+        at.load(c, str(path))
+        return [a[4] for a in c.calls]
+
+    p, q = tmp_path / "p.json", tmp_path / "q.json"
+    at.save([entry(1)], str(p))
+    at.save([entry(2), entry(4)], str(q))
+    assert loaded(p) == [1] and loaded(p) == [1] and len(reads) == 1
+    assert loaded(q) == [2, 4] and loaded(q) == [2, 4] and len(reads) == 2
+    at.save([entry(3)], str(q))
+    assert loaded(q) == [3] and loaded(p) == [1] and len(reads) == 4
+
+
 def test_table_path_follows_nb_tune_cache(tmp_path, monkeypatch):
     from paper_1409_5474_amd import autotune as at
     monkeypatch.delenv("NB_TUNE_CACHE", raising=False)
