@@ -50,8 +50,8 @@
  *    the order of the sums only), and a call that cannot (a forced launch, the
  *    scalar-path mirror, a batch) fails with NB_ENOMEM before anything is launched, leaving every
  *    output untouched.  The tree
- *    code keeps its own buffers (about 200 bytes per particle plus its
- *    interaction lists), which the cap does not cover.
+ *    code keeps its own buffers (about 500 bytes per particle with n_crit =
+ *    16, and up to 180 MB of walk stacks), which the cap does not cover.
  *  - NB_LOG, read by nb_create: 1 prints every error a call on the context
  *    returns (the nb_last_error text with its code) to stderr; 2 also prints
  *    each launch shape the host chooses (K, L, S, T, WG, work items, and the
