@@ -108,12 +108,14 @@ int nb_set_stream(nb_ctx *ctx, void *hip_stream);
  * memory, so no call has to copy active_idx to the host.  Returns
  * NB_EINVAL (message in nb_last_error) once for any such entries and clears
  * the bit; NB_OK otherwise; NB_EDEVICE on a failed synchronisation.
- * It also checks the context's work-queue words, which every force call
- * leaves at zero: non-zero words mean that calls which share its memory
- * (all but those of up to 4096 particles) overlapped on the
+ * It also checks the context's work-queue words, which every call leaves at
+ * zero: non-zero words mean that calls overlapped on the
  * device (see the conventions above).  They are then cleared, so later calls
  * are correct again, and NB_EINVAL reports that results since the last
- * nb_sync cannot be trusted. */
+ * nb_sync cannot be trusted.  Fourth-order force calls and block steps of
+ * more than 4096 particles always use these words (smaller ones share no
+ * memory of the context); sixth-order and tree calls only with more work
+ * items than workgroups. */
 int nb_sync(nb_ctx *ctx);
 
 /* The same range test on a host array: NB_OK when every active[k], k <

@@ -212,8 +212,6 @@ __device__ __forceinline__ void run_items6(Tile6& tile, unsigned int& slot, cons
   const int64_t n_iblk = (n_act + IB - 1) / IB;
   const int64_t items = n_iblk * S;
   const int64_t clen = chunk6(a.n, S);
-  const bool flight = a.n_active_dev || S > 1;  // k_reduce6 follows
-  if (flight) flight_begin_beside(a.wq, items);
   if (!queue_member(items)) return;
   int64_t w = queue_first(a.wq, items);
   while (w < items) {
@@ -224,7 +222,7 @@ __device__ __forceinline__ void run_items6(Tile6& tile, unsigned int& slot, cons
     item6<L, MASK>(tile, a, jb, je, n_act, iblk * IB, S == 1, a.part + chunk * kC6 * n_act);
     w = queue_next(a.wq, slot, items, w + gridDim.x);
   }
-  queue_done(a.wq, items, flight);
+  queue_done(a.wq, items);
 }
 
 __device__ __forceinline__ int64_t active_count6(const Force6Args& a) {
@@ -249,18 +247,14 @@ __global__ __launch_bounds__(kWG6) void k_forces6(Force6Args a) {
 // Fixed-order sum of the S partial blocks, self-term removal, output.
 __global__ __launch_bounds__(256) void k_reduce6(Force6Args a) {
   const int64_t n_act = active_count6(a);
-  if (blockIdx.x == 0) {  // no outputs: the in-flight word
-    if (threadIdx.x == 0) flight_end(a.wq);
-    return;
-  }
   const int S = split6(n_act, a.slots, a.target_items, a.n).S;
   if (S <= 1) return;
   const int64_t total = kC6 * n_act;
   const int g = chunk_lanes(S);
   const int lg = __builtin_ctz(g);
   const int lane = threadIdx.x & (g - 1);
-  for (int64_t idx = ((int64_t)(blockIdx.x - 1) * blockDim.x + threadIdx.x) >> lg; idx < total;
-       idx += ((int64_t)(gridDim.x - 1) * blockDim.x) >> lg) {
+  for (int64_t idx = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> lg; idx < total;
+       idx += ((int64_t)gridDim.x * blockDim.x) >> lg) {
     const int64_t c = idx / n_act;
     const int64_t k = idx - c * n_act;
     const double s = sum_blocks(a.part + c * n_act + k, kC6 * n_act, S, lane, g);
@@ -324,7 +318,6 @@ hipError_t launch_forces6(const Force6Args& a, bool mask, int grid, hipStream_t 
   int64_t rg = (threads + 255) / 256;
   if (rg > 4096) rg = 4096;
   if (rg < 1) rg = 1;
-  ++rg;  // block 0: the in-flight word
   hipLaunchKernelGGL(k_reduce6, dim3((int)rg), dim3(256), 0, st, a);
   return hipGetLastError();
 }
