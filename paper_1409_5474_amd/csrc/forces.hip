@@ -528,15 +528,15 @@ __device__ __forceinline__ int64_t checked_row(const int32_t* active, int64_t k,
   return -1;
 }
 
-// Placement of the loop that follows: its first instruction lies 20 bytes past
-// a 32-byte boundary.  The FP64 two-row pair loop, 908 bytes of mostly 8-byte
-// instructions, takes 1.74 ms for 40009 all active there (MI355X), 1.75 ms 4
-// bytes past one, 1.80 ms on one or 16 bytes past it; unpinned, every change to
-// the kernel before it moved it.
-template <bool ON>
-__device__ __forceinline__ void pin_loop() {
-  if constexpr (ON) asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
-}
+// Placement of the loop that follows: its first instruction lies 12 bytes past a
+// 32-byte boundary.  The pair loops are a few hundred bytes of mostly 8-byte
+// instructions, and their speed depends on it by up to 5%; unpinned, every
+// change to the kernel before them moved them.  12 bytes past is the best or
+// within 1% of it for every shape (MI355X; 4, 12, 20 and 28 past were timed:
+// mixed (2, 4), 4096 of 65536: 210, 199, 200, 201 us; mixed_ds (1, 4): 205, 200,
+// 199, 205).  The FP64 (2, 1) loop is up to 3% faster or slower 20 past with the
+// split (40009 all active: 1785 and 1762 us; 38463: 1638 and 1696 us).
+__device__ __forceinline__ void pin_loop() { asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0"); }
 
 // Shared body: one workgroup processes one (i-block, j-chunk) item.
 // Outputs: final rows (acc/jerk/pot at out_row0 + k) when `final_out`,
@@ -588,7 +588,7 @@ __device__ __forceinline__ void process_item(typename P::template JTileT<T>& til
     if (nb < jend) nxt = P::load(pos, vel, mass, nb + t, t < T && nb + t < jend);
 #pragma unroll 1
     for (int jb = 0; jb < T; jb += RUN * L) {
-      pin_loop<K == 2 && L == 1 && sizeof(typename P::T) == 8>();
+      pin_loop();
 #pragma unroll NB_JJ_UNROLL
       for (int jj = jb + sub; jj < jb + RUN * L; jj += L) P::template pair_tile<MASK>(tile, jj, I, e2, A, K);
       if constexpr (RUN < PER) {
